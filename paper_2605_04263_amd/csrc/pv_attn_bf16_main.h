@@ -24,7 +24,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     const uint16_t* __restrict__ krot, const uint16_t* __restrict__ vt,
     const float2* __restrict__ cs, void* __restrict__ out, float* __restrict__ lse, int hq, int hkv,
     float qscale, bool rope, bool out_f32, int split, float* __restrict__ part, KvSource raw_kv,
-    float scale, int n_short_blocks) {
+    float scale, int n_short_blocks, int order) {
   constexpr int KT = D / 16;            // MFMA steps along the feature dim for S^T
   constexpr int DB = D / 32;            // 32-feature blocks of O^T
   constexpr int CH32 = 32 * D / 8;      // 16-byte chunks per 32-key K (or V^T) slot
@@ -79,7 +79,8 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   } else {
     kvh = item % hkv;
     head = kvh * G + wave;
-    tile = reinterpret_cast<const QTile*>(plan + (split ? h.off_segwork : h.off_work))[item / hkv];
+    tile = reinterpret_cast<const QTile*>(
+        plan + (split ? h.off_segwork : h.off_work))[dispatch_rank(item / hkv, h.n_q_tiles, order)];
     mine = tile;
   }
   const bool valid = qrow < mine.rows;
@@ -102,9 +103,6 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     if (hh == 0) reinterpret_cast<float2*>(part_o + 32 * D)[qrow] = make_float2(0.0f, 0.0f);
     return;
   }
-  // the plan lists the longest items first: they bound the run time, so their waves go first
-  // wherever they share a SIMD with a shorter item
-  if (blockIdx.x < gridDim.x / 4) __builtin_amdgcn_s_setprio(3);
   const int64_t head_base = ((int64_t)kvh * h.padded_keys + tile.kpad_base) * D;   // elements
   auto step_key0 = [&](int j) {           // first key (request-local) of step j
     const int idx = (j >> 1) + kt0;
@@ -795,14 +793,15 @@ hipError_t launch_main(const int32_t* plan, const PlanHeader& h, const uint16_t*
   dim3 grid;
   const int64_t blocks = (split ? (int64_t)h.n_seg_tiles * hkv * split : (int64_t)h.n_q_tiles * hkv) + n_short;
   if (!grid_1d(blocks, G * 64, &grid)) return hipErrorInvalidConfiguration;
+  const int order = split ? 0 : dispatch_order(h.n_q_tiles, hkv, G);
   if (rope)
     k_attn_bf16<D, G, true><<<grid, dim3(G * 64), 0, s>>>(plan, h, q, krot, vt, cs, out, lse, hq, hkv,
                                                           qscale, rope, out_f32, split, part, raw_kv, scale,
-                                                          n_short);
+                                                          n_short, order);
   else
     k_attn_bf16<D, G, false><<<grid, dim3(G * 64), 0, s>>>(plan, h, q, krot, vt, cs, out, lse, hq, hkv,
                                                            qscale, rope, out_f32, split, part, raw_kv, scale,
-                                                           n_short);
+                                                           n_short, order);
   return hipGetLastError();
 }
 
@@ -818,11 +817,11 @@ hipError_t launch_query_tiles(const int32_t* plan, const PlanHeader& h, const ui
   if (rope)
     k_attn_bf16<D, 4, true, true><<<grid, dim3(256), 0, s>>>(plan, h, q, krot, vt, cs, out, lse, hq, hkv,
                                                              qscale, rope, out_f32, 0, nullptr, raw_kv, scale,
-                                                             n_short);
+                                                             n_short, 0);
   else
     k_attn_bf16<D, 4, false, true><<<grid, dim3(256), 0, s>>>(plan, h, q, krot, vt, cs, out, lse, hq, hkv,
                                                               qscale, rope, out_f32, 0, nullptr, raw_kv, scale,
-                                                              n_short);
+                                                              n_short, 0);
   return hipGetLastError();
 }
 

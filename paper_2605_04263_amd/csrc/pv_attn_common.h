@@ -68,6 +68,38 @@ __device__ __forceinline__ float2 rotary_cos_sin(int pos, double inv_freq) {
   return make_float2(__builtin_amdgcn_cosf(fr), __builtin_amdgcn_sinf(fr));
 }
 
+// Order in which a launch takes the work list (sorted longest first) when the whole grid is at most four
+// workgroups to a compute unit, two of them resident: plain longest-first then pairs the longest items
+// with each other and leaves some compute units one item more than others.  `a` tiles are one
+// workgroup for each of the 256 compute units, x = tiles beyond two for each.
+//   x <= 0, or a .. 2a     the second `a` tiles in reverse: a long first item gets a short partner
+//   0 < x <= a             the x shortest first (in reverse), then the middle ones: the slots they free
+//                          early take the middle ones, and no compute unit gets a fourth item
+//   x > 2a                 longest first as listed
+// Measured (32/8 heads, launch of the main kernel, us, longest first / this order, bf16; FP8): 0.75
+// workgroups per slot 32.3 / 30.6; 36.6 / 34.5 - 1.0: 43.5 / 41.3; 45.4 / 43.6 - 1.25: 63.6 / 62.7;
+// 63.8 / 63.5 - 1.5: 79.3 / 75.0; 77.7 / 72.1 - 1.75: 102.0 / 98.5; 100.9 / 94.5 - 2.0: 128.1 / 124.5;
+// 122.7 / 116.5 - beyond 2 within 1 % either way.
+// Returned: 0 as listed, a > 0 the second `a` reversed, -a the shortest first behind the first `a`.
+inline int dispatch_order(int n_tiles, int hkv, int G) {
+  const int a = 256 / hkv;
+  if ((G != 3 && G != 4) || a < 1) return 0;            // other group sizes: not two workgroups per unit
+  const int x = n_tiles - 2 * a;
+  if (n_tiles <= a || x > 2 * a) return 0;
+  return x > 0 && x <= a ? -a : a;
+}
+__device__ __forceinline__ int dispatch_rank(int pos, int n, int order) {
+  if (order == 0) return pos;
+  const int a = order > 0 ? order : -order;
+  if (pos < a) return pos;
+  if (order > 0) {
+    const int b = min(a, n - a);
+    return pos < a + b ? a + b - 1 - (pos - a) : pos;
+  }
+  const int x = n - 2 * a;
+  return pos < a + x ? n - 1 - (pos - a) : pos - x;
+}
+
 // s_waitcnt immediate (gfx9 encoding) that waits for vmcnt <= n only.
 __host__ __device__ constexpr int vmcnt_imm(int n) { return 0x0f70 | (n & 15) | ((n >> 4) << 14); }
 

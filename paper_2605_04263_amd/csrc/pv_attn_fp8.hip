@@ -216,7 +216,7 @@ __global__ __launch_bounds__(G * 64, 2) void k_attn_fp8(
     const uint8_t* __restrict__ kw, const uint8_t* __restrict__ vw, const float2* __restrict__ cs,
     const float* __restrict__ k_scale, const float* __restrict__ v_scale, void* __restrict__ out,
     float* __restrict__ lse, int hq, int hkv, float qscale, bool rope, bool out_f32,
-    const uint8_t* __restrict__ k8, const uint8_t* __restrict__ v8, float scale, int n_short_blocks) {
+    const uint8_t* __restrict__ k8, const uint8_t* __restrict__ v8, float scale, int n_short_blocks, int order) {
   static_assert(D == 128, "the FP8 path is built for head_dim 128");
   // The last n_short_blocks workgroups evaluate the rows with very few keys in fp32, one (row, query
   // head) per wave, from the caller's codes and the table of rotary angles: light work that starts
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(G * 64, 2) void k_attn_fp8(
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int qrow = lane & 31, hh = lane >> 5;
   const int kvh = item % hkv, head = kvh * G + wave;
-  const QTile tile = reinterpret_cast<const QTile*>(plan + h.off_work)[item / hkv];
+  const QTile tile = reinterpret_cast<const QTile*>(plan + h.off_work)[dispatch_rank(item / hkv, h.n_q_tiles, order)];
   const bool valid = qrow < tile.rows;
   const int row_l = tile.t0 + min(qrow, tile.rows - 1);    // pad lanes repeat the last row (never stored)
   const int64_t g = (int64_t)tile.tok_base + row_l;
@@ -442,7 +442,8 @@ static hipError_t launch_main_fp8(const int32_t* plan, const PlanHeader& h, cons
   if (n_short > 0x7fffffff || !grid_1d((int64_t)h.n_q_tiles * hkv + n_short, G * 64, &grid))
     return hipErrorInvalidConfiguration;
   k_attn_fp8<128, G><<<grid, dim3(G * 64), 0, s>>>(plan, h, q, kw, vw, cs, ks, vs, out, lse, hq, hkv, qscale, rope,
-                                                   out_f32, k8, v8, scale, (int)n_short);
+                                                   out_f32, k8, v8, scale, (int)n_short,
+                                                   dispatch_order(h.n_q_tiles, hkv, G));
   return hipGetLastError();
 }
 
