@@ -233,17 +233,19 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       sc[r] = __uint_as_float((__float_as_uint(sc[r]) & keep) | (0xff800000u & ~keep));
     }
   };
-  // p rounded to bf16 once; the row sum is taken over the rounded values (v_dot2c with a pair of
-  // ones), so that O is an exact convex combination of V rows with the weights the MFMA sees
+  // p rounded to bf16 once; the row sum is taken over the rounded values, unpacked again, so that O
+  // is an exact convex combination of V rows with the weights the MFMA sees.  (Four VALU operations per
+  // pair and not one v_dot2c: a dot runs on the matrix pipe.  Cycles per 32x32x16 MFMA with one exp2 and
+  // half a pack and a dot beside it 49, with the unpacked sum instead 34.)
   auto probs = [&](const f32x16& sc, unsigned (&pw)[8]) __attribute__((always_inline)) {
-    float rs = 0.0f;
+    float rs = 0.0f, rs_hi = 0.0f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       pw[e] = pack_bf16(prob(sc[2 * e]), prob(sc[2 * e + 1]));
-      rs = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[e]),
-                                           __builtin_bit_cast(bf16x2, 0x3f803f80u), rs, false);
+      rs += bf16_lo(pw[e]);
+      rs_hi += bf16_hi(pw[e]);
     }
-    return rs;
+    return rs + rs_hi;
   };
   // The window test of a step: its partial row sum `rs` must not exceed 2^40, and the running sum
   // with it must have reached 2^-40.  (The lower bound is on the total, not on the step: a step
@@ -498,7 +500,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     const int slot_ks = ST ? (PH + 2) % NS : sj + 2 >= NS ? sj + 2 - NS : sj + 2;   // (j + 2) % NS
     const bf16x8 pfa = as_bf16x8(make_uint4(p_in[0], p_in[1], p_in[2], p_in[3]));
     const bf16x8 pfb = as_bf16x8(make_uint4(p_in[4], p_in[5], p_in[6], p_in[7]));
-    float rs = 0.0f;
+    float rs = 0.0f, rs_hi = 0.0f;
     constexpr unsigned SBV = ST ? ((PH + 1) % NS) * SLOT_BYTES : 0, SBK = ST ? ((PH + 3) % NS) * SLOT_BYTES : 0;
     const unsigned sbv = ST ? 0u : (unsigned)slot_v * SLOT_BYTES, sbk = ST ? 0u : (unsigned)slot_k * SLOT_BYTES;
     // The step is 2 KT groups of one MFMA, at most one operand refill and a share of the VALU
@@ -509,6 +511,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     //   exponent argument -> exp2 -> (pair) bf16 pack -> (pair) row-sum dot,
     // each stage one group after the stage it depends on.
     constexpr int NG = 2 * KT, SPG = 16 / NG;          // groups; scores entering per group
+    constexpr int GHI = SPG == 1 ? 2 : 1;              // groups from the pack to the sum of the high halves
     constexpr int HB = KT / 4;                         // k-steps issued before the barrier
     float ea[16], ex[16];                              // exponent arguments, exponentials
     auto v_arg = [&](auto i) {
@@ -533,9 +536,8 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
         constexpr int E = decltype(e)::value;
         constexpr int GC = (2 * E + 1) / SPG;            // group after the pair's second exp2
         if constexpr (GC == GI) p_out[E] = pack_bf16(ex[2 * E], ex[2 * E + 1]);
-        if constexpr (GC + 1 == GI)
-          rs = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p_out[E]),
-                                               __builtin_bit_cast(bf16x2, 0x3f803f80u), rs, false);
+        if constexpr (GC + 1 == GI) rs += bf16_lo(p_out[E]);
+        if constexpr (GC + GHI == GI) rs_hi += bf16_hi(p_out[E]);
       });
     };
     // n-th staging instruction of this wave for a slot
@@ -670,7 +672,8 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       if constexpr (STEADY) stage_part2(std::integral_constant<int, 2 * R + 1>{});
       __builtin_amdgcn_sched_barrier(0);
     });
-    valu_group(std::integral_constant<int, NG>{});     // what is left: the last row-sum term
+    static_for<NG, NG + GHI>([&](auto g) { valu_group(g); });   // what is left: the last row-sum terms
+    rs += rs_hi;
     asm volatile("" : "+v"(rs));                      // the row sum belongs to this block
     __builtin_amdgcn_sched_barrier(0);
     if (have1) {
