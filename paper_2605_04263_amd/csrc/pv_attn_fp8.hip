@@ -43,9 +43,10 @@ __device__ __forceinline__ float fp8_byte(unsigned word, int byte) {
     default: return __builtin_amdgcn_cvt_f32_fp8((int)word, 3);
   }
 }
-// four floats -> four E4M3 codes in one dword (round to nearest even; callers keep |x| <= 448)
-__device__ __forceinline__ unsigned pack_fp8x4(float a, float b, float c, float d) {
-  int w = 0;
+// four floats -> four E4M3 codes in one dword (round to nearest even; callers keep |x| <= 448).  `old` is
+// overwritten: a dead value that already sits in the result's register saves clearing it first.
+__device__ __forceinline__ unsigned pack_fp8x4(float a, float b, float c, float d, int old = 0) {
+  int w = old;
   w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, w, false);
   w = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
   return (unsigned)w;
@@ -187,37 +188,29 @@ __device__ void short_unit_fp8(const int32_t* __restrict__ plan, const PlanHeade
 }
 
 // ---------------------------------------------------------------- main kernel
-// Staging of one step's K and V^T tiles (2 x 512 chunks of 16 bytes) through registers.  Free functions
-// on purpose: a private array captured by a lambda is not kept in registers by the compiler.
-template <int G, int CPT>
-__device__ __forceinline__ void fp8_fetch(uint4 (&st)[CPT], const uint8_t* __restrict__ kw,
-                                          const uint8_t* __restrict__ vw, int64_t off, int tid) {
-  constexpr int CH = kStepKeys * 128 / 16;
-#pragma unroll
-  for (int n = 0; n < CPT; ++n) {
-    // (threads beyond the last chunk repeat it: every register is loaded unconditionally)
-    const int x = min(tid + n * (G * 64), 2 * CH - 1);
-    st[n] = x < CH ? reinterpret_cast<const uint4*>(kw + off)[x] : reinterpret_cast<const uint4*>(vw + off)[x - CH];
-  }
+// 64 x 16 bytes straight from memory into LDS: lane l's 16 bytes at src + lane_off land at lds + 16 l.
+// Inline assembly on purpose: the compiler orders its own LDS reads behind every global->LDS load it
+// knows of, which would serialise the staging; the waits that are needed are placed by hand.
+__device__ __forceinline__ void stage_1k(const uint8_t* src, unsigned lane_off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               : : "s"(lds), "v"(lane_off), "s"(src) : "memory", "m0");
 }
-template <int G, int CPT>
-__device__ __forceinline__ void fp8_commit(const uint4 (&st)[CPT], uint4* __restrict__ buf, int tid) {
-  constexpr int CH = kStepKeys * 128 / 16;
-#pragma unroll
-  for (int n = 0; n < CPT; ++n) {
-    const int x = tid + n * (G * 64);
-    if ((2 * CH) % (G * 64) == 0 || x < 2 * CH) buf[x] = st[n];
-  }
+template <int N>
+__device__ __forceinline__ void wait_loads() {            // at most N loads of this wave outstanding
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
-template <int D, int G>
-__global__ __launch_bounds__(G * 64, 2) void k_attn_fp8(
+// QT as in the bf16 kernel: the four waves are four consecutive query tiles of one query head; `tile` is
+// the union of the four (it drives the key loop and the staging), `mine` the wave's own.
+template <int D, int G, bool QT>
+__global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) void k_attn_fp8(
     const int32_t* __restrict__ plan, PlanHeader h, const uint16_t* __restrict__ q,
     const uint8_t* __restrict__ kw, const uint8_t* __restrict__ vw, const float2* __restrict__ cs,
     const float* __restrict__ k_scale, const float* __restrict__ v_scale, void* __restrict__ out,
     float* __restrict__ lse, int hq, int hkv, float qscale, bool rope, bool out_f32,
     const uint8_t* __restrict__ k8, const uint8_t* __restrict__ v8, float scale, int n_short_blocks, int order) {
   static_assert(D == 128, "the FP8 path is built for head_dim 128");
+  static_assert(!QT || G == 4, "query-tile workgroups have four waves");
   // The last n_short_blocks workgroups evaluate the rows with very few keys in fp32, one (row, query
   // head) per wave, from the caller's codes and the table of rotary angles: light work that starts
   // when every item of the grid has been taken, in the tail of the launch.
@@ -228,22 +221,59 @@ __global__ __launch_bounds__(G * 64, 2) void k_attn_fp8(
                         unit, (int)threadIdx.x & 63);
     return;
   }
-  constexpr int TILE_BYTES = kStepKeys * D;               // 8 KB of K, the same of V^T
-  constexpr int TILE_CHUNKS = TILE_BYTES / 16;            // 512
-  constexpr int CPT = (2 * TILE_CHUNKS + G * 64 - 1) / (G * 64);   // staging chunks per thread and step
-  __shared__ uint4 smem[2][2 * TILE_CHUNKS];              // [buffer][K chunks, then V^T chunks]
+  constexpr int NS = 4;                                    // slots per ring, one key tile each
+  constexpr int TILE_BYTES = kStepKeys * D;                // 8 KB of K, the same of V^T
+  constexpr int CH = TILE_BYTES / 16;                      // 16-byte chunks of a slot
+  constexpr int NREP = (CH / 64 + G - 1) / G;              // staging instructions of a wave for one slot
+  constexpr int RS = 2 * D + 16;                           // row stride of the epilogue's transposition
+  constexpr int SMEM = (2 * NS * CH * 16 > G * 32 * RS ? 2 * NS * CH * 16 : G * 32 * RS) / 16;
+  // K ring, then V^T ring; step j lives in slot j % NS of each
+  __shared__ uint4 smem[SMEM];
 
-  const int item = (int)blockIdx.x;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int qrow = lane & 31, hh = lane >> 5;
-  const int kvh = item % hkv, head = kvh * G + wave;
-  const QTile tile = reinterpret_cast<const QTile*>(plan + h.off_work)[dispatch_rank(item / hkv, h.n_q_tiles, order)];
-  const bool valid = qrow < tile.rows;
-  const int row_l = tile.t0 + min(qrow, tile.rows - 1);    // pad lanes repeat the last row (never stored)
-  const int64_t g = (int64_t)tile.tok_base + row_l;
-  const int i_loc = valid ? tile.t0 + qrow : -1;
+  int kvh, head;
+  QTile tile, mine;
+  if constexpr (QT) {
+    head = (int)blockIdx.x % hq;
+    kvh = head / (hq / hkv);
+    tile = reinterpret_cast<const QTile*>(plan + h.off_quadwork)[(int)blockIdx.x / hq];
+    mine = tile;                                           // a wave without a tile of its own: no row, never masks
+    mine.t0 = tile.t0 + 32 * wave_s;
+    mine.rows = 0;
+    mine.n_full = 1 << 24;
+    if (32 * wave_s < tile.rows)                           // tile.n_full: index of the group's first tile
+      mine = reinterpret_cast<const QTile*>(plan + h.off_tiles)[tile.n_full + wave_s];
+  } else {
+    const int item = (int)blockIdx.x;
+    kvh = item % hkv;
+    head = kvh * G + wave;
+    tile = reinterpret_cast<const QTile*>(plan + h.off_work)[dispatch_rank(item / hkv, h.n_q_tiles, order)];
+    mine = tile;
+  }
+  const bool valid = qrow < mine.rows;
+  // pad lanes repeat the last row (never stored)
+  const int64_t g = (int64_t)tile.tok_base + tile.t0 + min((QT ? 32 * wave : 0) + qrow, tile.rows - 1);
+  const int i_loc = valid ? mine.t0 + qrow : -1;
   int a_end = 0, b_start = 0;
   if (valid) { a_end = plan[h.off_aend + g]; b_start = plan[h.off_bstart + g]; }
+
+  // ---- staging.  The key tiles of the item are [0, n_a) then [jb0, jb1), one step each.  A wave moves
+  // chunks wave * NREP .. of every slot (beyond the last chunk it repeats the last one: every wave issues
+  // the same number of loads, so the waits are constants).  Steps beyond the last repeat the last one.
+  const int n_steps = tile.n_a + (tile.jb1 - tile.jb0), last = n_steps - 1;
+  const int64_t head_base = ((int64_t)kvh * h.padded_keys + tile.kpad_base) * D;     // bytes
+  auto step_tile = [&](int j) { return j < tile.n_a ? j : tile.jb0 + (j - tile.n_a); };
+  const unsigned lane16 = (unsigned)lane * 16;
+  const unsigned smem_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)(char*)&smem[0];
+  auto stage_one = [&](const uint8_t* ring_src, unsigned ring, int j, int n) __attribute__((always_inline)) {
+    const int c = min(wave_s * NREP + n, CH / 64 - 1);
+    stage_1k(ring_src + head_base + (int64_t)step_tile(min(j, last)) * TILE_BYTES + c * 1024, lane16,
+             smem_base + ring + (unsigned)(j & (NS - 1)) * TILE_BYTES + (unsigned)c * 1024);
+  };
+  auto stage_k = [&](int j) { for (int n = 0; n < NREP; ++n) stage_one(kw, 0u, j, n); };
+  auto stage_v = [&](int j) { for (int n = 0; n < NREP; ++n) stage_one(vw, NS * TILE_BYTES, j, n); };
 
   // ---- Q: features 32 hh .. + 31 and 64 + 32 hh .. + 31 of this lane's row (the rotation pairs
   // (c, c + 64) sit in one lane), rotated, scaled by a power of two that brings the row's largest
@@ -252,11 +282,25 @@ __global__ __launch_bounds__(G * 64, 2) void k_attn_fp8(
   float c_row;                                             // exponent argument per unit of S
   {
     const uint16_t* qr = q + (caller_row(plan, h, g) * hq + head) * D;
+    uint4 raw[2][4], tab[16];
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) {
+      raw[0][v4] = reinterpret_cast<const uint4*>(qr + 32 * hh)[v4];
+      raw[1][v4] = reinterpret_cast<const uint4*>(qr + 64 + 32 * hh)[v4];
+    }
+    if (rope) {
+      const uint4* t = reinterpret_cast<const uint4*>(cs + g * (D / 2) + 32 * hh);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) tab[j] = t[j];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    stage_k(0);
+    stage_k(1);
+    __builtin_amdgcn_sched_barrier(0);
     float lo[32], hi[32];
 #pragma unroll
     for (int v4 = 0; v4 < 4; ++v4) {
-      const uint4 a = reinterpret_cast<const uint4*>(qr + 32 * hh)[v4];
-      const uint4 b = reinterpret_cast<const uint4*>(qr + 64 + 32 * hh)[v4];
+      const uint4 a = raw[0][v4], b = raw[1][v4];
       const unsigned aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -265,15 +309,16 @@ __global__ __launch_bounds__(G * 64, 2) void k_attn_fp8(
       }
     }
     if (rope) {
-      const float2* t = cs + g * (D / 2) + 32 * hh;
 #pragma unroll
       for (int j = 0; j < 32; ++j) {
-        const float2 w = t[j];
+        const uint4 w4 = tab[j / 2];
+        const float wc = __uint_as_float(j % 2 ? w4.z : w4.x), wsn = __uint_as_float(j % 2 ? w4.w : w4.y);
         const float l0 = lo[j], h0 = hi[j];
-        lo[j] = l0 * w.x - h0 * w.y;
-        hi[j] = h0 * w.x + l0 * w.y;
+        lo[j] = l0 * wc - h0 * wsn;
+        hi[j] = h0 * wc + l0 * wsn;
       }
     }
+    stage_v(0); stage_k(2); stage_v(1); stage_k(3); stage_v(2);
     float amax = 0.0f;
 #pragma unroll
     for (int j = 0; j < 32; ++j) amax = fmaxf(amax, fmaxf(fabsf(lo[j]), fabsf(hi[j])));
@@ -309,68 +354,56 @@ __global__ __launch_bounds__(G * 64, 2) void k_attn_fp8(
   for (int w = 0; w < 8; ++w) ones[w] = 0x38383838;       // 1.0 in E4M3
   float mref = -INFINITY;                                  // reference of the exponent, log2 units
 
-  const int n_steps = tile.n_a + (tile.jb1 - tile.jb0);
-  const int64_t head_base = ((int64_t)kvh * h.padded_keys + tile.kpad_base) * D;     // bytes
-  auto step_tile = [&](int j) { return j < tile.n_a ? j : tile.jb0 + (j - tile.n_a); };
-  // staging through registers: chunk x of the 2 * TILE_CHUNKS of a step (K first, then V^T)
-  uint4 st[CPT];
-  fp8_fetch<G, CPT>(st, kw, vw, head_base + (int64_t)step_tile(0) * TILE_BYTES, tid);
-  fp8_commit<G, CPT>(st, &smem[0][0], tid);
-  __syncthreads();
-
-  for (int j = 0; j < n_steps; ++j) {
-    const int buf = j & 1;
-    // (the last step fetches its own tile once more instead of branching: a conditional fetch makes
-    // the compiler keep the staging registers in scratch memory)
-    fp8_fetch<G, CPT>(st, kw, vw, head_base + (int64_t)step_tile(min(j + 1, n_steps - 1)) * TILE_BYTES, tid);
-    const uint4* kt = &smem[buf][0];
-    const uint4* vt = &smem[buf][TILE_CHUNKS];
-    // S^T of the two 32-key halves
-    f32x16 s[2];
+  // ---- pipeline.  Step j: S^T of tile j + 1 beside the probabilities of tile j, then O^T += V^T P^T of
+  // tile j beside the row maxima of tile j + 1.  One set of operand registers serves both products: an
+  // operand of K is refilled with one of V^T as soon as it is consumed, and the other way round.
+  i32x8 op[4];          // K operand (half u, features 64 t ..) is op[2 t + u]; V^T operand of features 32 db .. is op[db]
+  i32x8 pb;             // probabilities of the current tile
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+  for (int w = 0; w < 8; ++w) pb[w] = 0;
+  f32x16 sA[2], sB[2];  // score tiles (two 32-key halves each)
+  auto load_op = [&](i32x8& r, int chunk) __attribute__((always_inline)) {
+    const uint4 a0 = smem[chunk], a1 = smem[chunk + 64];
+    r[0] = (int)a0.x; r[1] = (int)a0.y; r[2] = (int)a0.z; r[3] = (int)a0.w;
+    r[4] = (int)a1.x; r[5] = (int)a1.y; r[6] = (int)a1.z; r[7] = (int)a1.w;
+  };
+  auto k_chunk = [&](int j) { return (j & (NS - 1)) * CH + lane; };
+  auto v_chunk = [&](int j) { return (NS + (j & (NS - 1))) * CH + lane; };
+  constexpr int KOFF[4] = {0, 2 * 128, 1 * 128, 3 * 128};  // chunk of op[2 t + u]: (2 u + t) * 128
+  // product x of the eight of S^T: t = x / 4, high or low term of Q = (x / 2) % 2, u = x % 2
+  auto mfma_qk = [&](f32x16 (&s)[2], auto x) __attribute__((always_inline)) {
+    constexpr int X = decltype(x)::value, t = X / 4, lo = (X / 2) % 2, u = X % 2;
+    if constexpr (X < 2) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[u][r] = 0.0f;
+    }
+    if constexpr (lo) s[u] = mfma_fp8_b_sixteenth(op[2 * t + u], qlo[t], s[u]);
+    else s[u] = mfma_fp8(op[2 * t + u], qf[t], s[u]);
+  };
+  // Row predicate: the keys of half u that this lane holds are key0 + 32 u + 4 hh + c,
+  // c = 8 (r / 4) + r % 4; the row's visible ones among the 32 become a bit mask, and a score
+  // is kept or replaced by -inf with one bit-field extract and one bit-field insert.
+  auto apply_mask = [&](f32x16 (&s)[2], int key0) __attribute__((always_inline)) {
+    auto low_bits = [](int n) {                            // bits [0, n) of 32, n clamped to [0, 32]
+      const unsigned m = (1u << (n & 31)) - 1u;
+      return n <= 0 ? 0u : n >= 32 ? 0xffffffffu : m;
+    };
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const uint4 a0 = kt[((u * 2 + t) * 2 + 0) * 64 + lane], a1 = kt[((u * 2 + t) * 2 + 1) * 64 + lane];
-        i32x8 a;
-        a[0] = (int)a0.x; a[1] = (int)a0.y; a[2] = (int)a0.z; a[3] = (int)a0.w;
-        a[4] = (int)a1.x; a[5] = (int)a1.y; a[6] = (int)a1.z; a[7] = (int)a1.w;
-        s[u] = mfma_fp8(a, qf[t], s[u]);
-        s[u] = mfma_fp8_b_sixteenth(a, qlo[t], s[u]);
+    for (int u = 0; u < 2; ++u) {
+      const int base = key0 + 32 * u + 4 * hh;
+      const unsigned vis = low_bits(a_end - base) | (low_bits(i_loc - base + 1) & ~low_bits(b_start - base));
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const unsigned keep = (unsigned)__builtin_amdgcn_sbfe((int)vis, 8 * (r / 4) + (r % 4), 1);
+        s[u][r] = __uint_as_float((__float_as_uint(s[u][r]) & keep) | (0xff800000u & ~keep));
       }
     }
-    const int jt = step_tile(j);
-    const int key0 = jt * kStepKeys;
-    if (jt >= tile.n_full) {
-      // Row predicate: the keys of half u that this lane holds are key0 + 32 u + 4 hh + c,
-      // c = 8 (r / 4) + r % 4; the row's visible ones among the 32 become a bit mask, and a score
-      // is kept or replaced by -inf with one bit-field extract and one bit-field insert.
-      auto low_bits = [](int n) {                          // bits [0, n) of 32, n clamped to [0, 32]
-        const unsigned m = (1u << (n & 31)) - 1u;
-        return n <= 0 ? 0u : n >= 32 ? 0xffffffffu : m;
-      };
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int base = key0 + 32 * u + 4 * hh;
-        const unsigned vis = low_bits(a_end - base) | (low_bits(i_loc - base + 1) & ~low_bits(b_start - base));
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const unsigned keep = (unsigned)__builtin_amdgcn_sbfe((int)vis, 8 * (r / 4) + (r % 4), 1);
-          s[u][r] = __uint_as_float((__float_as_uint(s[u][r]) & keep) | (0xff800000u & ~keep));
-        }
-      }
-    }
-    // running reference: moved up when this step's largest exponent exceeds it by more than 0.75
-    // octave (probabilities scaled by 2^8 then stay below 2^8.75 = 431 < 448, the largest E4M3 value)
-    float mx = s[0][0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[0][r]);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[1][r]);
+  };
+  // Running reference: moved up when a tile's largest exponent exceeds it by more than 0.75 octave
+  // (probabilities scaled by 2^8 then stay below 2^8.75 = 431 < 448, the largest E4M3 value).
+  auto raise_reference = [&](float mx) __attribute__((always_inline)) {
     mx = pair_max(mx) * c_row;                              // c_row > 0
-    const bool raise = mx > mref + 0.75f || (mref == -INFINITY && mx > -INFINITY);
+    const bool raise = mx > mref + 0.75f;                   // (mref = -inf: any visible key)
     if (__builtin_amdgcn_ballot_w64(raise) != 0) {
       const float m_new = raise ? mx : mref;
       const float alpha = mref == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mref - m_new);   // 1 when unchanged
@@ -380,58 +413,196 @@ __global__ __launch_bounds__(G * 64, 2) void k_attn_fp8(
         o[0][r] *= alpha; o[1][r] *= alpha; o[2][r] *= alpha; o[3][r] *= alpha; lacc[r] *= alpha;
       }
     }
-    // probabilities: 2^(S c - mref + 8), rounded to E4M3, in accumulator key order
-    const float bias = mref == -INFINITY ? 0.0f : 8.0f - mref;   // no key seen yet: every S is -inf, p = 0
-    i32x8 pb;
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float p[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][4 * i + e], c_row, bias));
-        pb[4 * u + i] = (int)pack_fp8x4(p[0], p[1], p[2], p[3]);
-      }
-    // O^T += V^T P^T, and the row sums through a tile of ones
-#pragma unroll
-    for (int db = 0; db < 4; ++db) {
-      const uint4 a0 = vt[(db * 2 + 0) * 64 + lane], a1 = vt[(db * 2 + 1) * 64 + lane];
-      i32x8 a;
-      a[0] = (int)a0.x; a[1] = (int)a0.y; a[2] = (int)a0.z; a[3] = (int)a0.w;
-      a[4] = (int)a1.x; a[5] = (int)a1.y; a[6] = (int)a1.z; a[7] = (int)a1.w;
-      o[db] = mfma_fp8(a, pb, o[db]);
-    }
-    lacc = mfma_fp8(ones, pb, lacc);
-    fp8_commit<G, CPT>(st, &smem[buf ^ 1][0], tid);
-    __syncthreads();
-  }
+  };
+  auto max_of = [&](float mx, const f32x16& s, auto r0, auto n) __attribute__((always_inline)) {
+    constexpr int R0 = decltype(r0)::value, N = decltype(n)::value;
+    static_for<0, N / 2>([&](auto i) {
+      constexpr int I = R0 + 2 * decltype(i)::value;
+      mx = fmaxf(fmaxf(mx, s[I]), s[I + 1]);
+    });
+    return mx;
+  };
+  using c0 = std::integral_constant<int, 0>;
+  using c8 = std::integral_constant<int, 8>;
+  using c16 = std::integral_constant<int, 16>;
 
-  // ---- epilogue: every register of lacc holds the row sum of this lane's query column
+  // S^T of tile j + 1 into s_out (QK) and P of tile j from s_in.  The work is issued in groups of one
+  // product and the softmax of four scores; exponent argument, exponential and rounding of a score sit in
+  // consecutive groups, so that none waits for its input in front of a product.
+  auto scores = [&](auto with_qk, int j, f32x16 (&s_in)[2], f32x16 (&s_out)[2]) __attribute__((always_inline)) {
+    constexpr bool QK = decltype(with_qk)::value;
+    const float bias = mref == -INFINITY ? 0.0f : 8.0f - mref;   // no key seen yet: every S is -inf, p = 0
+    const int vc = v_chunk(j);
+    float ea[8][4], ex[8][4];
+    auto v_arg = [&](auto w) {
+      constexpr int W = decltype(w)::value;
+      if constexpr (W < 8)
+        static_for<0, 4>([&](auto e) {
+          constexpr int E = decltype(e)::value;
+          ea[W][E] = __builtin_fmaf(s_in[W / 4][4 * (W % 4) + E], c_row, bias);
+        });
+    };
+    v_arg(c0{});
+    static_for<0, 8>([&](auto g8) {
+      constexpr int X = decltype(g8)::value;
+      if constexpr (QK) mfma_qk(s_out, g8);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (QK && X == 1) {
+        // V^T of tile j and K of tile j + 2 have to be there; younger: V^T(j+1), K(j+3), V^T(j+2).  Every
+        // wave is done with K of tile j and V^T of tile j - 1, whose slots the loads below refill.
+        wait_loads<3 * NREP>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+      if constexpr (QK && X >= 2) {                        // K of tile j + 4, then V^T of tile j + 3
+        static_for<0, 2 * NREP>([&](auto y) {
+          constexpr int Y = decltype(y)::value;
+          if constexpr (2 + Y * 6 / (2 * NREP) == X) {
+            if constexpr (Y < NREP) stage_one(kw, 0u, j + NS, Y);
+            else stage_one(vw, NS * TILE_BYTES, j + NS - 1, Y - NREP);
+          }
+        });
+        if constexpr ((X / 2) % 2) load_op(op[2 * (X / 4) + X % 2], vc + (2 * (X / 4) + X % 2) * 128);
+      }
+      static_for<0, 4>([&](auto e) {
+        constexpr int E = decltype(e)::value;
+        ex[X][E] = __builtin_amdgcn_exp2f(ea[X][E]);
+        asm volatile("" :: "v"(ex[X][E]));                 // a use in this group: not sunk to the pack
+      });
+      v_arg(std::integral_constant<int, X + 1>{});
+      if constexpr (X > 0) pb[X - 1] = (int)pack_fp8x4(ex[X - 1][0], ex[X - 1][1], ex[X - 1][2], ex[X - 1][3], pb[X - 1]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    pb[7] = (int)pack_fp8x4(ex[7][0], ex[7][1], ex[7][2], ex[7][3], pb[7]);
+  };
+  // O^T and the row sums (through a tile of ones) of tile j; then the reference for tile j + 1, whose
+  // scores are s_next, and the K operands of tile j + 2.
+  auto values = [&](int j, f32x16 (&s_next)[2]) __attribute__((always_inline)) {
+    const int kc = k_chunk(j + 2);
+    o[0] = mfma_fp8(op[0], pb, o[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    load_op(op[0], kc + KOFF[0]);
+    o[1] = mfma_fp8(op[1], pb, o[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    load_op(op[1], kc + KOFF[1]);
+    const int jt = step_tile(j + 1);
+    if (__builtin_expect(jt >= mine.n_full, 0)) apply_mask(s_next, jt * kStepKeys);
+    lacc = mfma_fp8(ones, pb, lacc);
+    __builtin_amdgcn_sched_barrier(0);
+    float mx = max_of(s_next[0][0], s_next[0], c0{}, c16{});
+    __builtin_amdgcn_sched_barrier(0);
+    o[2] = mfma_fp8(op[2], pb, o[2]);
+    __builtin_amdgcn_sched_barrier(0);
+    load_op(op[2], kc + KOFF[2]);
+    mx = max_of(mx, s_next[1], c0{}, c8{});
+    __builtin_amdgcn_sched_barrier(0);
+    o[3] = mfma_fp8(op[3], pb, o[3]);
+    __builtin_amdgcn_sched_barrier(0);
+    load_op(op[3], kc + KOFF[3]);
+    mx = max_of(mx, s_next[1], c8{}, c8{});
+    raise_reference(mx);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // prologue: S^T of tile 0, its reference, and the K operands of tile 1
+  wait_loads<5 * NREP>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  static_for<0, 4>([&](auto x) { load_op(op[decltype(x)::value], k_chunk(0) + KOFF[decltype(x)::value]); });
+  static_for<0, 8>([&](auto x) { mfma_qk(sA, x); });
+  static_for<0, 4>([&](auto x) { load_op(op[decltype(x)::value], k_chunk(1) + KOFF[decltype(x)::value]); });
+  {
+    const int jt = step_tile(0);
+    if (jt >= mine.n_full) apply_mask(sA, jt * kStepKeys);
+    float mx = max_of(sA[0][0], sA[0], c0{}, c16{});
+    mx = max_of(mx, sA[1], c0{}, c16{});
+    raise_reference(mx);
+  }
+  int j = 0;
+  for (; j + 2 <= last; j += 2) {
+    scores(std::true_type{}, j, sA, sB);
+    values(j, sB);
+    scores(std::true_type{}, j + 1, sB, sA);
+    values(j + 1, sA);
+  }
+  if (j < last) {
+    scores(std::true_type{}, j, sA, sB);
+    values(j, sB);
+    sA[0] = sB[0]; sA[1] = sB[1];
+    ++j;
+  }
+  // the last tile: probabilities and O^T only
+  wait_loads<0>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  static_for<0, 4>([&](auto x) { load_op(op[decltype(x)::value], v_chunk(j) + decltype(x)::value * 128); });
+  scores(std::false_type{}, j, sA, sB);
+  static_for<0, 4>([&](auto x) {
+    constexpr int X = decltype(x)::value;
+    o[X] = mfma_fp8(op[X], pb, o[X]);
+  });
+  lacc = mfma_fp8(ones, pb, lacc);
+  __syncthreads();                                         // every wave is done with the rings
+
+  // ---- epilogue: every register of lacc holds the row sum of this lane's query column.  The result is
+  // transposed through LDS so that every row leaves in contiguous pieces.
   const float l_tot = lacc[0];
-  const bool stored = valid && a_end + i_loc - b_start + 1 > PV_SHORT_ROW_KEYS;   // short rows: the extra workgroups
-  if (stored) {
+  {
     const float inv = v_scale[kvh] / l_tot;
-    const int64_t orow = (caller_row(plan, h, g) * hq + head) * D;
+    // (lane r < 32 holds the descriptor of row r); short rows come from the extra workgroups
+    const unsigned stored_rows = (unsigned)__builtin_amdgcn_ballot_w64(
+        valid && a_end + i_loc - b_start + 1 > PV_SHORT_ROW_KEYS);
+    auto stored = [&](int row) { return ((stored_rows >> row) & 1u) != 0; };
+    const int64_t tok0 = (int64_t)mine.tok_base + mine.t0;
+    char* tr = reinterpret_cast<char*>(&smem[0]) + (size_t)wave * (32 * RS);
+    if (out_f32) {
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+      for (int half = 0; half < 2; ++half) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int feat = 32 * db + 8 * i + 4 * hh;
-        const float x0 = o[db][4 * i] * inv, x1 = o[db][4 * i + 1] * inv, x2 = o[db][4 * i + 2] * inv, x3 = o[db][4 * i + 3] * inv;
-        if (out_f32) {
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + orow + feat) = make_float4(x0, x1, x2, x3);
-        } else {
-          uint2 w;
-          w.x = pack_bf16(x0, x1); w.y = pack_bf16(x2, x3);
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + orow + feat) = w;
+        for (int dbh = 0; dbh < 2; ++dbh)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const f32x16& x = o[half * 2 + dbh];
+            *reinterpret_cast<float4*>(tr + qrow * RS + (dbh * 32 + 8 * i + 4 * hh) * 4) =
+                make_float4(x[4 * i] * inv, x[4 * i + 1] * inv, x[4 * i + 2] * inv, x[4 * i + 3] * inv);
+          }
+        constexpr int LPR = D / 8;                         // lanes per row: D/2 floats
+#pragma unroll
+        for (int it = 0; it < 32 * LPR / 64; ++it) {
+          const int row = it * (64 / LPR) + lane / LPR, c = lane % LPR;
+          const float4 w = *reinterpret_cast<const float4*>(tr + row * RS + c * 16);
+          if (stored(row))
+            *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) +
+                                       (caller_row(plan, h, tok0 + row) * hq + head) * D + half * (D / 2) + c * 4) = w;
         }
       }
-    if (lse && hh == 0)
+    } else {
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint2 w;
+          w.x = pack_bf16(o[db][4 * i] * inv, o[db][4 * i + 1] * inv);
+          w.y = pack_bf16(o[db][4 * i + 2] * inv, o[db][4 * i + 3] * inv);
+          *reinterpret_cast<uint2*>(tr + qrow * RS + (db * 32 + 8 * i + 4 * hh) * 2) = w;
+        }
+      constexpr int LPR = D / 8;                           // lanes per row: 2 D bytes
+#pragma unroll
+      for (int it = 0; it < 32 * LPR / 64; ++it) {
+        const int row = it * (64 / LPR) + lane / LPR, c = lane % LPR;
+        const uint4 w = *reinterpret_cast<const uint4*>(tr + row * RS + c * 16);
+        if (stored(row))
+          *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(out) +
+                                    (caller_row(plan, h, tok0 + row) * hq + head) * D + c * 8) = w;
+      }
+    }
+    if (lse && hh == 0 && stored(qrow))
       lse[(int64_t)head * h.total_tokens + caller_row(plan, h, g)] = (log2f(l_tot) - 8.0f + mref) * 0.6931471805599453f;
   }
 }
 
-template <int G>
+// QT: one workgroup per (group of four tiles, query head), else one per (tile, kv head).
+template <int G, bool QT>
 static hipError_t launch_main_fp8(const int32_t* plan, const PlanHeader& h, const uint16_t* q, const uint8_t* kw,
                                   const uint8_t* vw, const float2* cs, const float* ks, const float* vs, void* out,
                                   float* lse, int hq, int hkv, float qscale, bool rope, bool out_f32,
@@ -439,11 +610,11 @@ static hipError_t launch_main_fp8(const int32_t* plan, const PlanHeader& h, cons
   dim3 grid;
   // one wave per (short row, query head), G of them to a workgroup, behind the items of the grid
   const int64_t n_short = ((int64_t)h.n_short_rows * hq + G - 1) / G;
-  if (n_short > 0x7fffffff || !grid_1d((int64_t)h.n_q_tiles * hkv + n_short, G * 64, &grid))
-    return hipErrorInvalidConfiguration;
-  k_attn_fp8<128, G><<<grid, dim3(G * 64), 0, s>>>(plan, h, q, kw, vw, cs, ks, vs, out, lse, hq, hkv, qscale, rope,
-                                                   out_f32, k8, v8, scale, (int)n_short,
-                                                   dispatch_order(h.n_q_tiles, hkv, G));
+  const int64_t items = QT ? (int64_t)h.n_quads * hq : (int64_t)h.n_q_tiles * hkv;
+  if (n_short > 0x7fffffff || !grid_1d(items + n_short, G * 64, &grid)) return hipErrorInvalidConfiguration;
+  k_attn_fp8<128, G, QT><<<grid, dim3(G * 64), 0, s>>>(plan, h, q, kw, vw, cs, ks, vs, out, lse, hq, hkv, qscale,
+                                                       rope, out_f32, k8, v8, scale, (int)n_short,
+                                                       QT ? 0 : dispatch_order(h.n_q_tiles, hkv, G));
   return hipGetLastError();
 }
 
@@ -464,10 +635,13 @@ hipError_t launch_attn_fp8(const int32_t* plan_dev, const PlanHeader& h, const v
   if (e != hipSuccess) return e;
   const float qscale = scale * 1.4426950408889634f;
   if (ev0) { e = hipEventRecord(ev0, s); if (e != hipSuccess) return e; }
-  switch (hq / hkv) {
-#define PV_CASE(GG) case GG: e = launch_main_fp8<GG>(plan_dev, h, kq, kw, vw, cs, k_scale, v_scale, out, lse, hq, hkv, qscale, rope, out_f32, (const uint8_t*)k8, (const uint8_t*)v8, scale, s); break;
+#define PV_LAUNCH(GG, QT) launch_main_fp8<GG, QT>(plan_dev, h, kq, kw, vw, cs, k_scale, v_scale, out, lse, hq, hkv, qscale, rope, out_f32, (const uint8_t*)k8, (const uint8_t*)v8, scale, s)
+  if (group_uses_query_tiles(hq / hkv) && h.n_quads > 0) e = PV_LAUNCH(4, true);
+  else switch (hq / hkv) {
+#define PV_CASE(GG) case GG: e = PV_LAUNCH(GG, false); break;
     PV_CASE(1) PV_CASE(2) PV_CASE(3) PV_CASE(4) PV_CASE(5) PV_CASE(6) PV_CASE(7) PV_CASE(8)
 #undef PV_CASE
+#undef PV_LAUNCH
     default: e = hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;
