@@ -23,7 +23,7 @@
 namespace pv {
 
 typedef __attribute__((ext_vector_type(8))) int i32x8;
-typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kStepKeys = 64;            // keys per step = depth of the second product
 
@@ -34,6 +34,11 @@ __device__ __forceinline__ f32x16 mfma_fp8(const i32x8& a, const i32x8& b, const
 // exponents, 0x7f = 1; checked on the device): used for the low part of Q.
 __device__ __forceinline__ f32x16 mfma_fp8_b_sixteenth(const i32x8& a, const i32x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0x7f, 0, 0x7b);
+}
+// 16 x 16 x 128: lane l holds row (or column) l % 16 and the depth block l / 16; the accumulator has column
+// l % 16, rows 4 (l / 16) ..
+__device__ __forceinline__ f32x4 mfma_fp8_16(const i32x8& a, const i32x8& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
 }
 __device__ __forceinline__ float fp8_byte(unsigned word, int byte) {
   switch (byte) {
@@ -346,12 +351,20 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     c_row = qscale * k_scale[kvh] * inv_fac;               // qscale = softmax scale * log2(e)
   }
 
-  f32x16 o[4], lacc;
+  f32x16 o[4];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) { o[0][r] = 0.0f; o[1][r] = 0.0f; o[2][r] = 0.0f; o[3][r] = 0.0f; lacc[r] = 0.0f; }
+  for (int r = 0; r < 16; ++r) { o[0][r] = 0.0f; o[1][r] = 0.0f; o[2][r] = 0.0f; o[3][r] = 0.0f; }
+  // Row sums: P^T as the B operand of the 16 x 16 x 128 product.  Its columns are l % 16, so the lanes of
+  // queries c and c + 16 share a column and fill different depth blocks (l / 16): rows with ones in blocks 0
+  // and 2 sum query c, rows with ones in blocks 1 and 3 query c + 16.  Row r takes the blocks of parity
+  // (r / 4) % 2, which gives every lane its own query's sum in all four accumulators.
+  f32x4 lacc = {0.0f, 0.0f, 0.0f, 0.0f};
   i32x8 ones;
+  {
+    int x = (lane >> 4 & 1) == (lane >> 2 & 1) ? 0x38383838 : 0;   // 1.0 in E4M3
 #pragma unroll
-  for (int w = 0; w < 8; ++w) ones[w] = 0x38383838;       // 1.0 in E4M3
+    for (int w = 0; w < 8; ++w) { asm volatile("" : "+v"(x)); ones[w] = x; }
+  }
   float mref = -INFINITY;                                  // reference of the exponent, log2 units
 
   // ---- pipeline.  Step j: S^T of tile j + 1 beside the probabilities of tile j, then O^T += V^T P^T of
@@ -410,8 +423,9 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       mref = m_new;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        o[0][r] *= alpha; o[1][r] *= alpha; o[2][r] *= alpha; o[3][r] *= alpha; lacc[r] *= alpha;
+        o[0][r] *= alpha; o[1][r] *= alpha; o[2][r] *= alpha; o[3][r] *= alpha;
       }
+      lacc[0] *= alpha;                                     // (the other three are not read)
     }
   };
   auto max_of = [&](float mx, const f32x16& s, auto r0, auto n) __attribute__((always_inline)) {
@@ -487,7 +501,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     load_op(op[1], kc + KOFF[1]);
     const int jt = step_tile(j + 1);
     if (__builtin_expect(jt >= mine.n_full, 0)) apply_mask(s_next, jt * kStepKeys);
-    lacc = mfma_fp8(ones, pb, lacc);
+    lacc = mfma_fp8_16(ones, pb, lacc);
     __builtin_amdgcn_sched_barrier(0);
     float mx = max_of(s_next[0][0], s_next[0], c0{}, c16{});
     __builtin_amdgcn_sched_barrier(0);
@@ -541,10 +555,10 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     constexpr int X = decltype(x)::value;
     o[X] = mfma_fp8(op[X], pb, o[X]);
   });
-  lacc = mfma_fp8(ones, pb, lacc);
+  lacc = mfma_fp8_16(ones, pb, lacc);
   __syncthreads();                                         // every wave is done with the rings
 
-  // ---- epilogue: every register of lacc holds the row sum of this lane's query column.  The result is
+  // ---- epilogue: lacc[0] holds the row sum of this lane's query.  The result is
   // transposed through LDS so that every row leaves in contiguous pieces.
   const float l_tot = lacc[0];
   {
