@@ -358,7 +358,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   // queries c and c + 16 share a column and fill different depth blocks (l / 16): rows with ones in blocks 0
   // and 2 sum query c, rows with ones in blocks 1 and 3 query c + 16.  Row r takes the blocks of parity
   // (r / 4) % 2, which gives every lane its own query's sum in all four accumulators.
-  f32x4 lacc = {0.0f, 0.0f, 0.0f, 0.0f};
+  float l_run = 0.0f;
   i32x8 ones;
   {
     int x = (lane >> 4 & 1) == (lane >> 2 & 1) ? 0x38383838 : 0;   // 1.0 in E4M3
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       for (int r = 0; r < 16; ++r) {
         o[0][r] *= alpha; o[1][r] *= alpha; o[2][r] *= alpha; o[3][r] *= alpha;
       }
-      lacc[0] *= alpha;                                     // (the other three are not read)
+      l_run *= alpha;
     }
   };
   auto max_of = [&](float mx, const f32x16& s, auto r0, auto n) __attribute__((always_inline)) {
@@ -489,6 +489,22 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     });
     pb[7] = (int)pack_fp8x4(ex[7][0], ex[7][1], ex[7][2], ex[7][3], pb[7]);
   };
+  // The sum over a tile's probabilities.  A query's NaN (a NaN in its Q row, or in a key that its neighbour
+  // does not see) meets the zeros of the query that shares its column: such a tile is summed from the codes.
+  auto add_row_sum = [&](const f32x4& d) __attribute__((always_inline)) {
+    float rs = d[0];
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(rs != rs) != 0, 0)) {
+      rs = 0.0f;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) {
+        const unsigned c = (unsigned)pb[w];
+        rs += (fp8_byte(c, 0) + fp8_byte(c, 1)) + (fp8_byte(c, 2) + fp8_byte(c, 3));
+      }
+      rs = pair_sum(rs);
+    }
+    l_run += rs;
+  };
+  const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
   // O^T and the row sums (through a tile of ones) of tile j; then the reference for tile j + 1, whose
   // scores are s_next, and the K operands of tile j + 2.
   auto values = [&](int j, f32x16 (&s_next)[2]) __attribute__((always_inline)) {
@@ -501,7 +517,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     load_op(op[1], kc + KOFF[1]);
     const int jt = step_tile(j + 1);
     if (__builtin_expect(jt >= mine.n_full, 0)) apply_mask(s_next, jt * kStepKeys);
-    lacc = mfma_fp8_16(ones, pb, lacc);
+    const f32x4 row_sum = mfma_fp8_16(ones, pb, zero4);
     __builtin_amdgcn_sched_barrier(0);
     float mx = max_of(s_next[0][0], s_next[0], c0{}, c16{});
     __builtin_amdgcn_sched_barrier(0);
@@ -514,6 +530,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     __builtin_amdgcn_sched_barrier(0);
     load_op(op[3], kc + KOFF[3]);
     mx = max_of(mx, s_next[1], c8{}, c8{});
+    add_row_sum(row_sum);
     raise_reference(mx);
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -555,12 +572,12 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     constexpr int X = decltype(x)::value;
     o[X] = mfma_fp8(op[X], pb, o[X]);
   });
-  lacc = mfma_fp8_16(ones, pb, lacc);
+  add_row_sum(mfma_fp8_16(ones, pb, zero4));
   __syncthreads();                                         // every wave is done with the rings
 
-  // ---- epilogue: lacc[0] holds the row sum of this lane's query.  The result is
+  // ---- epilogue: l_run holds the row sum of this lane's query.  The result is
   // transposed through LDS so that every row leaves in contiguous pieces.
-  const float l_tot = lacc[0];
+  const float l_tot = l_run;
   {
     const float inv = v_scale[kvh] / l_tot;
     // (lane r < 32 holds the descriptor of row r); short rows come from the extra workgroups
