@@ -60,9 +60,9 @@ void plan_layout(int batch, int64_t total_tokens, int64_t total_segments, int64_
   h->off_kpad_start = take(batch + 1);
   h->off_mask_start = take(2 * (int64_t)(batch + 1));
   h->off_bounds = take(total_segments);
-  h->off_short = take(4 * n_short_rows);
   h->off_segtile_start = take(batch + 1);
   h->off_quad_start = take(batch + 1);
+  h->off_short = take(4 * n_short_rows);
   h->off_device_begin = (int32_t)o;
   h->off_pos = take(total_tokens);
   h->off_aend = take(total_tokens);

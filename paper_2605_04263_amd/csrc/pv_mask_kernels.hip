@@ -120,10 +120,6 @@ __device__ inline void plan_token(int32_t* plan, const int32_t* img, const PlanH
   }
 }
 
-__global__ __launch_bounds__(256) void k_plan_tokens(int32_t* plan, PlanHeader h) {
-  plan_token(plan, plan, h, blockIdx.x * blockDim.x + threadIdx.x);
-}
-
 // Query tile t: the union of its rows' visible key sets, in key-tile units.  *seg_slot is the
 // tile's place in the list of tiles that hold segment rows (request after request), -1 if it
 // holds none.
@@ -175,45 +171,74 @@ __device__ inline QTile plan_tile(const int32_t* plan, const PlanHeader& h, int 
 // fewer): the union of their key-tile lists, for the launch whose workgroups take four query tiles
 // of one head.  Every wave of such a workgroup masks with its own tile's descriptor, so key tiles
 // that only some of the four need are simply fully masked for the others.  `n_full` of the result
-// carries the index of the group's first tile in the tile list instead.  *slot: the groups of a
-// request are listed last first (the last group has the longest key list).
-__device__ inline QTile plan_quad(const int32_t* plan, const PlanHeader& h, int qd, int* slot) {
-  const int b = find_owner(plan + h.off_quad_start, h.batch, qd);
-  const int q0 = plan[h.off_quad_start + b], nq = plan[h.off_quad_start + b + 1] - q0;
+// carries the index of the group's first tile in the tile list instead.  The groups of a request are
+// listed last first (the last group has the longest key list).  Four neighbouring lanes take the four
+// tiles (one thread after the other's tile is four chains of dependent reads and divisions); all four
+// call this together, `lane4` = their place.
+__device__ inline void plan_quad(int32_t* plan, const int32_t* img, const PlanHeader& h, int qd, int lane4) {
+  const int b = find_owner(img + h.off_quad_start, h.batch, qd);
+  const int q0 = img[h.off_quad_start + b], nq = img[h.off_quad_start + b + 1] - q0;
   const int ql = qd - q0;
-  const int t_first = plan[h.off_qtile_start + b] + 4 * ql;
-  const int t_end = min(t_first + 4, plan[h.off_qtile_start + b + 1]);
+  const int t_first = img[h.off_qtile_start + b] + 4 * ql;
+  const int t = t_first + lane4, t_last = img[h.off_qtile_start + b + 1] - 1;
   int unused;
-  QTile u = plan_tile(plan, h, t_first, &unused);
-  for (int t = t_first + 1; t < t_end; ++t) {
-    const QTile q = plan_tile(plan, h, t, &unused);
-    u.rows += q.rows;
-    u.n_a = max(u.n_a, q.n_a);
-    if (q.jb1 > q.jb0) {
-      if (u.jb1 > u.jb0) { u.jb0 = min(u.jb0, q.jb0); u.jb1 = max(u.jb1, q.jb1); }
-      else { u.jb0 = q.jb0; u.jb1 = q.jb1; }
-    }
+  QTile u = plan_tile(img, h, min(t, t_last), &unused);
+  const bool two = u.jb1 > u.jb0;                // the tile has a second range
+  int rows = t <= t_last ? u.rows : 0, n_a = u.n_a;
+  int jb0 = two ? u.jb0 : 0x7fffffff, jb1 = two ? u.jb1 : -1;
+#pragma unroll
+  for (int off = 1; off < 4; off <<= 1) {
+    rows += __shfl_xor(rows, off);
+    n_a = max(n_a, __shfl_xor(n_a, off));
+    jb0 = min(jb0, __shfl_xor(jb0, off));
+    jb1 = max(jb1, __shfl_xor(jb1, off));
   }
-  if (u.jb1 > u.jb0) { u.jb0 = max(u.jb0, u.n_a); u.jb1 = max(u.jb1, u.jb0); }
-  else { u.jb0 = u.n_a; u.jb1 = u.n_a; }
+  if (lane4 != 0) return;
+  u.rows = rows;
+  u.n_a = n_a;
+  u.jb0 = jb1 >= 0 ? max(jb0, n_a) : n_a;
+  u.jb1 = max(jb1, u.jb0);
   u.n_full = t_first;
-  *slot = q0 + (nq - 1 - ql);
-  return u;
+  reinterpret_cast<QTile*>(plan + h.off_quadwork)[q0 + (nq - 1 - ql)] = u;
 }
 
-__global__ __launch_bounds__(256) void k_plan_tiles(int32_t* plan, PlanHeader h) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < h.n_q_tiles) {
-    int seg_slot;
-    const QTile q = plan_tile(plan, h, t, &seg_slot);
-    reinterpret_cast<QTile*>(plan + h.off_tiles)[t] = q;
-    if (seg_slot >= 0) reinterpret_cast<QTile*>(plan + h.off_segwork)[seg_slot] = q;
+// Larger problems: per-token arrays, tiles and groups of tiles in one launch, a range of workgroups for
+// each; all of them read the request data only (`img` as in plan_token).
+__device__ inline void plan_build(int32_t* plan, const int32_t* img, const PlanHeader& h, int tile_blocks,
+                                  int quad_blocks) {
+  const int blk = (int)blockIdx.x, tid = (int)threadIdx.x;
+  if (blk < tile_blocks) {
+    const int t = blk * 256 + tid;
+    if (t < h.n_q_tiles) {
+      int seg_slot;
+      const QTile q = plan_tile(img, h, t, &seg_slot);
+      reinterpret_cast<QTile*>(plan + h.off_tiles)[t] = q;
+      if (seg_slot >= 0) reinterpret_cast<QTile*>(plan + h.off_segwork)[seg_slot] = q;
+    }
+  } else if (blk < tile_blocks + quad_blocks) {
+    const int qd = (blk - tile_blocks) * 64 + (tid >> 2);
+    if (qd < h.n_quads) plan_quad(plan, img, h, qd, tid & 3);
+  } else {
+    plan_token(plan, img, h, (blk - tile_blocks - quad_blocks) * 256 + tid);
   }
-  if (t < h.n_quads) {
-    int slot;
-    const QTile u = plan_quad(plan, h, t, &slot);
-    reinterpret_cast<QTile*>(plan + h.off_quadwork)[slot] = u;
+}
+
+// The request data in the kernel arguments: every workgroup has it without a launch before this one
+// (workgroup 0 writes it to the plan) and looks its requests up in LDS.
+__global__ __launch_bounds__(256) void k_plan_build_args(int32_t* plan, PlanHeader h, UploadChunk c, int n_img,
+                                                         int tile_blocks, int quad_blocks) {
+  __shared__ int32_t img_s[kUploadInts];
+  for (int i = threadIdx.x; i < n_img; i += 256) {
+    const int32_t x = c.v[i];
+    if (blockIdx.x == 0) plan[i] = x;
+    img_s[i] = x;
   }
+  __syncthreads();
+  plan_build(plan, img_s, h, tile_blocks, quad_blocks);
+}
+// The request data uploaded before (too many requests or segments for the arguments).
+__global__ __launch_bounds__(256) void k_plan_build(int32_t* plan, PlanHeader h, int tile_blocks, int quad_blocks) {
+  plan_build(plan, plan, h, tile_blocks, quad_blocks);
 }
 
 // Small problems: the whole plan in one launch.  The host image arrives in the kernel arguments, so
@@ -247,17 +272,14 @@ __global__ __launch_bounds__(1024) void k_plan_small(int32_t* plan, PlanHeader h
     my_cost = mine.n_a + (mine.jb1 - mine.jb0);
     reinterpret_cast<QTile*>(plan + h.off_tiles)[tid] = mine;
     if (seg_slot >= 0) reinterpret_cast<QTile*>(plan + h.off_segwork)[seg_slot] = mine;
-
     cost_s[tid] = my_cost;
   }
-  // the groups of four tiles go to the threads after those of the tiles; if the workgroup is too
-  // small for both, the first threads take them as well
-  const bool beside = h.n_q_tiles + h.n_quads <= 1024;
-  for (int qd = beside ? tid - h.n_q_tiles : tid; qd >= 0 && qd < h.n_quads; qd += 1024) {
-    int slot;
-    const QTile u = plan_quad(img_s, h, qd, &slot);
-    reinterpret_cast<QTile*>(plan + h.off_quadwork)[slot] = u;
-  }
+  // the groups of four tiles (four lanes each) go to the waves after those of the tiles; if the workgroup
+  // is too small for both, the first ones take them as well
+  const int q_first = (h.n_q_tiles + 63) & ~63;
+  const bool beside = q_first + 4 * h.n_quads <= 1024;
+  for (int x = beside ? tid - q_first : tid; x >= 0 && x < 4 * h.n_quads; x += 1024)
+    plan_quad(plan, img_s, h, x >> 2, x & 3);
   __syncthreads();
   if (tid < h.n_q_tiles) {          // longest first, stable
     int rank = 0;
@@ -269,22 +291,40 @@ __global__ __launch_bounds__(1024) void k_plan_small(int32_t* plan, PlanHeader h
   }
 }
 
-// Longest-first order (stable): rank = number of tiles that must run before this one.  One wave
-// per tile; its lanes share the comparisons against all other tiles.
+// Longest-first order (stable): rank = number of tiles that must run before this one.  One wave per
+// four tiles; its lanes share the comparisons against all other tiles, whose costs they read eight at a
+// time: one read per round trip and one tile per wave left the launch waiting for L2.
+constexpr int kSortTiles = 4, kSortReads = 8;
 __global__ __launch_bounds__(256) void k_plan_sort(int32_t* plan, PlanHeader h) {
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (t >= h.n_q_tiles) return;                 // whole waves leave together
+  const int n = h.n_q_tiles, lane = threadIdx.x & 63;
+  const int t0 = ((int)blockIdx.x * 4 + ((int)threadIdx.x >> 6)) * kSortTiles;
+  if (t0 >= n) return;                          // whole waves leave together
   const QTile* tiles = reinterpret_cast<const QTile*>(plan + h.off_tiles);
-  const QTile mine = tiles[t];
-  const int my_cost = mine.n_a + (mine.jb1 - mine.jb0);
-  int rank = 0;
-  for (int u = lane; u < h.n_q_tiles; u += 64) {
-    const int c = tiles[u].n_a + (tiles[u].jb1 - tiles[u].jb0);
-    rank += (c > my_cost) || (c == my_cost && u < t);
-  }
+  auto cost = [&](int t) { return tiles[t].n_a + (tiles[t].jb1 - tiles[t].jb0); };
+  int mine[kSortTiles], rank[kSortTiles];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) rank += __shfl_xor(rank, off);
-  if (lane == 0) reinterpret_cast<QTile*>(plan + h.off_work)[rank] = mine;
+  for (int i = 0; i < kSortTiles; ++i) { mine[i] = cost(min(t0 + i, n - 1)); rank[i] = 0; }
+  for (int u0 = lane; u0 < n; u0 += 64 * kSortReads) {
+    int c[kSortReads];
+#pragma unroll
+    for (int r = 0; r < kSortReads; ++r) c[r] = cost(min(u0 + 64 * r, n - 1));
+#pragma unroll
+    for (int r = 0; r < kSortReads; ++r) {
+      const int u = u0 + 64 * r;
+#pragma unroll
+      for (int i = 0; i < kSortTiles; ++i)
+        rank[i] += u < n && (c[r] > mine[i] || (c[r] == mine[i] && u < t0 + i));
+    }
+  }
+  int my_rank = 0;
+#pragma unroll
+  for (int i = 0; i < kSortTiles; ++i) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) rank[i] += __shfl_xor(rank[i], off);
+    if (lane == i) my_rank = rank[i];
+  }
+  if (lane < kSortTiles && t0 + lane < n)
+    reinterpret_cast<QTile*>(plan + h.off_work)[my_rank] = tiles[t0 + lane];
 }
 
 // Dense mask from the stored row descriptors (what the attention kernels consume).
@@ -315,16 +355,25 @@ hipError_t launch_plan_kernels(int32_t* plan_dev, const PlanHeader& h, const int
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   } else {
-    e = launch_upload(plan_dev, host_ints, n_img, s);
+    // The request data go with the launch that uses them where they fit its arguments; the rows with few
+    // keys, behind them in the image, are for later calls only.
+    const bool in_args = h.off_short <= kUploadInts;
+    const int n_args = in_args ? h.off_short : 0;
+    e = launch_upload(plan_dev + n_args, host_ints + n_args, n_img - n_args, s);
     if (e != hipSuccess) return e;
-    k_plan_tokens<<<dim3((n1 + 255) / 256), dim3(256), 0, s>>>(plan_dev, h);
+    const int tile_blocks = (h.n_q_tiles + 255) / 256, quad_blocks = (h.n_quads + 63) / 64;
+    const dim3 grid(tile_blocks + quad_blocks + (n1 + 255) / 256);
+    if (in_args) {
+      UploadChunk c;
+      for (int i = 0; i < n_args; ++i) c.v[i] = host_ints[i];
+      for (int i = n_args; i < kUploadInts; ++i) c.v[i] = 0;
+      k_plan_build_args<<<grid, dim3(256), 0, s>>>(plan_dev, h, c, n_args, tile_blocks, quad_blocks);
+    } else {
+      k_plan_build<<<grid, dim3(256), 0, s>>>(plan_dev, h, tile_blocks, quad_blocks);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int nt = (h.n_q_tiles + 255) / 256;
-    k_plan_tiles<<<dim3(nt), dim3(256), 0, s>>>(plan_dev, h);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_plan_sort<<<dim3((h.n_q_tiles + 3) / 4), dim3(256), 0, s>>>(plan_dev, h);
+    k_plan_sort<<<dim3((h.n_q_tiles + 4 * kSortTiles - 1) / (4 * kSortTiles)), dim3(256), 0, s>>>(plan_dev, h);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
