@@ -508,7 +508,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     // the MFMAs, and the VALU work then runs while the matrix pipe idles.)  The wave issues in
     // order, so a VALU instruction waiting for its input also holds back the next MFMA: the
     // softmax work of a score is therefore spread over consecutive groups,
-    //   exponent argument -> exp2 -> (pair) bf16 pack -> (pair) row-sum dot,
+    //   exponent argument -> exp2 -> (pair) bf16 pack -> (pair) row sum,
     // each stage one group after the stage it depends on.
     constexpr int NG = 2 * KT, SPG = 16 / NG;          // groups; scores entering per group
     constexpr int GHI = SPG == 1 ? 2 : 1;              // groups from the pack to the sum of the high halves

@@ -7,12 +7,12 @@
 //   (rows that see at most PV_SHORT_ROW_KEYS keys are evaluated in plain fp32 by extra workgroups at the
 //   end of k_attn_fp8's grid, one wave per row and query head)
 //   k_attn_fp8   flash-style pass: one workgroup = one 32-token query tile x one kv head, wave w =
-//                query head kvh*G + w; a step is one 64-key tile.  Q is rotated, scaled by a per-row
+//                query head kvh*G + w (or four query tiles of one head); a step is one 64-key tile.  Q is rotated, scaled by a per-row
 //                power of two and split into two E4M3 terms (the rounded value and 16 x the rounding
 //                residual, the second product scaled by 2^-4 inside the instruction), which carries Q
 //                at about bf16 precision through the FP8 pipe; probabilities are formed against a running
 //                reference, scaled by 2^8 and rounded to E4M3; the row sum comes out of the matrix
-//                pipe (a tile of ones as the fifth V^T block), so the output is an exact convex
+//                pipe (a product with ones over the same codes), so the output is an exact convex
 //                combination of V rows with the rounded weights.
 // Operand layout of the instruction (checked on the device): lane l holds row (or column) l % 32 and
 // the 32 consecutive depth indices 32 * (l / 32) .. + 31, byte j of its 32 bytes = depth offset j;
@@ -205,6 +205,11 @@ __device__ __forceinline__ void wait_loads() {            // at most N loads of 
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
+// What bounds it: the matrix pipe, 12 products of 64 cycles and one of 32 per wave and step, and the issue of
+// the ~120 VALU instructions of the softmax beside them; hence the products of one tile are issued between
+// the softmax of its neighbour, and staging bypasses the registers.  Pass, us, against phases one after the
+// other with staging through registers: 4 x (2048 + 8192) tokens, 64/8 heads 8240 / 6920; 512 + 2048, 32/8
+// heads 90.6 / 80; 1024 + 4096, 40/8 heads (query tiles instead of one wave per head) 561 / 271.
 // QT as in the bf16 kernel: the four waves are four consecutive query tiles of one query head; `tile` is
 // the union of the four (it drives the key loop and the staging), `mine` the wave's own.
 template <int D, int G, bool QT>
