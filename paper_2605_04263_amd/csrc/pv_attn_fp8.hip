@@ -324,8 +324,10 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
         const uint4 w4 = tab[j / 2];
         const float wc = __uint_as_float(j % 2 ? w4.z : w4.x), wsn = __uint_as_float(j % 2 ? w4.w : w4.y);
         const float l0 = lo[j], h0 = hi[j];
-        lo[j] = l0 * wc - h0 * wsn;
-        hi[j] = h0 * wc + l0 * wsn;
+        // (spelled out: which product the compiler contracts shows in the codes of values next to a rounding
+        // boundary, a change of 1e-4 of the output's norm from one build to another)
+        lo[j] = __builtin_fmaf(l0, wc, -(h0 * wsn));
+        hi[j] = __builtin_fmaf(l0, wsn, h0 * wc);
       }
     }
     stage_v(0); stage_k(2); stage_v(1); stage_k(3); stage_v(2);
