@@ -512,10 +512,23 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     l_run += rs;
   };
   const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+  // QT: a key tile that only the other query tiles of the group read has probability zero throughout, and its
+  // V^T is replaced by zero as well: a NaN in it is not this tile's.
+  auto drop_foreign = [&](int j) __attribute__((always_inline)) {
+    if constexpr (QT) {
+      const int jt = step_tile(j);
+      if (__builtin_expect(jt >= mine.n_a && (jt < mine.jb0 || jt >= mine.jb1), 0))
+        static_for<0, 4>([&](auto x) {
+#pragma unroll
+          for (int w = 0; w < 8; ++w) op[decltype(x)::value][w] = 0;
+        });
+    }
+  };
   // O^T and the row sums (through a tile of ones) of tile j; then the reference for tile j + 1, whose
   // scores are s_next, and the K operands of tile j + 2.
   auto values = [&](int j, f32x16 (&s_next)[2]) __attribute__((always_inline)) {
     const int kc = k_chunk(j + 2);
+    drop_foreign(j);
     o[0] = mfma_fp8(op[0], pb, o[0]);
     __builtin_amdgcn_sched_barrier(0);
     load_op(op[0], kc + KOFF[0]);
@@ -575,6 +588,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   asm volatile("" ::: "memory");
   static_for<0, 4>([&](auto x) { load_op(op[decltype(x)::value], v_chunk(j) + decltype(x)::value * 128); });
   scores(std::false_type{}, j, sA, sB);
+  drop_foreign(j);
   static_for<0, 4>([&](auto x) {
     constexpr int X = decltype(x)::value;
     o[X] = mfma_fp8(op[X], pb, o[X]);
