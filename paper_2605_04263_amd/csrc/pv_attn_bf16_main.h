@@ -233,17 +233,34 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       sc[r] = __uint_as_float((__float_as_uint(sc[r]) & keep) | (0xff800000u & ~keep));
     }
   };
-  // p rounded to bf16 once; the row sum is taken over the rounded values, unpacked again, so that O
-  // is an exact convex combination of V rows with the weights the MFMA sees.  (Four VALU operations per
-  // pair and not one v_dot2c: a dot runs on the matrix pipe.  Cycles per 32x32x16 MFMA with one exp2 and
-  // half a pack and a dot beside it 49, with the unpacked sum instead 34.)
+  // p rounded to bf16 once; the row sum is taken over the rounded values, so that O is an exact convex
+  // combination of V rows with the weights the MFMA sees.
+  // kSumByDot: v_dot2c with a pair of ones, one instruction per pair, which runs on the matrix pipe; else the
+  // pair unpacked and added, four on the VALU.  D = 128 has one MFMA per score and is bound by the matrix pipe
+  // (cycles per 32x32x16 MFMA with one exp2 and half a pack beside it: 49 with the dot, 34 unpacked); D = 64 has
+  // half an MFMA per score and is bound by VALU issue where a SIMD holds two waves.  Either way the sum is two
+  // chains: a dot that waits for the one before it holds back the next MFMA.
+  // Passes, us, unpacked / one chain of dots / two: D = 64, 512 + 2048 + 512 tokens, 32/8 heads 62.3 / 58.2 /
+  // 58.1; 40/8 heads, 4 ragged requests of 2 to 6 K 931 / 943 / 920; 16/4 heads, 1.25 workgroups per slot
+  // 78.2 / 85.7 / 79.8.  Seven waves at D = 128 are the exception there, 28/4 heads, 2 x 4592 tokens 304.5 /
+  // 297.2 / 297.6 (eight waves 312.7 / 319.9 / 323.5); what makes them one was not isolated.
+  constexpr bool kSumByDot = D == 64 || (G == 7 && !QT);
+  auto dot_ones = [](unsigned pair, float acc) __attribute__((always_inline)) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair),
+                                           __builtin_bit_cast(bf16x2, 0x3f803f80u), acc, false);
+  };
   auto probs = [&](const f32x16& sc, unsigned (&pw)[8]) __attribute__((always_inline)) {
     float rs = 0.0f, rs_hi = 0.0f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       pw[e] = pack_bf16(prob(sc[2 * e]), prob(sc[2 * e + 1]));
-      rs += bf16_lo(pw[e]);
-      rs_hi += bf16_hi(pw[e]);
+      if constexpr (kSumByDot) {
+        float& x = e % 2 ? rs : rs_hi;
+        x = dot_ones(pw[e], x);
+      } else {
+        rs += bf16_lo(pw[e]);
+        rs_hi += bf16_hi(pw[e]);
+      }
     }
     return rs + rs_hi;
   };
@@ -536,8 +553,13 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
         constexpr int E = decltype(e)::value;
         constexpr int GC = (2 * E + 1) / SPG;            // group after the pair's second exp2
         if constexpr (GC == GI) p_out[E] = pack_bf16(ex[2 * E], ex[2 * E + 1]);
-        if constexpr (GC + 1 == GI) rs += bf16_lo(p_out[E]);
-        if constexpr (GC + GHI == GI) rs_hi += bf16_hi(p_out[E]);
+        if constexpr (kSumByDot) {
+          float& x = E % 2 ? rs : rs_hi;
+          if constexpr (GC + 1 == GI) x = dot_ones(p_out[E], x);
+        } else {
+          if constexpr (GC + 1 == GI) rs += bf16_lo(p_out[E]);
+          if constexpr (GC + GHI == GI) rs_hi += bf16_hi(p_out[E]);
+        }
       });
     };
     // n-th staging instruction of this wave for a slot
