@@ -237,8 +237,11 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   constexpr int NREP = (CH / 64 + G - 1) / G;              // staging instructions of a wave for one slot
   constexpr int RS = 2 * D + 16;                           // row stride of the epilogue's transposition
   constexpr int SMEM = (2 * NS * CH * 16 > G * 32 * RS ? 2 * NS * CH * 16 : G * 32 * RS) / 16;
-  // K ring, then V^T ring; step j lives in slot j % NS of each
-  __shared__ uint4 smem[SMEM];
+  // K ring, then V^T ring; step j lives in slot j % NS of each.  QT: a slot of zeros behind them (72 KB, two
+  // workgroups still fit a compute unit).
+  constexpr int ZERO = 2 * NS * CH;
+  __shared__ uint4 smem[SMEM + (QT ? CH : 0)];
+  static_assert(!QT || SMEM == ZERO, "the slot of zeros starts behind the rings");
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
@@ -388,7 +391,12 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     r[4] = (int)a1.x; r[5] = (int)a1.y; r[6] = (int)a1.z; r[7] = (int)a1.w;
   };
   auto k_chunk = [&](int j) { return (j & (NS - 1)) * CH + lane; };
-  auto v_chunk = [&](int j) { return (NS + (j & (NS - 1))) * CH + lane; };
+  // QT: a key tile that only the other query tiles of the group read has probability zero throughout, and its
+  // V^T is read from the slot of zeros: a NaN in it is not this tile's.  Every such tile is masked, so the test
+  // sits with the mask, and a step in the open pays for a scalar select.  (Zeroing the operands instead, behind
+  // a branch of its own, cost 1.5 to 3 % of the pass.)
+  bool foreign = false;                                    // the tile of the current scores is such a one
+  auto v_chunk = [&](int j) { return (QT && foreign ? ZERO : (NS + (j & (NS - 1))) * CH) + lane; };
   constexpr int KOFF[4] = {0, 2 * 128, 1 * 128, 3 * 128};  // chunk of op[2 t + u]: (2 u + t) * 128
   // product x of the eight of S^T: t = x / 4, high or low term of Q = (x / 2) % 2, u = x % 2
   auto mfma_qk = [&](f32x16 (&s)[2], auto x) __attribute__((always_inline)) {
@@ -417,6 +425,13 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
         const unsigned keep = (unsigned)__builtin_amdgcn_sbfe((int)vis, 8 * (r / 4) + (r % 4), 1);
         s[u][r] = __uint_as_float((__float_as_uint(s[u][r]) & keep) | (0xff800000u & ~keep));
       }
+    }
+  };
+  auto mask_tile = [&](f32x16 (&s)[2], int jt) __attribute__((always_inline)) {
+    foreign = false;
+    if (__builtin_expect(jt >= mine.n_full, 0)) {
+      if constexpr (QT) foreign = jt >= mine.n_a && (jt < mine.jb0 || jt >= mine.jb1);
+      apply_mask(s, jt * kStepKeys);
     }
   };
   // Running reference: moved up when a tile's largest exponent exceeds it by more than 0.75 octave
@@ -512,31 +527,17 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     l_run += rs;
   };
   const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-  // QT: a key tile that only the other query tiles of the group read has probability zero throughout, and its
-  // V^T is replaced by zero as well: a NaN in it is not this tile's.
-  auto drop_foreign = [&](int j) __attribute__((always_inline)) {
-    if constexpr (QT) {
-      const int jt = step_tile(j);
-      if (__builtin_expect(jt >= mine.n_a && (jt < mine.jb0 || jt >= mine.jb1), 0))
-        static_for<0, 4>([&](auto x) {
-#pragma unroll
-          for (int w = 0; w < 8; ++w) op[decltype(x)::value][w] = 0;
-        });
-    }
-  };
   // O^T and the row sums (through a tile of ones) of tile j; then the reference for tile j + 1, whose
   // scores are s_next, and the K operands of tile j + 2.
   auto values = [&](int j, f32x16 (&s_next)[2]) __attribute__((always_inline)) {
     const int kc = k_chunk(j + 2);
-    drop_foreign(j);
     o[0] = mfma_fp8(op[0], pb, o[0]);
     __builtin_amdgcn_sched_barrier(0);
     load_op(op[0], kc + KOFF[0]);
     o[1] = mfma_fp8(op[1], pb, o[1]);
     __builtin_amdgcn_sched_barrier(0);
     load_op(op[1], kc + KOFF[1]);
-    const int jt = step_tile(j + 1);
-    if (__builtin_expect(jt >= mine.n_full, 0)) apply_mask(s_next, jt * kStepKeys);
+    mask_tile(s_next, step_tile(j + 1));
     const f32x4 row_sum = mfma_fp8_16(ones, pb, zero4);
     __builtin_amdgcn_sched_barrier(0);
     float mx = max_of(s_next[0][0], s_next[0], c0{}, c16{});
@@ -556,6 +557,11 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   };
 
   // prologue: S^T of tile 0, its reference, and the K operands of tile 1
+  if constexpr (QT) {
+#pragma unroll
+    for (int n = 0; n < CH / (G * 64); ++n) smem[ZERO + n * (G * 64) + tid] = make_uint4(0u, 0u, 0u, 0u);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the barrier below makes them everyone's
+  }
   wait_loads<5 * NREP>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
@@ -563,8 +569,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   static_for<0, 8>([&](auto x) { mfma_qk(sA, x); });
   static_for<0, 4>([&](auto x) { load_op(op[decltype(x)::value], k_chunk(1) + KOFF[decltype(x)::value]); });
   {
-    const int jt = step_tile(0);
-    if (jt >= mine.n_full) apply_mask(sA, jt * kStepKeys);
+    mask_tile(sA, step_tile(0));
     float mx = max_of(sA[0][0], sA[0], c0{}, c16{});
     mx = max_of(mx, sA[1], c0{}, c16{});
     raise_reference(mx);
@@ -588,7 +593,6 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   asm volatile("" ::: "memory");
   static_for<0, 4>([&](auto x) { load_op(op[decltype(x)::value], v_chunk(j) + decltype(x)::value * 128); });
   scores(std::false_type{}, j, sA, sB);
-  drop_foreign(j);
   static_for<0, 4>([&](auto x) {
     constexpr int X = decltype(x)::value;
     o[X] = mfma_fp8(op[X], pb, o[X]);
