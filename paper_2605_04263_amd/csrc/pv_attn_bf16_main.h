@@ -242,9 +242,11 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   // chains: a dot that waits for the one before it holds back the next MFMA.
   // Passes, us, unpacked / one chain of dots / two: D = 64, 512 + 2048 + 512 tokens, 32/8 heads 62.3 / 58.2 /
   // 58.1; 40/8 heads, 4 ragged requests of 2 to 6 K 931 / 943 / 920; 16/4 heads, 1.25 workgroups per slot
-  // 78.2 / 85.7 / 79.8.  Seven waves at D = 128 are the exception there, 28/4 heads, 2 x 4592 tokens 304.5 /
-  // 297.2 / 297.6 (eight waves 312.7 / 319.9 / 323.5); what makes them one was not isolated.
-  constexpr bool kSumByDot = D == 64 || (G == 7 && !QT);
+  // 78.2 / 85.7 / 79.8.  Workgroups of five to seven waves, one to a compute unit, are the exception at D = 128:
+  // 28/4 heads, 2 x 4592 tokens 304.5 / 297.2 / 297.6 (eight waves 312.7 / 319.9 / 323.5), segment rows of 8
+  // requests at 40/8 and 48/8 heads 347 and 351 unpacked, 338 and 340 with two chains (before there were any
+  // unpacked sums 346 and 348); why they differ from eight was not isolated.
+  constexpr bool kSumByDot = D == 64 || (!QT && G >= 5 && G <= 7);
   auto dot_ones = [](unsigned pair, float acc) __attribute__((always_inline)) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair),
                                            __builtin_bit_cast(bf16x2, 0x3f803f80u), acc, false);
