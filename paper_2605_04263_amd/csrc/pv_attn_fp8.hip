@@ -692,14 +692,13 @@ hipError_t launch_attn_fp8(const int32_t* plan_dev, const PlanHeader& h, const v
   const float qscale = scale * 1.4426950408889634f;
   if (ev0) { e = hipEventRecord(ev0, s); if (e != hipSuccess) return e; }
 #define PV_LAUNCH(GG, QT) launch_main_fp8<GG, QT>(plan_dev, h, kq, kw, vw, cs, k_scale, v_scale, out, lse, hq, hkv, qscale, rope, out_f32, (const uint8_t*)k8, (const uint8_t*)v8, scale, s)
-  if (group_uses_query_tiles(hq / hkv) && h.n_quads > 0) e = PV_LAUNCH(4, true);
-  else switch (hq / hkv) {
-#define PV_CASE(GG) case GG: e = PV_LAUNCH(GG, false); break;
-    PV_CASE(1) PV_CASE(2) PV_CASE(3) PV_CASE(4) PV_CASE(5) PV_CASE(6) PV_CASE(7) PV_CASE(8)
-#undef PV_CASE
+  const int G = hq / hkv;
+  if (group_uses_query_tiles(G) && h.n_quads > 0) e = PV_LAUNCH(4, true);
+  else if (G == 4) e = PV_LAUNCH(4, false);
+  else if (G == 7) e = PV_LAUNCH(7, false);
+  else if (G == 8) e = PV_LAUNCH(8, false);
+  else e = hipErrorInvalidValue;
 #undef PV_LAUNCH
-    default: e = hipErrorInvalidValue;
-  }
   if (e != hipSuccess) return e;
   if (ev1) { e = hipEventRecord(ev1, s); if (e != hipSuccess) return e; }
   return hipSuccess;

@@ -274,12 +274,12 @@ __global__ __launch_bounds__(1024) void k_plan_small(int32_t* plan, PlanHeader h
     if (seg_slot >= 0) reinterpret_cast<QTile*>(plan + h.off_segwork)[seg_slot] = mine;
     cost_s[tid] = my_cost;
   }
-  // the groups of four tiles (four lanes each) go to the waves after those of the tiles; if the workgroup
-  // is too small for both, the first ones take them as well
-  const int q_first = (h.n_q_tiles + 63) & ~63;
-  const bool beside = q_first + 4 * h.n_quads <= 1024;
-  for (int x = beside ? tid - q_first : tid; x >= 0 && x < 4 * h.n_quads; x += 1024)
-    plan_quad(plan, img_s, h, x >> 2, x & 3);
+  // The groups of four tiles (four lanes each) go to the waves after those of the tiles.  There is room for both:
+  // a request takes at least 16 ints of the image, so there are at most 56, with at most 8192 / 32 + 56 = 312
+  // tiles and 312 / 4 + 56 = 134 groups, and 320 + 4 * 134 threads are fewer than 1024.
+  static_assert(kUploadInts / 16 == 56 && kSmallTokens / 32 == 256, "the bound above");
+  const int x = tid - ((h.n_q_tiles + 63) & ~63);
+  if (x >= 0 && x < 4 * h.n_quads) plan_quad(plan, img_s, h, x >> 2, x & 3);
   __syncthreads();
   if (tid < h.n_q_tiles) {          // longest first, stable
     int rank = 0;
