@@ -109,6 +109,18 @@ def test_group_sizes_long_rows(group):
     run_fp8(w, label=f"group {group}")
 
 
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("group", [1, 2, 3, 5, 6])
+def test_query_tiles_ragged_batch(group, layout):
+    # several requests, groups of four query tiles of 1 to 4 tiles and 3 to 128 rows, with and without segments
+    pr = wl.Problem([40, 3, 90, 200], [300, 128, 410, 33], [2, 0, 4, 3], [24, 1, 33, 40],
+                    [[90, 300], [], [50, 51, 200, 410], [0, 20, 33]])
+    w = wl.make_custom(dataclasses.replace(pr, layout=layout), 2 * group, 2, 128, dtype=torch.bfloat16,
+                       rope_theta=0.0 if group == 2 else 5e5, seed=660 + group)
+    _, _, ver = run_fp8(w, label=f"ragged, group {group}, layout {layout}")
+    assert ver.sizes.n_quads == 4 + 2 + 5 + 3
+
+
 def test_8b_every_row():
     run_fp8(wl.make("8b"), label="8b, every row")
 

@@ -37,10 +37,11 @@ def test_bf16(n_tiles):
 @pytest.mark.parametrize("n_tiles", TILES)
 def test_fp8(n_tiles):
     pr = problem(n_tiles)
-    w = wl.make_custom(pr, 96, 32, 128, dtype=torch.bfloat16, rope_theta=5e5, seed=950 + n_tiles)
+    w = wl.make_custom(pr, 128, 32, 128, dtype=torch.bfloat16, rope_theta=5e5, seed=950 + n_tiles)
     kc, ksc = wl.quantize_fp8(w.k)
     vc, vsc = wl.quantize_fp8(w.v)
     ver = gc.make_verifier(pv, w)
+    assert ver.sizes.n_q_tiles == n_tiles and ver.sizes.n_quads == 0     # one workgroup per tile and kv head
     ver.build_mask()
     dev = ver.device
     out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=dev)

@@ -82,7 +82,7 @@ def test_readout_named_and_patterns():
 
 def test_70b_plan_mask_work_list_readout():
     # the long configuration (4 requests of 14 336 tokens, 1 792 tiles: the plan comes from the separate
-    # upload / tokens / tiles / ranking kernels): positions and judge rows of every token, the dense
+    # upload / build / ranking kernels): positions and judge rows of every token, the dense
     # mask of every request entry by entry (822 MB on the device, one request at a time on the host),
     # the row descriptors (rebuilt into mask rows), the tile classifier and the order of the work
     # list against the oracle's mask, and the readout in both modes
@@ -230,7 +230,7 @@ def test_work_list_8b_single_launch_plan():
 
 
 def test_work_list_multi_kernel_plan():
-    # more than 8192 tokens: the plan is built by the separate upload / tokens / tiles / ranking
+    # more than 8192 tokens: the plan is built by the separate upload / build / ranking
     # kernels instead of the single-workgroup kernel
     rng = np.random.default_rng(11)
     B = 6

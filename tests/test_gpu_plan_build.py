@@ -1,13 +1,16 @@
 """Plans that are built by several launches, at the edges of their split: request data that fit the kernel
-arguments of the launch that uses them or not, with and without rows behind them to upload; tile counts
-around a workgroup (256), around what a ranking pass reads (512) and with a last wave of 1 to 4 tiles.
-Everything is whole numbers, against the oracle's mask and arrays."""
+arguments of the launch that uses them or not; tile counts around a workgroup (256), around what a ranking
+pass reads (512) and with a last wave of 1 to 4 tiles; and the single launch at its largest.  Each problem
+states the route that it is here for.  Everything is whole numbers, against the oracle's mask and arrays."""
 import pytest
+import torch
 
 import pv_workloads as wl
 from tests.test_gpu_mask_readout import check_plan, check_quad_list, check_work_list
 
 pytestmark = pytest.mark.gpu
+
+ARG_INTS, SMALL_TOKENS = 896, 8192       # ints of request data in kernel arguments; tokens of the single launch
 
 
 def even(lengths, k, s):
@@ -16,22 +19,33 @@ def even(lengths, k, s):
                       [[(j + 1) * (n - 9 - k * s) // (k + 1) for j in range(k)] for n in lengths])
 
 
+SINGLE, IN_ARGS, UPLOADED = "single launch", "data in the arguments", "data uploaded before"
 PROBLEMS = {
-    "few_tokens_many_short_rows": even([300] * 16, 2, 5),            # data in the arguments, short rows uploaded
-    "few_tokens_data_too_large": even([420] * 18, 40, 4),            # request data beyond the arguments
-    "one_tile_requests": even([32] * 70, 1, 3),                      # as many groups of tiles as tiles
-    "tiles_256": even([2720] * 3 + [32], 3, 7),
-    "tiles_257": even([2720] * 3 + [33], 3, 7),
-    "tiles_512": even([4096] * 4, 5, 33),
-    "tiles_513": even([4096] * 3 + [4097], 5, 33),
-    "tiles_515_no_segments": even([4096] * 4 + [70], 0, 1),
-    "single_launch_256_tiles": even([8187], 3, 64),                  # tiles and groups of four side by side
+    "few_tokens_many_short_rows": (even([300] * 16, 2, 5), IN_ARGS),
+    "few_tokens_data_too_large": (even([420] * 18, 40, 4), UPLOADED),
+    "one_tile_requests": (even([32] * 70, 1, 3), UPLOADED),          # as many groups of tiles as tiles
+    "one_tile_requests_in_arguments": (even([32] * 45, 1, 3), IN_ARGS),
+    "tiles_256_one_workgroup": (even([192] * 16 + [160] * 32, 1, 7), IN_ARGS),
+    "tiles_257_two_workgroups": (even([192] * 17 + [160] * 31, 1, 7), IN_ARGS),
+    "tiles_256": (even([2720] * 3 + [32], 3, 7), SINGLE),
+    "tiles_257": (even([2720] * 3 + [33], 3, 7), IN_ARGS),
+    "tiles_512": (even([4096] * 4, 5, 33), IN_ARGS),
+    "tiles_513": (even([4096] * 3 + [4097], 5, 33), IN_ARGS),
+    "tiles_515_no_segments": (even([4096] * 4 + [70], 0, 1), IN_ARGS),
+    "single_launch_256_tiles": (even([8187], 3, 64), SINGLE),        # tiles and groups of four side by side
+    "single_launch_most_requests": (wl.Problem([0] * 50, [1] * 50, [0] * 50, [1] * 50, [[]] * 50), SINGLE),
 }
 
 
 @pytest.mark.parametrize("name", list(PROBLEMS))
 def test_plan(name):
-    pr = PROBLEMS[name]
-    check_plan(pr)
+    pr, route = PROBLEMS[name]
+    ver = check_plan(pr)
+    head = ver.plan.view(torch.int32)[:36].cpu().tolist()            # off_short at 18, off_device_begin at 19
+    in_args, whole_image = head[18] <= ARG_INTS, head[19] <= ARG_INTS
+    single = whole_image and max(pr.total_tokens, pr.total_segments) <= SMALL_TOKENS
+    assert route == (SINGLE if single else IN_ARGS if in_args else UPLOADED), (head[18], head[19], pr.total_tokens)
+    if "tiles_" in name and name.split("tiles_")[1].split("_")[0].isdigit():
+        assert ver.sizes.n_q_tiles == int(name.split("tiles_")[1].split("_")[0])
     check_work_list(pr)
     check_quad_list(pr)
