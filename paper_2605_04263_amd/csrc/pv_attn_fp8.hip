@@ -208,8 +208,8 @@ __device__ __forceinline__ void wait_loads() {            // at most N loads of 
 // What bounds it: the matrix pipe, 12 products of 64 cycles and one of 32 per wave and step, and the issue of
 // the ~120 VALU instructions of the softmax beside them; hence the products of one tile are issued between
 // the softmax of its neighbour, and staging bypasses the registers.  Pass, us, against phases one after the
-// other with staging through registers: 4 x (2048 + 8192) tokens, 64/8 heads 8240 / 6920; 512 + 2048, 32/8
-// heads 90.6 / 80; 1024 + 4096, 40/8 heads (query tiles instead of one wave per head) 561 / 271.
+// other with staging through registers: 4 x (2048 + 8192) tokens, 64/8 heads 8272 / 6978; 512 + 2048, 32/8
+// heads 91.3 / 80.0; three requests of 1.5 to 4 K, 40/8 heads (query tiles instead of one wave per head) 300 / 162.
 // QT as in the bf16 kernel: the four waves are four consecutive query tiles of one query head; `tile` is
 // the union of the four (it drives the key loop and the staging), `mine` the wave's own.
 template <int D, int G, bool QT>
