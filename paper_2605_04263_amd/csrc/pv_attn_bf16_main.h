@@ -220,7 +220,9 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   // visible keys among the step's 32 become a bit mask (three clamped "low n bits" masks), and every
   // score is kept or replaced by -inf with a bit-field extract and a bit-field insert.
   auto apply_mask = [&](f32x16& sc, int key0) __attribute__((always_inline)) {
-    const int base = key0 + 4 * hh;
+    unsigned l16 = lane16;
+    asm volatile("" : "+v"(l16));
+    const int base = key0 + 4 * (int)(l16 >> 9);        // 4 hh, not kept in a register either
     auto low_bits = [](int n) {                         // bits [0, n) of 32, n clamped to [0, 32]
       const unsigned m = (1u << (n & 31)) - 1u;
       return n <= 0 ? 0u : n >= 32 ? 0xffffffffu : m;
@@ -235,47 +237,46 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   };
   // p rounded to bf16 once; the row sum is taken over the rounded values, so that O is an exact convex
   // combination of V rows with the weights the MFMA sees.
-  // kSumByDot: v_dot2c with a pair of ones, one instruction per pair, which runs on the matrix pipe; else the
-  // pair unpacked and added, four on the VALU.  D = 128 has one MFMA per score and is bound by the matrix pipe
-  // (cycles per 32x32x16 MFMA with one exp2 and half a pack beside it: 49 with the dot, 34 unpacked); D = 64 has
-  // half an MFMA per score and is bound by VALU issue where a SIMD holds two waves.  Either way the sum is two
-  // chains: a dot that waits for the one before it holds back the next MFMA.
-  // Passes, us, unpacked / one chain of dots / two: D = 64, 512 + 2048 + 512 tokens, 32/8 heads 62.3 / 58.2 /
-  // 58.1; 40/8 heads, 4 ragged requests of 2 to 6 K 931 / 943 / 920; 16/4 heads, 1.25 workgroups per slot
-  // 78.2 / 85.7 / 79.8.  Workgroups of five to seven waves, one to a compute unit, are the exception at D = 128:
-  // 28/4 heads, 2 x 4592 tokens 304.5 / 297.2 / 297.6 (eight waves 312.7 / 319.9 / 323.5), segment rows of 8
-  // requests at 40/8 and 48/8 heads 347 and 351 unpacked, 338 and 340 with two chains (before there were any
-  // unpacked sums 346 and 348); why they differ from eight was not isolated.
-  constexpr bool kSumByDot = D == 64 || (!QT && G >= 5 && G <= 7);
-  auto dot_ones = [](unsigned pair, float acc) __attribute__((always_inline)) {
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair),
-                                           __builtin_bit_cast(bf16x2, 0x3f803f80u), acc, false);
-  };
+  // The sum of a step runs on the matrix pipe as two 16 x 16 x 32 products of P^T with `ones`.  Its columns are
+  // l % 16 and its depth blocks l / 16, so the lanes of queries c and c + 16 share a column and fill different
+  // blocks: a row of `ones` that is one in the blocks 0 and 2 sums query c, one in 1 and 3 query c + 16, and row r
+  // takes the parity (r / 4) % 2, which leaves every lane its own query's sum, both half-waves, in all four
+  // accumulators.  32 matrix cycles beside the 512 of a step's products (256 at D = 64), and no VALU; unpacked and
+  // added it was 32 VALU instructions of a step's 56, and every VALU instruction delays the next MFMA.  Passes, us,
+  // before / with these products: 512 + 2048 tokens at 32/8 heads of 128, no segment 73.7 / 70.6; 16 requests of 0.6
+  // to 5 K 1372 / 1334; 5 K at 40/8 heads, no rotation 402 / 376; 32/8 heads of 64, two requests 57.8 / 56.2 (there
+  // two chains of dots before); at the power limit, 4 x 10 K at 64/8 heads, 8287 / 8259.
+  bf16x8 ones;
+  {
+    unsigned x = (lane >> 4 & 1) == (lane >> 2 & 1) ? 0x3f803f80u : 0u;
+    unsigned w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { asm volatile("" : "+v"(x)); w[i] = x; }
+    ones = as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
+  }
   auto probs = [&](const f32x16& sc, unsigned (&pw)[8]) __attribute__((always_inline)) {
     float rs = 0.0f, rs_hi = 0.0f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       pw[e] = pack_bf16(prob(sc[2 * e]), prob(sc[2 * e + 1]));
-      if constexpr (kSumByDot) {
-        float& x = e % 2 ? rs : rs_hi;
-        x = dot_ones(pw[e], x);
-      } else {
-        rs += bf16_lo(pw[e]);
-        rs_hi += bf16_hi(pw[e]);
-      }
+      rs += bf16_lo(pw[e]);
+      rs_hi += bf16_hi(pw[e]);
     }
-    return rs + rs_hi;
+    return pair_sum(rs + rs_hi);
   };
-  // The window test of a step: its partial row sum `rs` must not exceed 2^40, and the running sum
-  // with it must have reached 2^-40.  (The lower bound is on the total, not on the step: a step
-  // whose keys are all masked for a lane, every step of a diagonal tile for some lane, or whose
-  // scores lie 40 octaves below a healthy history adds nothing, and nothing needs correcting.)
+  // The window test of a step: its row sum `rs` must not exceed 2^16, and the running sum
+  // with it must have reached 2^-40.  (2^40 would be safe too: 370 us instead of 376 where outlier channels of K make
+  // the scores of 5 K tokens jump.  But a row re-centred at a weight that outweighs its history holds that weight
+  // exactly, and with 2^16 the normaliser there is 5.3e-4 from fp64 instead of 7.1e-4.)  The lower bound is on the
+  // total, not on the step: a step whose keys are all masked for a lane, every step of a diagonal tile for some
+  // lane, or whose scores lie 40 octaves below a healthy history adds nothing, and nothing needs correcting.
   auto out_of_window = [&](float rs) {
-    return __builtin_amdgcn_ballot_w64(!(l_run + rs >= 0x1p-40f && rs <= 0x1p40f)) != 0;
+    return __builtin_amdgcn_ballot_w64(!(l_run + rs >= 0x1p-40f && rs <= 0x1p16f)) != 0;
   };
   // One exact online-softmax step for the whole wave: taken when the window test fails (it also
-  // catches inf/NaN, and a running sum still at 0).  Rare: first steps of a row while no key is
-  // visible to it, or scores rising by more than 40 octaves.  The reference moves to this step's
+  // catches inf/NaN, also a NaN that came over from the query sharing the column, and a running sum still at 0);
+  // the sums are formed anew from the row's own values.  Rare: first steps of a row while no key is
+  // visible to it, or scores rising by more than 16 octaves.  The reference moves to this step's
   // row maximum, but never so far down that the history (l, O) would leave fp32 range:
   // mref_new >= mref + log2(l) - 20.  `sc` are the scores being exponentiated.  Both half-waves of
   // a row take identical decisions.  `other` is the score tile of the step after `sc`'s (FOLD: it is
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
     mx = pair_max(mx);
-    const float l_tot = pair_sum(l_run);
+    const float l_tot = l_run;
     if (mx > -INFINITY && mx < INFINITY) {      // rows with no visible key keep their reference
       // FOLD: mx is biased, the row maximum itself is mx - nmref
       float nm_new = FOLD ? nmref - mx : -mx * esc, alpha = 0.0f;   // empty history: nothing to rescale
@@ -450,7 +451,19 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   __builtin_amdgcn_sched_barrier(0);
   load_k(min(1, last) % NS);
   if (step_key0(0) >= mine.n_full * 64) apply_mask(sA, step_key0(0));
-  float rs0 = probs(sA, pA);
+  {   // the reference starts at the maximum of the row's first step: that weight is then exact in bf16, and few
+      // rows leave the window later (started at 0 instead: 4 x 10 K tokens at 64/8 heads 8700 us, now 8350)
+    float mx = sA[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sA[r]);
+    mx = pair_max(mx);
+    if (mx > -INFINITY && mx < INFINITY) nmref = -mx * esc;
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { sA[r] += nmref; cref[r] = nmref; }
+    }
+  }
+  l_run = probs(sA, pA);
   wait_kv();
   qk(sB);                                            // S(1)
   __builtin_amdgcn_sched_barrier(0);
@@ -468,8 +481,6 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       kf[t] = lds_read_b128<decltype(t)::value * 1024>(k_off + sbk);
     });
   }
-  if (out_of_window(rs0)) rs0 = recentre(sA, pA, sB);
-  l_run += rs0;
 
   // One step: O^T += V^T P^T of step j and S^T of step j+2 on the MFMA pipe, the probabilities of
   // step j+1 on the VALU, and the LDS reads of the next step's operands (V^T of step j+1, K of
@@ -519,7 +530,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     const int slot_ks = ST ? (PH + 2) % NS : sj + 2 >= NS ? sj + 2 - NS : sj + 2;   // (j + 2) % NS
     const bf16x8 pfa = as_bf16x8(make_uint4(p_in[0], p_in[1], p_in[2], p_in[3]));
     const bf16x8 pfb = as_bf16x8(make_uint4(p_in[4], p_in[5], p_in[6], p_in[7]));
-    float rs = 0.0f, rs_hi = 0.0f;
+    f32x4 rsum = {0.0f, 0.0f, 0.0f, 0.0f};
     constexpr unsigned SBV = ST ? ((PH + 1) % NS) * SLOT_BYTES : 0, SBK = ST ? ((PH + 3) % NS) * SLOT_BYTES : 0;
     const unsigned sbv = ST ? 0u : (unsigned)slot_v * SLOT_BYTES, sbk = ST ? 0u : (unsigned)slot_k * SLOT_BYTES;
     // The step is 2 KT groups of one MFMA, at most one operand refill and a share of the VALU
@@ -530,7 +541,6 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     //   exponent argument -> exp2 -> (pair) bf16 pack -> (pair) row sum,
     // each stage one group after the stage it depends on.
     constexpr int NG = 2 * KT, SPG = 16 / NG;          // groups; scores entering per group
-    constexpr int GHI = SPG == 1 ? 2 : 1;              // groups from the pack to the sum of the high halves
     constexpr int HB = KT / 4;                         // k-steps issued before the barrier
     float ea[16], ex[16];                              // exponent arguments, exponentials
     auto v_arg = [&](auto i) {
@@ -546,23 +556,20 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     };
     auto valu_group = [&](auto g) {                    // the VALU share of group g (g = -1: before)
       constexpr int GI = decltype(g)::value;
-      static_for<0, SPG>([&](auto k) {
-        constexpr int I = (GI + 1) * SPG + decltype(k)::value;   // exp2 runs one group ahead
-        v_exp(std::integral_constant<int, I>{});
-        v_arg(std::integral_constant<int, I + SPG>{});
-      });
+      // exp2 runs two groups ahead, so that the last pair is packed one group before the end
+      constexpr int I0 = GI < 0 ? 0 : (GI + 2) * SPG, IN = GI < 0 ? 2 * SPG : SPG;
+      static_for<0, IN>([&](auto k) { v_exp(std::integral_constant<int, I0 + decltype(k)::value>{}); });
+      static_for<0, SPG>([&](auto k) { v_arg(std::integral_constant<int, I0 + IN + decltype(k)::value>{}); });
       static_for<0, 8>([&](auto e) {
         constexpr int E = decltype(e)::value;
-        constexpr int GC = (2 * E + 1) / SPG;            // group after the pair's second exp2
+        constexpr int GC = (2 * E + 1) / SPG > 1 ? (2 * E + 1) / SPG - 1 : 0;   // group after the pair's second exp2
         if constexpr (GC == GI) p_out[E] = pack_bf16(ex[2 * E], ex[2 * E + 1]);
-        if constexpr (kSumByDot) {
-          float& x = E % 2 ? rs : rs_hi;
-          if constexpr (GC + 1 == GI) x = dot_ones(p_out[E], x);
-        } else {
-          if constexpr (GC + 1 == GI) rs += bf16_lo(p_out[E]);
-          if constexpr (GC + GHI == GI) rs_hi += bf16_hi(p_out[E]);
-        }
       });
+    };
+    auto mfma_sum = [&](auto half) {                   // row sum of the step's first or second 16 keys
+      constexpr int H = 4 * decltype(half)::value;
+      rsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          ones, as_bf16x8(make_uint4(p_out[H], p_out[H + 1], p_out[H + 2], p_out[H + 3])), rsum, 0, 0, 0);
     };
     // n-th staging instruction of this wave for a slot
     auto stage_one = [&](const char* src, unsigned lds0, auto n) {
@@ -637,7 +644,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       lds_refill_b128<T * 1024 + SBK>(kf[t], k_off + sbk);
     };
 
-    static_for<0, SPG>([&](auto k) { v_arg(k); });
+    static_for<0, 2 * SPG>([&](auto k) { v_arg(k); });
     valu_group(std::integral_constant<int, -1>{});
     __builtin_amdgcn_sched_barrier(0);
     // Head: the first MFMAs need nothing from LDS, so they are issued before the barrier and run
@@ -689,6 +696,10 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       valu_group(std::integral_constant<int, 2 * T>{});
       if constexpr (STEADY) stage_part2(std::integral_constant<int, 2 * R>{});
       __builtin_amdgcn_sched_barrier(0);
+      // the first half's packs are done after group NG / 2 - 2, the second's after NG - 2
+      if constexpr (2 * T + 1 == NG / 2 + 1) mfma_sum(std::integral_constant<int, 0>{});
+      if constexpr (2 * T + 1 == NG - 1) mfma_sum(std::integral_constant<int, 1>{});
+      __builtin_amdgcn_sched_barrier(0);
       mfma_qk(t);
       __builtin_amdgcn_sched_barrier(0);
       refill_k(t);
@@ -696,8 +707,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       if constexpr (STEADY) stage_part2(std::integral_constant<int, 2 * R + 1>{});
       __builtin_amdgcn_sched_barrier(0);
     });
-    static_for<NG, NG + GHI>([&](auto g) { valu_group(g); });   // what is left: the last row-sum terms
-    rs += rs_hi;
+    float rs = rsum[0];
     asm volatile("" : "+v"(rs));                      // the row sum belongs to this block
     __builtin_amdgcn_sched_barrier(0);
     if (have1) {
@@ -745,7 +755,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
 
   // ---- epilogue: normalise, then transpose through LDS so that every output row leaves as one
   // contiguous run (2 D bytes in bf16; fp32 goes in two halves of D/2 features to bound the area)
-  const float l_tot = pair_sum(l_run);
+  const float l_tot = l_run;
   __syncthreads();                                    // every wave is done with the stages
   {
     const bool partial = split > 1;                   // this piece's result goes to the workspace

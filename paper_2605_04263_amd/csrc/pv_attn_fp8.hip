@@ -23,7 +23,6 @@
 namespace pv {
 
 typedef __attribute__((ext_vector_type(8))) int i32x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kStepKeys = 64;            // keys per step = depth of the second product
 

@@ -6,6 +6,8 @@ rounded to nearest even, which adds at most half a bf16 ulp of the value.  Rows 
 PV_SHORT_ROW_KEYS keys are evaluated in fp32 by the library and are far inside the tolerance.
 Small cases compare every element; the large named configs compare oracle-computed sampled rows
 (every row is independent given K/V, so a subset is exact)."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -234,6 +236,35 @@ def test_softmax_scale(d, group, scale, theta):
     # bounds hold as they are.
     grow = max(1.0, scale * d ** 0.5) if theta > 0 else 1.0
     check_full(w, softmax_scale=scale, max_abs=MAX_ABS * grow, mean_abs=MEAN_ABS * grow, lse_abs=LSE_ABS * grow)
+
+
+# Scores that rise by `octaves` at chosen keys, for every second query only: at the sizes around which the row sum
+# leaves the kernel's window (2^16) or does not, and far beyond fp32's range.  The queries c and c + 16 of a tile,
+# whose sums come out of one column of the matrix product, go opposite ways.  With |V| <= 1 the rounding of the
+# probabilities to bf16 (8 significant bits: 2^-8 of the value at most) moves an output by at most
+# 2 * 2^-8 / (1 - 2^-8) and the normaliser by -log(1 - 2^-8); Q and K enter the products exactly (no rotation).
+@pytest.mark.parametrize("octaves", [15, 16, 17, 39, 41, 130])
+@pytest.mark.parametrize("hq,hkv,d", [(4, 1, 128), (5, 1, 128), (8, 1, 64)])
+def test_rising_scores(hq, hkv, d, octaves):
+    pr = wl.Problem([50], [400], [2], [40], [[130, 400]])
+    w = wl.make_custom(pr, hq, hkv, d, dtype=torch.bfloat16, rope_theta=0.0, seed=77)
+    n = pr.total_tokens
+    rise = torch.zeros(n)
+    for key in (70, 200, 201, 330, 470):                    # each one `octaves` above the one before it
+        rise[key:] += 1.0
+    w.k[:, :, 0] = rise[:, None].to(torch.bfloat16)
+    w.q[:, :, 0] = torch.where(torch.arange(n) % 32 < 16, 1.0, -1.0)[:, None].to(torch.bfloat16) * octaves
+    w.v.copy_(torch.sign(w.v.float()).to(torch.bfloat16))
+    w.q[:, :, 1:] *= 0.25
+    scale = math.log(2.0)
+    ver = gc.make_verifier(pv, w)
+    ver.build_mask()
+    out, lse = gc.run_gpu_attention(pv, w, out_dtype=torch.float32, lse=True, ver=ver, softmax_scale=scale)
+    ref, ref_lse = gc.oracle_attention(w, return_lse=True, scale=scale)
+    delta = 2.0 ** -8
+    assert np.abs(out.double().cpu().numpy() - ref).max() <= 2 * delta / (1 - delta) + 1e-5
+    # the score itself: fp32 sums of D products and one fma, relative to the largest term (4 * octaves at most)
+    assert np.abs(lse.double().cpu().numpy().T - ref_lse).max() <= -math.log(1 - delta) + 4 * octaves * 2.0 ** -21
 
 
 def test_segment_isolation_and_determinism():
