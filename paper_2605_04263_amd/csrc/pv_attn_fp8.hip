@@ -30,9 +30,10 @@ __device__ __forceinline__ f32x16 mfma_fp8(const i32x8& a, const i32x8& b, const
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);   // both operands E4M3, no block scales
 }
 // The same product with the B operand scaled by 2^-4 in the instruction (block scales are E8M0
-// exponents, 0x7f = 1; checked on the device): used for the low part of Q.
+// exponents, 0x7f = 1; checked on the device; byte 0 of the word scales A, byte 1 B, so that the two take one
+// register): used for the low part of Q.
 __device__ __forceinline__ f32x16 mfma_fp8_b_sixteenth(const i32x8& a, const i32x8& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0x7f, 0, 0x7b);
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0x7b7f, 1, 0x7b7f);
 }
 // 16 x 16 x 128: lane l holds row (or column) l % 16 and the depth block l / 16; the accumulator has column
 // l % 16, rows 4 (l / 16) ..
@@ -204,11 +205,15 @@ __device__ __forceinline__ void wait_loads() {            // at most N loads of 
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
-// What bounds it: the matrix pipe, 12 products of 64 cycles and one of 32 per wave and step, and the issue of
-// the ~120 VALU instructions of the softmax beside them; hence the products of one tile are issued between
-// the softmax of its neighbour, and staging bypasses the registers.  Pass, us, against phases one after the
-// other with staging through registers: 4 x (2048 + 8192) tokens, 64/8 heads 8272 / 6978; 512 + 2048, 32/8
-// heads 91.3 / 80.0; three requests of 1.5 to 4 K, 40/8 heads (query tiles instead of one wave per head) 300 / 162.
+// What bounds it: VALU issue.  A wave's step has 12 products of 64 matrix cycles and one of 32 (800), and ~115 VALU
+// instructions of the softmax, 32 of them exponentials (16 cycles each): ~850 cycles of issue, and a product holds
+// back VALU issue for about half its time.  Hence staging bypasses the registers, and every product of a step has its
+// share of the softmax beside it: with the softmax of a tile beside S^T of the next and only the row maxima beside
+// O^T, the two waves of a SIMD met the barrier in the same phase where they belong to one workgroup.  Passes, us,
+// before / with it: 4 x (2048 + 8192) tokens, 64/8 heads 7057 / 6731; 4000 + 512, 28/4 heads 160.2 / 153.8;
+// 1024 + 4096, 64/8 heads, no rotation 439 / 419; four waves to a workgroup: 512 + 2048, 32/8 heads 78.8 / 79.5, 8
+// ragged requests 575.6 / 574.5, three requests at 40/8 heads 327.4 / 324.8.  Matrix pipe 52 / 56 % busy, 14.6 / 13.7 M
+// cycles for the first of them.
 // QT as in the bf16 kernel: the four waves are four consecutive query tiles of one query head; `tile` is
 // the union of the four (it drives the key loop and the staging), `mine` the wave's own.
 template <int D, int G, bool QT>
@@ -267,7 +272,6 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   const bool valid = qrow < mine.rows;
   // pad lanes repeat the last row (never stored)
   const int64_t g = (int64_t)tile.tok_base + tile.t0 + min((QT ? 32 * wave : 0) + qrow, tile.rows - 1);
-  const int i_loc = valid ? mine.t0 + qrow : -1;
   int a_end = 0, b_start = 0;
   if (valid) { a_end = plan[h.off_aend + g]; b_start = plan[h.off_bstart + g]; }
 
@@ -332,7 +336,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
         hi[j] = __builtin_fmaf(l0, wsn, h0 * wc);
       }
     }
-    stage_v(0); stage_k(2); stage_v(1); stage_k(3); stage_v(2);
+    stage_v(0); stage_k(2); stage_v(1); stage_k(3);
     float amax = 0.0f;
 #pragma unroll
     for (int j = 0; j < 32; ++j) amax = fmaxf(amax, fmaxf(fabsf(lo[j]), fabsf(hi[j])));
@@ -346,8 +350,8 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       const float x0 = x[0] * fac, x1 = x[1] * fac, x2 = x[2] * fac, x3 = x[3] * fac;
       const unsigned w = pack_fp8x4(x0, x1, x2, x3);
       top = (int)w;
-      rest = (int)pack_fp8x4((x0 - fp8_byte(w, 0)) * 16.0f, (x1 - fp8_byte(w, 1)) * 16.0f,
-                             (x2 - fp8_byte(w, 2)) * 16.0f, (x3 - fp8_byte(w, 3)) * 16.0f);
+      const f32x2 t0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false), t1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true);
+      rest = (int)pack_fp8x4((x0 - t0[0]) * 16.0f, (x1 - t0[1]) * 16.0f, (x2 - t1[0]) * 16.0f, (x3 - t1[1]) * 16.0f);
     };
 #pragma unroll
     for (int w = 0; w < 8; ++w) {
@@ -374,16 +378,22 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
 #pragma unroll
     for (int w = 0; w < 8; ++w) { asm volatile("" : "+v"(x)); ones[w] = x; }
   }
+  auto sum_product = [&](const i32x8& p) __attribute__((always_inline)) {
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    return mfma_fp8_16(ones, p, zero);
+  };
   float mref = -INFINITY;                                  // reference of the exponent, log2 units
 
-  // ---- pipeline.  Step j: S^T of tile j + 1 beside the probabilities of tile j, then O^T += V^T P^T of
-  // tile j beside the row maxima of tile j + 1.  One set of operand registers serves both products: an
-  // operand of K is refilled with one of V^T as soon as it is consumed, and the other way round.
-  i32x8 op[4];          // K operand (half u, features 64 t ..) is op[2 t + u]; V^T operand of features 32 db .. is op[db]
-  i32x8 pb;             // probabilities of the current tile
+  // ---- pipeline.  Step j: O^T += V^T P^T of tile j and S^T of tile j + 2 on the matrix pipe, the probabilities of
+  // tile j + 1 between them, so that every product has softmax work beside it.  Eight operands a step (a 32-key half
+  // of K by 64 features, or 32 features of V^T) go through four register sets in the order of their use,
+  //   K(u0,t0) V0 K(u0,t1) V1 K(u1,t0) K(u1,t1) V2 V3
+  // and a set is refilled with the operand four places on as soon as it has been consumed.
+  i32x8 op[4];
+  i32x8 pA, pB;         // probabilities of two tiles, alternating roles from step to step
 #pragma unroll
-  for (int w = 0; w < 8; ++w) pb[w] = 0;
-  f32x16 sA[2], sB[2];  // score tiles (two 32-key halves each)
+  for (int w = 0; w < 8; ++w) { pA[w] = 0; pB[w] = 0; }
+  f32x16 sA[2], sB[2];  // score tiles (two 32-key halves each), likewise
   auto load_op = [&](i32x8& r, int chunk) __attribute__((always_inline)) {
     const uint4 a0 = smem[chunk], a1 = smem[chunk + 64];
     r[0] = (int)a0.x; r[1] = (int)a0.y; r[2] = (int)a0.z; r[3] = (int)a0.w;
@@ -394,18 +404,18 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   // V^T is read from the slot of zeros: a NaN in it is not this tile's.  Every such tile is masked, so the test
   // sits with the mask, and a step in the open pays for a scalar select.  (Zeroing the operands instead, behind
   // a branch of its own, cost 1.5 to 3 % of the pass.)
-  bool foreign = false;                                    // the tile of the current scores is such a one
-  auto v_chunk = [&](int j) { return (QT && foreign ? ZERO : (NS + (j & (NS - 1))) * CH) + lane; };
-  constexpr int KOFF[4] = {0, 2 * 128, 1 * 128, 3 * 128};  // chunk of op[2 t + u]: (2 u + t) * 128
-  // product x of the eight of S^T: t = x / 4, high or low term of Q = (x / 2) % 2, u = x % 2
-  auto mfma_qk = [&](f32x16 (&s)[2], auto x) __attribute__((always_inline)) {
-    constexpr int X = decltype(x)::value, t = X / 4, lo = (X / 2) % 2, u = X % 2;
-    if constexpr (X < 2) {
+  bool foreign = false, foreign_next = false;              // tile j, tile j + 1 is such a one
+  auto v_chunk = [&](int j, bool zeros) { return (QT && zeros ? ZERO : (NS + (j & (NS - 1))) * CH) + lane; };
+  constexpr auto koff = [](int u, int t) { return (2 * u + t) * 128; };
+  // one of the eight products of S^T: half u of the keys, half t of the features, high or low term of Q
+  auto mfma_qk = [&](f32x16 (&s)[2], const i32x8& a, auto u, auto t, auto lo) __attribute__((always_inline)) {
+    constexpr int U = decltype(u)::value, T = decltype(t)::value, LO = decltype(lo)::value;
+    if constexpr (T == 0 && LO == 0) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[u][r] = 0.0f;
+      for (int r = 0; r < 16; ++r) s[U][r] = 0.0f;
     }
-    if constexpr (lo) s[u] = mfma_fp8_b_sixteenth(op[2 * t + u], qlo[t], s[u]);
-    else s[u] = mfma_fp8(op[2 * t + u], qf[t], s[u]);
+    if constexpr (LO) s[U] = mfma_fp8_b_sixteenth(a, qlo[T], s[U]);
+    else s[U] = mfma_fp8(a, qf[T], s[U]);
   };
   // Row predicate: the keys of half u that this lane holds are key0 + 32 u + 4 hh + c,
   // c = 8 (r / 4) + r % 4; the row's visible ones among the 32 become a bit mask, and a score
@@ -415,9 +425,14 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       const unsigned m = (1u << (n & 31)) - 1u;
       return n <= 0 ? 0u : n >= 32 ? 0xffffffffu : m;
     };
+    // (4 hh and the row's index are formed anew from an opaque lane index: the register file is full, and what lives
+    // through the loop for the sake of a rare path ends up in scratch memory)
+    unsigned l16 = lane16;
+    asm volatile("" : "+v"(l16));
+    const int row = (int)((l16 >> 4) & 31u), i_loc = row < mine.rows ? mine.t0 + row : -1;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int base = key0 + 32 * u + 4 * hh;
+      const int base = key0 + 32 * u + 4 * (int)(l16 >> 9);
       const unsigned vis = low_bits(a_end - base) | (low_bits(i_loc - base + 1) & ~low_bits(b_start - base));
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -426,177 +441,210 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       }
     }
   };
+  // returns whether the tile is one that only other query tiles read
   auto mask_tile = [&](f32x16 (&s)[2], int jt) __attribute__((always_inline)) {
-    foreign = false;
+    bool other = false;
     if (__builtin_expect(jt >= mine.n_full, 0)) {
-      if constexpr (QT) foreign = jt >= mine.n_a && (jt < mine.jb0 || jt >= mine.jb1);
+      if constexpr (QT) other = jt >= mine.n_a && (jt < mine.jb0 || jt >= mine.jb1);
       apply_mask(s, jt * kStepKeys);
     }
+    return other;
   };
   // Running reference: moved up when a tile's largest exponent exceeds it by more than 0.75 octave
-  // (probabilities scaled by 2^8 then stay below 2^8.75 = 431 < 448, the largest E4M3 value).
-  auto raise_reference = [&](float mx) __attribute__((always_inline)) {
-    mx = pair_max(mx) * c_row;                              // c_row > 0
-    const bool raise = mx > mref + 0.75f;                   // (mref = -inf: any visible key)
-    if (__builtin_amdgcn_ballot_w64(raise) != 0) {
-      const float m_new = raise ? mx : mref;
-      const float alpha = mref == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mref - m_new);   // 1 when unchanged
-      mref = m_new;
+  // (probabilities scaled by 2^8 then stay below 2^8.75 = 431 < 448, the largest E4M3 value).  O and the row sum
+  // follow one step later, when the tile before it, whose probabilities stand on the old reference, is in them.
+  float bias = 0.0f;                                       // 8 - mref; 0 while no key has been seen (every S is -inf, p = 0)
+  float alpha = 1.0f;                                      // what O and the row sum still have to be scaled by
+  uint64_t rescale = 0;                                    // the lanes whose alpha is not 1
+  auto apply_alpha = [&]() __attribute__((always_inline)) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        o[0][r] *= alpha; o[1][r] *= alpha; o[2][r] *= alpha; o[3][r] *= alpha;
-      }
-      l_run *= alpha;
+    for (int r = 0; r < 16; ++r) {
+      o[0][r] *= alpha; o[1][r] *= alpha; o[2][r] *= alpha; o[3][r] *= alpha;
     }
+    l_run *= alpha;
   };
-  auto max_of = [&](float mx, const f32x16& s, auto r0, auto n) __attribute__((always_inline)) {
-    constexpr int R0 = decltype(r0)::value, N = decltype(n)::value;
-    static_for<0, N / 2>([&](auto i) {
-      constexpr int I = R0 + 2 * decltype(i)::value;
-      mx = fmaxf(fmaxf(mx, s[I]), s[I + 1]);
+  auto raise_to = [&](float mx) __attribute__((always_inline)) {   // mx: the tile's largest exponent
+    const bool raise = mx > mref + 0.75f;                  // (mref = -inf: any visible key)
+    const float m_new = raise ? mx : mref;
+    alpha = mref == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mref - m_new);   // 1 when unchanged
+    mref = m_new;
+    bias = mref == -INFINITY ? 0.0f : 8.0f - mref;
+  };
+  auto max3 = [](float a, float b, float c) __attribute__((always_inline)) { return fmaxf(fmaxf(a, b), c); };
+  auto max_half = [&](const f32x16& s) __attribute__((always_inline)) {    // of elements 0 .. 14
+    float mx = max3(s[0], s[1], s[2]);
+    static_for<0, 6>([&](auto i) {
+      constexpr int I = 3 + 2 * decltype(i)::value;
+      mx = max3(mx, s[I], s[I + 1]);
     });
     return mx;
   };
   using c0 = std::integral_constant<int, 0>;
-  using c8 = std::integral_constant<int, 8>;
+  using c1 = std::integral_constant<int, 1>;
   using c16 = std::integral_constant<int, 16>;
-
-  // S^T of tile j + 1 into s_out (QK) and P of tile j from s_in.  The work is issued in groups of one
-  // product and the softmax of four scores; exponent argument, exponential and rounding of a score sit in
-  // consecutive groups, so that none waits for its input in front of a product.
-  auto scores = [&](auto with_qk, int j, f32x16 (&s_in)[2], f32x16 (&s_out)[2]) __attribute__((always_inline)) {
-    constexpr bool QK = decltype(with_qk)::value;
-    const float bias = mref == -INFINITY ? 0.0f : 8.0f - mref;   // no key seen yet: every S is -inf, p = 0
-    const int vc = v_chunk(j);
-    float ea[8][4], ex[8][4];
-    auto v_arg = [&](auto w) {
-      constexpr int W = decltype(w)::value;
-      if constexpr (W < 8)
-        static_for<0, 4>([&](auto e) {
-          constexpr int E = decltype(e)::value;
-          ea[W][E] = __builtin_fmaf(s_in[W / 4][4 * (W % 4) + E], c_row, bias);
-        });
-    };
-    v_arg(c0{});
-    static_for<0, 8>([&](auto g8) {
-      constexpr int X = decltype(g8)::value;
-      if constexpr (QK) mfma_qk(s_out, g8);
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (QK && X == 1) {
-        // V^T of tile j and K of tile j + 2 have to be there; younger: V^T(j+1), K(j+3), V^T(j+2).  Every
-        // wave is done with K of tile j and V^T of tile j - 1, whose slots the loads below refill.
-        wait_loads<3 * NREP>();
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-      }
-      if constexpr (QK && X >= 2) {                        // K of tile j + 4, then V^T of tile j + 3
-        static_for<0, 2 * NREP>([&](auto y) {
-          constexpr int Y = decltype(y)::value;
-          if constexpr (2 + Y * 6 / (2 * NREP) == X) {
-            if constexpr (Y < NREP) stage_one(kw, 0u, j + NS, Y);
-            else stage_one(vw, NS * TILE_BYTES, j + NS - 1, Y - NREP);
-          }
-        });
-        if constexpr ((X / 2) % 2) load_op(op[2 * (X / 4) + X % 2], vc + (2 * (X / 4) + X % 2) * 128);
-      }
-      static_for<0, 4>([&](auto e) {
-        constexpr int E = decltype(e)::value;
-        ex[X][E] = __builtin_amdgcn_exp2f(ea[X][E]);
-        asm volatile("" :: "v"(ex[X][E]));                 // a use in this group: not sunk to the pack
-      });
-      v_arg(std::integral_constant<int, X + 1>{});
-      if constexpr (X > 0) pb[X - 1] = (int)pack_fp8x4(ex[X - 1][0], ex[X - 1][1], ex[X - 1][2], ex[X - 1][3], pb[X - 1]);
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    pb[7] = (int)pack_fp8x4(ex[7][0], ex[7][1], ex[7][2], ex[7][3], pb[7]);
-  };
   // The sum over a tile's probabilities.  A query's NaN (a NaN in its Q row, or in a key that its neighbour
   // does not see) meets the zeros of the query that shares its column: such a tile is summed from the codes.
-  auto add_row_sum = [&](const f32x4& d) __attribute__((always_inline)) {
-    float rs = d[0];
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(rs != rs) != 0, 0)) {
-      rs = 0.0f;
+  auto sum_codes = [&](const i32x8& p) __attribute__((always_inline)) {
+    float rs = 0.0f;
 #pragma unroll
-      for (int w = 0; w < 8; ++w) {
-        const unsigned c = (unsigned)pb[w];
-        rs += (fp8_byte(c, 0) + fp8_byte(c, 1)) + (fp8_byte(c, 2) + fp8_byte(c, 3));
-      }
-      rs = pair_sum(rs);
+    for (int w = 0; w < 8; ++w) {
+      const unsigned c = (unsigned)p[w];
+      rs += (fp8_byte(c, 0) + fp8_byte(c, 1)) + (fp8_byte(c, 2) + fp8_byte(c, 3));
     }
+    return pair_sum(rs);
+  };
+  auto add_row_sum = [&](const f32x4& sum, const i32x8& p) __attribute__((always_inline)) {
+    float rs = sum[0];
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(rs != rs) != 0, 0)) rs = sum_codes(p);
     l_run += rs;
   };
-  const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-  // O^T and the row sums (through a tile of ones) of tile j; then the reference for tile j + 1, whose
-  // scores are s_next, and the K operands of tile j + 2.
-  auto values = [&](int j, f32x16 (&s_next)[2]) __attribute__((always_inline)) {
-    const int kc = k_chunk(j + 2);
-    o[0] = mfma_fp8(op[0], pb, o[0]);
+
+  // PV, QK: which of the two products the step has.  Step -1 forms S^T of tile 1 beside the probabilities of tile 0,
+  // step last - 1 has no tile left to score.
+  auto step = [&](int j, f32x16 (&s_in)[2], f32x16 (&s_out)[2], i32x8& p_in, i32x8& p_out, auto with_pv,
+                  auto with_qk) __attribute__((always_inline)) {
+    constexpr bool PV = decltype(with_pv)::value, QK = decltype(with_qk)::value;
+    const int kc = k_chunk(j + 2), vc = v_chunk(j, foreign), kc1 = k_chunk(j + 3), vc1 = v_chunk(j + 1, foreign_next);
+    // Softmax share of group g: the exponentials of three scores, the arguments of the next group's, and the
+    // rounding of the pairs that the group before completed, so that none waits for its input in front of a product.
+    float ea[32], ex[32];
+    auto v_arg = [&](auto i) {
+      constexpr int I = decltype(i)::value;
+      if constexpr (I < 32) ea[I] = __builtin_fmaf(s_in[I / 16][I % 16], c_row, bias);
+    };
+    auto v_exp = [&](auto i) {
+      constexpr int I = decltype(i)::value;
+      if constexpr (I < 32) {
+        ex[I] = __builtin_amdgcn_exp2f(ea[I]);
+        asm volatile("" :: "v"(ex[I]));                    // a use in this group: not sunk to the pack
+      }
+    };
+    auto softmax = [&](auto g) {
+      constexpr int GI = decltype(g)::value;
+      static_for<0, 16>([&](auto e) {                      // pair e: scores 2 e and 2 e + 1
+        constexpr int E = decltype(e)::value;
+        if constexpr ((2 * E + 1) / 3 + 1 == GI) {
+          if constexpr (E % 2 == 0) p_out[E / 2] = __builtin_amdgcn_cvt_pk_fp8_f32(ex[2 * E], ex[2 * E + 1], p_out[E / 2], false);
+          else p_out[E / 2] = __builtin_amdgcn_cvt_pk_fp8_f32(ex[2 * E], ex[2 * E + 1], p_out[E / 2], true);
+          asm volatile("" :: "v"(p_out[E / 2]));           // a use here: not sunk behind the branches below
+        }
+      });
+      static_for<0, 3>([&](auto k) { v_exp(std::integral_constant<int, 3 * GI + decltype(k)::value>{}); });
+      static_for<0, 3>([&](auto k) { v_arg(std::integral_constant<int, 3 * GI + 3 + decltype(k)::value>{}); });
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto mfma_done = [&]() { __builtin_amdgcn_sched_barrier(0); };   // the product first, its group's other work behind it
+    auto stage = [&](auto x) {                             // K of tile j + 5, then V^T of tile j + 3
+      constexpr int X = decltype(x)::value;
+      if constexpr (X < NREP) stage_one(kw, 0u, j + 5, X);
+      else if constexpr (X < 2 * NREP) stage_one(vw, NS * TILE_BYTES, j + 3, X - NREP);
+    };
+#define PV_G(n) std::integral_constant<int, n>{}
+    static_for<0, 3>([&](auto k) { v_arg(k); });
     __builtin_amdgcn_sched_barrier(0);
-    load_op(op[0], kc + KOFF[0]);
-    o[1] = mfma_fp8(op[1], pb, o[1]);
+    auto qk = [&](const i32x8& k, auto u, auto t, auto lo) {
+      if constexpr (QK) { mfma_qk(s_out, k, u, t, lo); mfma_done(); }
+    };
+    auto pv = [&](auto x, const i32x8& v) {
+      constexpr int X = decltype(x)::value;
+      if constexpr (PV) { o[X] = mfma_fp8(v, p_in, o[X]); mfma_done(); }
+    };
+    qk(op[0], c0{}, c0{}, c0{}); softmax(PV_G(0));
+    pv(PV_G(0), op[1]); if constexpr (QK) load_op(op[1], kc + koff(1, 1)); softmax(PV_G(1));
+    qk(op[0], c0{}, c0{}, c1{}); if constexpr (QK) load_op(op[0], kc + koff(1, 0)); softmax(PV_G(2));
+    qk(op[2], c0{}, c1{}, c0{}); softmax(PV_G(3));
+    pv(PV_G(1), op[3]); if constexpr (PV) load_op(op[3], vc + 3 * 128); softmax(PV_G(4));
+    qk(op[2], c0{}, c1{}, c1{}); if constexpr (PV) load_op(op[2], vc + 2 * 128); softmax(PV_G(5));
+    qk(op[0], c1{}, c0{}, c0{}); softmax(PV_G(6));
+    // K of tile j + 3 and V^T of tile j + 1 have to be there; younger: K(j+4), V^T(j+2).  Every wave is done with K of
+    // tile j + 1 and V^T of tile j - 1, whose slots the loads below refill.
+    wait_loads<2 * NREP>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    qk(op[0], c1{}, c0{}, c1{}); if constexpr (QK) { load_op(op[0], kc1 + koff(0, 0)); stage(PV_G(0)); } softmax(PV_G(7));
+    qk(op[1], c1{}, c1{}, c0{}); if constexpr (QK) stage(PV_G(1)); softmax(PV_G(8));
+    qk(op[1], c1{}, c1{}, c1{}); load_op(op[1], vc1); if constexpr (QK) stage(PV_G(2)); softmax(PV_G(9));
+    pv(PV_G(2), op[2]); if constexpr (QK) { load_op(op[2], kc1 + koff(0, 1)); stage(PV_G(3)); } softmax(PV_G(10));
+    softmax(PV_G(11));
+#undef PV_G
+    foreign = foreign_next;
+    if constexpr (QK) foreign_next = mask_tile(s_out, step_tile(j + 2));
+    f32x4 row_sum = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (PV) row_sum = sum_product(p_in);
     __builtin_amdgcn_sched_barrier(0);
-    load_op(op[1], kc + KOFF[1]);
-    mask_tile(s_next, step_tile(j + 1));
-    const f32x4 row_sum = mfma_fp8_16(ones, pb, zero4);
+    float m0 = 0.0f, mx = 0.0f;
+    if constexpr (QK) {
+      m0 = max_half(s_out[0]);
+      asm volatile("" : "+v"(m0));                         // stays here, beside the products
+    }
     __builtin_amdgcn_sched_barrier(0);
-    float mx = max_of(s_next[0][0], s_next[0], c0{}, c16{});
+    if constexpr (PV) o[3] = mfma_fp8(op[3], p_in, o[3]);
     __builtin_amdgcn_sched_barrier(0);
-    o[2] = mfma_fp8(op[2], pb, o[2]);
-    __builtin_amdgcn_sched_barrier(0);
-    load_op(op[2], kc + KOFF[2]);
-    mx = max_of(mx, s_next[1], c0{}, c8{});
-    __builtin_amdgcn_sched_barrier(0);
-    o[3] = mfma_fp8(op[3], pb, o[3]);
-    __builtin_amdgcn_sched_barrier(0);
-    load_op(op[3], kc + KOFF[3]);
-    mx = max_of(mx, s_next[1], c8{}, c8{});
-    add_row_sum(row_sum);
-    raise_reference(mx);
+    load_op(op[3], vc1 + 128);
+    if constexpr (QK) mx = pair_max(fmaxf(max_half(s_out[1]), max3(s_out[1][15], s_out[0][15], m0))) * c_row;   // c_row > 0
+    if constexpr (PV) {
+      asm volatile("" :: "v"(row_sum));                    // (its unused elements are not handed to the maxima, which would wait)
+      add_row_sum(row_sum, p_in);
+      if (__builtin_expect(rescale != 0, 0)) apply_alpha();
+    }
+    if constexpr (QK) {
+      rescale = __builtin_amdgcn_ballot_w64(mx > mref + 0.75f);
+      if (__builtin_expect(rescale != 0, 0)) raise_to(mx);
+    }
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  // prologue: S^T of tile 0, its reference, and the K operands of tile 1
+  // ---- prologue: S^T of tile 0 and its reference
   if constexpr (QT) {
 #pragma unroll
     for (int n = 0; n < CH / (G * 64); ++n) smem[ZERO + n * (G * 64) + tid] = make_uint4(0u, 0u, 0u, 0u);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the barrier below makes them everyone's
   }
-  wait_loads<5 * NREP>();
+  wait_loads<4 * NREP>();                                  // K of tiles 0 and 1
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  static_for<0, 4>([&](auto x) { load_op(op[decltype(x)::value], k_chunk(0) + KOFF[decltype(x)::value]); });
-  static_for<0, 8>([&](auto x) { mfma_qk(sA, x); });
-  static_for<0, 4>([&](auto x) { load_op(op[decltype(x)::value], k_chunk(1) + KOFF[decltype(x)::value]); });
+  load_op(op[0], k_chunk(0) + koff(0, 0)); load_op(op[1], k_chunk(0) + koff(1, 0));
+  load_op(op[2], k_chunk(0) + koff(0, 1)); load_op(op[3], k_chunk(0) + koff(1, 1));
+  mfma_qk(sA, op[0], c0{}, c0{}, c0{}); mfma_qk(sA, op[1], c1{}, c0{}, c0{});
+  mfma_qk(sA, op[0], c0{}, c0{}, c1{}); mfma_qk(sA, op[1], c1{}, c0{}, c1{});
+  mfma_qk(sA, op[2], c0{}, c1{}, c0{}); mfma_qk(sA, op[3], c1{}, c1{}, c0{});
+  mfma_qk(sA, op[2], c0{}, c1{}, c1{}); mfma_qk(sA, op[3], c1{}, c1{}, c1{});
+  load_op(op[0], k_chunk(1) + koff(0, 0)); load_op(op[2], k_chunk(1) + koff(0, 1));
+  foreign_next = mask_tile(sA, step_tile(0));
   {
-    mask_tile(sA, step_tile(0));
-    float mx = max_of(sA[0][0], sA[0], c0{}, c16{});
-    mx = max_of(mx, sA[1], c0{}, c16{});
-    raise_reference(mx);
+    raise_to(pair_max(fmaxf(max3(max_half(sA[0]), sA[0][15], sA[1][15]), max_half(sA[1]))) * c_row);             // O and the row sum are still zero
   }
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
   int j = 0;
-  for (; j + 2 <= last; j += 2) {
-    scores(std::true_type{}, j, sA, sB);
-    values(j, sB);
-    scores(std::true_type{}, j + 1, sB, sA);
-    values(j + 1, sA);
-  }
-  if (j < last) {
-    scores(std::true_type{}, j, sA, sB);
-    values(j, sB);
-    sA[0] = sB[0]; sA[1] = sB[1];
+  if (last >= 1) {
+    step(-1, sA, sB, pB, pA, no, yes);
+    for (; j + 3 <= last; j += 2) {
+      step(j, sB, sA, pA, pB, yes, yes);
+      step(j + 1, sA, sB, pB, pA, yes, yes);
+    }
+    if (j + 2 <= last) {
+      step(j, sB, sA, pA, pB, yes, yes);
+      sB[0] = sA[0]; sB[1] = sA[1];
+      pA = pB;
+      ++j;
+    }
+    step(j, sB, sA, pA, pB, yes, no);                      // j = last - 1
+    pA = pB;
     ++j;
+  } else {
+    step(-1, sA, sB, pB, pA, no, no);
   }
-  // the last tile: probabilities and O^T only
+  // the last tile's O^T: its probabilities in pA, two of its operands in op[1] and op[3]
+  load_op(op[0], v_chunk(j, foreign) + 2 * 128);
+  load_op(op[2], v_chunk(j, foreign) + 3 * 128);
+  const f32x4 row_sum = sum_product(pA);
+  o[0] = mfma_fp8(op[1], pA, o[0]);
+  o[1] = mfma_fp8(op[3], pA, o[1]);
+  o[2] = mfma_fp8(op[0], pA, o[2]);
+  o[3] = mfma_fp8(op[2], pA, o[3]);
+  add_row_sum(row_sum, pA);
   wait_loads<0>();
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  static_for<0, 4>([&](auto x) { load_op(op[decltype(x)::value], v_chunk(j) + decltype(x)::value * 128); });
-  scores(std::false_type{}, j, sA, sB);
-  static_for<0, 4>([&](auto x) {
-    constexpr int X = decltype(x)::value;
-    o[X] = mfma_fp8(op[X], pb, o[X]);
-  });
-  add_row_sum(mfma_fp8_16(ones, pb, zero4));
   __syncthreads();                                         // every wave is done with the rings
 
   // ---- epilogue: l_run holds the row sum of this lane's query.  The result is
@@ -606,7 +654,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     const float inv = v_scale[kvh] / l_tot;
     // (lane r < 32 holds the descriptor of row r); short rows come from the extra workgroups
     const unsigned stored_rows = (unsigned)__builtin_amdgcn_ballot_w64(
-        valid && a_end + i_loc - b_start + 1 > PV_SHORT_ROW_KEYS);
+        valid && a_end + mine.t0 + qrow - b_start + 1 > PV_SHORT_ROW_KEYS);
     auto stored = [&](int row) { return ((stored_rows >> row) & 1u) != 0; };
     const int64_t tok0 = (int64_t)mine.tok_base + mine.t0;
     char* tr = reinterpret_cast<char*>(&smem[0]) + (size_t)wave * (32 * RS);
