@@ -152,28 +152,37 @@ def pv_query_sizes(problem: HostProblem, n_q_heads: int, n_kv_heads: int, head_d
     return out
 
 
-def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+def _ptr(t: Optional[torch.Tensor], dev: int) -> Optional[int]:
+    """Address of `t`, which has to be contiguous memory of the current GPU, `dev`."""
     if t is None:
         return None
     # the library dereferences these on the GPU of the current stream: host memory or another
     # GPU's memory would fault there, so it is refused here
-    if not t.is_cuda or t.device.index != torch.cuda.current_device():
+    if not t.is_cuda or t.get_device() != dev:
         raise ValueError("tensor must live on the current GPU")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
     return t.data_ptr()
 
 
-def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+# A call of a few microseconds of GPU work is bound by what happens before its launches, so the device is looked up
+# once per call, and the stream without building a Stream object.
+def _device(t: Optional[torch.Tensor]) -> int:
+    """The current GPU (-1 if `t` is not on one: _ptr refuses it)."""
+    return torch.cuda.current_device() if t is None or t.is_cuda else -1
+
+
+def _stream(dev: int) -> int:
+    return torch._C._cuda_getCurrentRawStream(dev)
 
 
 def pv_build_mask(problem: HostProblem, sizes: PvSizes, plan: torch.Tensor,
                   dense_mask: Optional[torch.Tensor] = None) -> None:
     """Writes the plan (and optionally the uint8 dense mask) on the current stream."""
-    _check(lib.pv_build_mask(C.byref(problem.struct), C.byref(sizes), _ptr(plan),
-                             plan.numel() * plan.element_size(), _ptr(dense_mask),
-                             0 if dense_mask is None else dense_mask.numel(), _stream()),
+    dev = _device(plan)
+    _check(lib.pv_build_mask(C.byref(problem.struct), C.byref(sizes), _ptr(plan, dev),
+                             plan.numel() * plan.element_size(), _ptr(dense_mask, dev),
+                             0 if dense_mask is None else dense_mask.numel(), _stream(dev)),
            "pv_build_mask")
 
 
@@ -185,10 +194,9 @@ def pv_masked_attention(sizes: PvSizes, plan: torch.Tensor, q: torch.Tensor, k: 
     if q.dtype != want or k.dtype != want or v.dtype != want:
         raise ValueError("q/k/v dtype does not match sizes.in_dtype")
     n, hq, hkv, d = sizes.total_tokens, sizes.n_q_heads, sizes.n_kv_heads, sizes.head_dim
-    if tuple(q.shape) != (n, hq, d) or tuple(k.shape) != (n, hkv, d) or tuple(v.shape) != (n, hkv, d) \
-            or tuple(out.shape) != (n, hq, d):
+    if q.shape != (n, hq, d) or k.shape != (n, hkv, d) or v.shape != (n, hkv, d) or out.shape != (n, hq, d):
         raise ValueError("q/k/v/out shapes do not match sizes")
-    if lse is not None and (lse.dtype != torch.float32 or tuple(lse.shape) != (hq, n)):
+    if lse is not None and (lse.dtype != torch.float32 or lse.shape != (hq, n)):
         raise ValueError("lse must be float32 [Hq, total_tokens]")
     if out.dtype == torch.bfloat16:
         out_dtype = PV_BF16
@@ -197,9 +205,10 @@ def pv_masked_attention(sizes: PvSizes, plan: torch.Tensor, q: torch.Tensor, k: 
     else:
         raise ValueError("out must be bf16 or fp32")
     fn = lib.pv_segment_attention if segments_only else lib.pv_masked_attention
-    _check(fn(C.byref(sizes), _ptr(plan), _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), out_dtype,
-              softmax_scale, rope_theta, _ptr(workspace), workspace.numel() * workspace.element_size(),
-              _stream()),
+    dev = _device(plan)
+    _check(fn(C.byref(sizes), _ptr(plan, dev), _ptr(q, dev), _ptr(k, dev), _ptr(v, dev), _ptr(out, dev),
+              _ptr(lse, dev), out_dtype, softmax_scale, rope_theta, _ptr(workspace, dev), workspace.numel() * workspace.element_size(),
+              _stream(dev)),
            "pv_segment_attention" if segments_only else "pv_masked_attention")
 
 
@@ -209,21 +218,23 @@ def pv_masked_attention_fp8kv(sizes: PvSizes, plan: torch.Tensor, q: torch.Tenso
                               softmax_scale: float = 0.0, rope_theta: float = 0.0) -> None:
     """K/V as E4M3 codes (uint8 [tokens, Hkv, 128]) with per-head scales (float32 [Hkv]); Q bf16."""
     n, hq, hkv, d = sizes.total_tokens, sizes.n_q_heads, sizes.n_kv_heads, sizes.head_dim
-    if q.dtype != torch.bfloat16 or tuple(q.shape) != (n, hq, d) or tuple(out.shape) != (n, hq, d):
+    if q.dtype != torch.bfloat16 or q.shape != (n, hq, d) or out.shape != (n, hq, d):
         raise ValueError("q must be bfloat16 [total_tokens, Hq, D], out the same shape")
     for t in (k_fp8, v_fp8):
-        if t.dtype != torch.uint8 or tuple(t.shape) != (n, hkv, d):
+        if t.dtype != torch.uint8 or t.shape != (n, hkv, d):
             raise ValueError("k_fp8/v_fp8 must be uint8 [total_tokens, Hkv, D]")
     for t in (k_scale, v_scale):
-        if t.dtype != torch.float32 or tuple(t.shape) != (hkv,):
+        if t.dtype != torch.float32 or t.shape != (hkv,):
             raise ValueError("k_scale/v_scale must be float32 [Hkv]")
-    if lse is not None and (lse.dtype != torch.float32 or tuple(lse.shape) != (hq, n)):
+    if lse is not None and (lse.dtype != torch.float32 or lse.shape != (hq, n)):
         raise ValueError("lse must be float32 [Hq, total_tokens]")
     out_dtype = PV_F32 if out.dtype == torch.float32 else PV_BF16
-    _check(lib.pv_masked_attention_fp8kv(C.byref(sizes), _ptr(plan), _ptr(q), _ptr(k_fp8), _ptr(v_fp8),
-                                         _ptr(k_scale), _ptr(v_scale), _ptr(out), _ptr(lse), out_dtype,
-                                         softmax_scale, rope_theta, _ptr(workspace),
-                                         workspace.numel() * workspace.element_size(), _stream()),
+    dev = _device(plan)
+    _check(lib.pv_masked_attention_fp8kv(C.byref(sizes), _ptr(plan, dev), _ptr(q, dev), _ptr(k_fp8, dev),
+                                         _ptr(v_fp8, dev),
+                                         _ptr(k_scale, dev), _ptr(v_scale, dev), _ptr(out, dev), _ptr(lse, dev), out_dtype,
+                                         softmax_scale, rope_theta, _ptr(workspace, dev),
+                                         workspace.numel() * workspace.element_size(), _stream(dev)),
            "pv_masked_attention_fp8kv")
 
 
@@ -238,9 +249,10 @@ def pv_prepare_kv(sizes: PvSizes, plan: torch.Tensor, k: torch.Tensor, v: torch.
     if block_table is not None and block_table.dtype != torch.int32:
         raise ValueError("block_table must be int32")
     last = sizes.total_tokens if last_token is None else last_token
-    _check(lib.pv_prepare_kv(C.byref(sizes), _ptr(plan), _ptr(k), _ptr(v), _ptr(block_table), page_size,
-                             first_token, last, key_capacity, rope_theta, _ptr(workspace),
-                             workspace.numel() * workspace.element_size(), _stream()), "pv_prepare_kv")
+    dev = _device(plan)
+    _check(lib.pv_prepare_kv(C.byref(sizes), _ptr(plan, dev), _ptr(k, dev), _ptr(v, dev), _ptr(block_table, dev),
+                             page_size, first_token, last, key_capacity, rope_theta, _ptr(workspace, dev),
+                             workspace.numel() * workspace.element_size(), _stream(dev)), "pv_prepare_kv")
 
 
 def pv_segment_attention_prepared(sizes: PvSizes, plan: torch.Tensor, q: torch.Tensor, k: torch.Tensor,
@@ -250,11 +262,13 @@ def pv_segment_attention_prepared(sizes: PvSizes, plan: torch.Tensor, q: torch.T
                                   page_size: int = 0, key_capacity: int = 0) -> None:
     """Segment rows against the keys pv_prepare_kv left in `workspace`."""
     out_dtype = PV_F32 if out.dtype == torch.float32 else PV_BF16
-    _check(lib.pv_segment_attention_prepared(C.byref(sizes), _ptr(plan), _ptr(q), _ptr(k), _ptr(v),
-                                             _ptr(block_table), page_size, key_capacity, _ptr(out), _ptr(lse),
+    dev = _device(plan)
+    _check(lib.pv_segment_attention_prepared(C.byref(sizes), _ptr(plan, dev), _ptr(q, dev), _ptr(k, dev), _ptr(v, dev),
+                                             _ptr(block_table, dev), page_size, key_capacity, _ptr(out, dev),
+                                             _ptr(lse, dev),
                                              out_dtype,
-                                             softmax_scale, rope_theta, _ptr(workspace),
-                                             workspace.numel() * workspace.element_size(), _stream()),
+                                             softmax_scale, rope_theta, _ptr(workspace, dev),
+                                             workspace.numel() * workspace.element_size(), _stream(dev)),
            "pv_segment_attention_prepared")
 
 
@@ -279,8 +293,9 @@ def pv_masked_attention_static(sizes: PvSizes, plan: torch.Tensor, q: torch.Tens
                                softmax_scale: float = 0.0, rope_theta: float = 0.0) -> None:
     """pv_masked_attention with the library's own fixed workspace (no workspace argument)."""
     out_dtype = PV_F32 if out.dtype == torch.float32 else PV_BF16
-    _check(lib.pv_masked_attention_static(C.byref(sizes), _ptr(plan), _ptr(q), _ptr(k), _ptr(v), _ptr(out),
-                                          _ptr(lse), out_dtype, softmax_scale, rope_theta, _stream()),
+    dev = _device(plan)
+    _check(lib.pv_masked_attention_static(C.byref(sizes), _ptr(plan, dev), _ptr(q, dev), _ptr(k, dev), _ptr(v, dev),
+                                          _ptr(out, dev), _ptr(lse, dev), out_dtype, softmax_scale, rope_theta, _stream(dev)),
            "pv_masked_attention_static")
 
 
@@ -295,26 +310,28 @@ def pv_segment_attention(sizes: PvSizes, plan: torch.Tensor, q: torch.Tensor, k:
 
 def pv_first_reject(sizes: PvSizes, plan: torch.Tensor, logits: torch.Tensor, margin_threshold: float,
                     mode: int, out: torch.Tensor) -> None:
-    if logits.dtype != torch.float32 or tuple(logits.shape) != (sizes.total_segments, 2):
+    if logits.dtype != torch.float32 or logits.shape != (sizes.total_segments, 2):
         raise ValueError("logits must be float32 [total_segments, 2]")
-    if out.dtype != torch.int32 or tuple(out.shape) != (sizes.batch, 4):
+    if out.dtype != torch.int32 or out.shape != (sizes.batch, 4):
         raise ValueError("out must be int32 [batch, 4]")
-    _check(lib.pv_first_reject(C.byref(sizes), _ptr(plan), _ptr(logits) if logits.numel() else None,
-                               margin_threshold, mode, _ptr(out), _stream()), "pv_first_reject")
+    dev = _device(plan)
+    _check(lib.pv_first_reject(C.byref(sizes), _ptr(plan, dev), _ptr(logits, dev) if logits.numel() else None,
+                               margin_threshold, mode, _ptr(out, dev), _stream(dev)), "pv_first_reject")
 
 
 def pv_judge_logits(sizes: PvSizes, plan: torch.Tensor, hidden: torch.Tensor, w2: torch.Tensor,
                     logits: torch.Tensor) -> None:
     if hidden.dtype != torch.bfloat16 or hidden.dim() != 2 or hidden.shape[0] != sizes.total_tokens:
         raise ValueError("hidden must be bfloat16 [total_tokens, hidden_size]")
-    if w2.dtype != torch.bfloat16 or tuple(w2.shape) != (2, hidden.shape[1]):
+    if w2.dtype != torch.bfloat16 or w2.shape != (2, hidden.shape[1]):
         raise ValueError("w2 must be bfloat16 [2, hidden_size]")
-    if logits.dtype != torch.float32 or tuple(logits.shape) != (sizes.total_segments, 2):
+    if logits.dtype != torch.float32 or logits.shape != (sizes.total_segments, 2):
         raise ValueError("logits must be float32 [total_segments, 2]")
     if not (hidden.is_contiguous() and w2.is_contiguous() and logits.is_contiguous()):
         raise ValueError("tensors must be contiguous")
-    _check(lib.pv_judge_logits(C.byref(sizes), _ptr(plan), _ptr(hidden), _ptr(w2), hidden.shape[1],
-                               _ptr(logits) if logits.numel() else None, _stream()), "pv_judge_logits")
+    dev = _device(plan)
+    _check(lib.pv_judge_logits(C.byref(sizes), _ptr(plan, dev), _ptr(hidden, dev), _ptr(w2, dev), hidden.shape[1],
+                               _ptr(logits, dev) if logits.numel() else None, _stream(dev)), "pv_judge_logits")
 
 
 def make_policy(margin_chunk: float, margin_chunk_relaxed: float, margin_full: float,
@@ -334,15 +351,16 @@ def make_policy(margin_chunk: float, margin_chunk_relaxed: float, margin_full: f
 
 def pv_decide(sizes: PvSizes, plan: torch.Tensor, logits: torch.Tensor,
               full_logits: Optional[torch.Tensor], policy: PvPolicy, out: torch.Tensor) -> None:
-    if logits.dtype != torch.float32 or tuple(logits.shape) != (sizes.total_segments, 2):
+    if logits.dtype != torch.float32 or logits.shape != (sizes.total_segments, 2):
         raise ValueError("logits must be float32 [total_segments, 2]")
     if full_logits is not None and (full_logits.dtype != torch.float32 or
-                                    tuple(full_logits.shape) != (sizes.batch, 2)):
+                                    full_logits.shape != (sizes.batch, 2)):
         raise ValueError("full_logits must be float32 [batch, 2]")
-    if out.dtype != torch.int32 or tuple(out.shape) != (sizes.batch, 12):
+    if out.dtype != torch.int32 or out.shape != (sizes.batch, 12):
         raise ValueError("out must be int32 [batch, 12]")
-    _check(lib.pv_decide(C.byref(sizes), _ptr(plan), _ptr(logits) if logits.numel() else None,
-                         _ptr(full_logits), C.byref(policy), _ptr(out), _stream()), "pv_decide")
+    dev = _device(plan)
+    _check(lib.pv_decide(C.byref(sizes), _ptr(plan, dev), _ptr(logits, dev) if logits.numel() else None,
+                         _ptr(full_logits, dev), C.byref(policy), _ptr(out, dev), _stream(dev)), "pv_decide")
 
 
 def pv_plan_export(sizes: PvSizes, plan: torch.Tensor):
@@ -351,8 +369,10 @@ def pv_plan_export(sizes: PvSizes, plan: torch.Tensor):
     n, ns = sizes.total_tokens, sizes.total_segments
     pos, ae, bs = (torch.empty(n, dtype=torch.int32, device=dev) for _ in range(3))
     jr = torch.empty(max(ns, 1), dtype=torch.int32, device=dev)
-    _check(lib.pv_plan_export(C.byref(sizes), _ptr(plan), _ptr(pos), _ptr(ae), _ptr(bs), _ptr(jr),
-                              _stream()), "pv_plan_export")
+    dev = _device(plan)
+    _check(lib.pv_plan_export(C.byref(sizes), _ptr(plan, dev), _ptr(pos, dev), _ptr(ae, dev), _ptr(bs, dev),
+                              _ptr(jr, dev),
+                              _stream(dev)), "pv_plan_export")
     return pos, ae, bs, jr[:ns]
 
 

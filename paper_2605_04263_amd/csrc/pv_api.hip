@@ -251,6 +251,19 @@ static pv_status arch_ok_cached() {
   return st;
 }
 
+// theta^(-2c/d), c < d/2 (all zero for theta = 0).  The table of the last (theta, d) stays with the thread: its 64 powers
+// are a tenth of a small call's host time, and a model asks for the same ones in every layer.
+static const RopeFreq& rope_frequencies(float theta, int d) {
+  static thread_local struct { float theta = 0.0f; int d = 0; RopeFreq f = {}; } last;   // theta = 0: zeros for every d
+  if (last.theta != theta || (theta > 0.0f && last.d != d)) {
+    for (int c = 0; c < 64; ++c)
+      last.f.inv_freq[c] = (theta > 0.0f && c < d / 2) ? std::pow((double)theta, -2.0 * (double)c / (double)d) : 0.0;
+    last.theta = theta;
+    last.d = d;
+  }
+  return last.f;
+}
+
 }  // namespace pv
 
 using namespace pv;
@@ -400,11 +413,8 @@ static pv_status attention_call(const pv_sizes* sizes, const void* plan_dev, con
   if (st != PV_OK) return st;
 
   const float scale = softmax_scale == 0.0f ? (float)(1.0 / std::sqrt((double)d)) : softmax_scale;
-  RopeFreq freq;
   const bool rope = rope_theta > 0.0f;
-  for (int c = 0; c < 64; ++c)
-    freq.inv_freq[c] =
-        (rope && c < d / 2) ? std::pow((double)rope_theta, -2.0 * (double)c / (double)d) : 0.0;
+  const RopeFreq& freq = rope_frequencies(rope_theta, d);
 
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
@@ -546,10 +556,8 @@ pv_status pv_masked_attention_fp8kv(const pv_sizes* sizes, const void* plan_dev,
   st = arch_ok_cached();
   if (st != PV_OK) return st;
   const float scale = softmax_scale == 0.0f ? (float)(1.0 / std::sqrt((double)d)) : softmax_scale;
-  RopeFreq freq;
   const bool rope = rope_theta > 0.0f;
-  for (int c = 0; c < 64; ++c)
-    freq.inv_freq[c] = rope ? std::pow((double)rope_theta, -2.0 * (double)c / (double)d) : 0.0;
+  const RopeFreq& freq = rope_frequencies(rope_theta, d);
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   std::unique_lock<std::mutex> guard(g_profile_lock);
   const bool profiling = g_profile;
