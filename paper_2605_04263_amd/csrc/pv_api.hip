@@ -71,7 +71,7 @@ void plan_layout(int batch, int64_t total_tokens, int64_t total_segments, int64_
   h->off_tiles = take(n_q_tiles * 8);
   h->off_work = take(n_q_tiles * 8);
   h->off_map = layout == PV_LAYOUT_INTERLEAVED ? take(total_tokens) : 0;
-  h->off_segwork = take(n_seg_tiles * 8);
+  h->off_segwork = take(2 * n_seg_tiles * 8);
   h->off_quadwork = take(n_quads * 8);
   h->total_ints = (int32_t)o;
 }

@@ -38,7 +38,7 @@ struct PlanHeader {
   int32_t off_map;                                       // [total_tokens], interleaved layout only
   int32_t n_seg_tiles;                                   // query tiles with at least one segment row
   int32_t off_segtile_start;                             // [B+1] first such tile of a request, counted over the batch
-  int32_t off_segwork;                                   // [n_seg_tiles][8] those tiles, request after request
+  int32_t off_segwork;                                   // [n_seg_tiles][8] those tiles, longest first; as many again in front of the sort
   int32_t n_quads;                                       // groups of four consecutive query tiles of a request
   int32_t off_quad_start;                                // [B+1] first such group of a request
   int32_t off_quadwork;                                  // [n_quads][8], per request last group first

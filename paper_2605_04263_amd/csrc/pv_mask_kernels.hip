@@ -213,7 +213,7 @@ __device__ inline void plan_build(int32_t* plan, const int32_t* img, const PlanH
       int seg_slot;
       const QTile q = plan_tile(img, h, t, &seg_slot);
       reinterpret_cast<QTile*>(plan + h.off_tiles)[t] = q;
-      if (seg_slot >= 0) reinterpret_cast<QTile*>(plan + h.off_segwork)[seg_slot] = q;
+      if (seg_slot >= 0) reinterpret_cast<QTile*>(plan + h.off_segwork)[h.n_seg_tiles + seg_slot] = q;   // sorted below
     }
   } else if (blk < tile_blocks + quad_blocks) {
     const int qd = (blk - tile_blocks) * 64 + (tid >> 2);
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(256) void k_plan_build(int32_t* plan, PlanHeader h,
 constexpr int kSmallTokens = 8192, kSmallTiles = 1024;
 __global__ __launch_bounds__(1024) void k_plan_small(int32_t* plan, PlanHeader h, UploadChunk c,
                                                      int n_img) {
-  __shared__ int cost_s[kSmallTiles];
+  __shared__ int key_s[kSmallTiles];
   __shared__ int32_t img_s[kUploadInts];       // the request data is read from here, not from HBM
   const int tid = threadIdx.x;
   const bool first = blockIdx.x == 0;
@@ -265,14 +265,14 @@ __global__ __launch_bounds__(1024) void k_plan_small(int32_t* plan, PlanHeader h
   }
   if (!first) return;
   QTile mine;
-  int my_cost = 0;
+  int my_key = 0;              // 2 x cost, + 1 if the tile holds segment rows
   if (tid < h.n_q_tiles) {
     int seg_slot;
     mine = plan_tile(img_s, h, tid, &seg_slot);
-    my_cost = mine.n_a + (mine.jb1 - mine.jb0);
+    const int my_cost = mine.n_a + (mine.jb1 - mine.jb0);
     reinterpret_cast<QTile*>(plan + h.off_tiles)[tid] = mine;
-    if (seg_slot >= 0) reinterpret_cast<QTile*>(plan + h.off_segwork)[seg_slot] = mine;
-    cost_s[tid] = my_cost;
+    my_key = 2 * my_cost + (seg_slot >= 0 ? 1 : 0);
+    key_s[tid] = my_key;
   }
   // The groups of four tiles (four lanes each) go to the waves after those of the tiles.  There is room for both:
   // a request takes at least 16 ints of the image, so there are at most 56, with at most 8192 / 32 + 56 = 312
@@ -282,24 +282,31 @@ __global__ __launch_bounds__(1024) void k_plan_small(int32_t* plan, PlanHeader h
   if (x >= 0 && x < 4 * h.n_quads) plan_quad(plan, img_s, h, x >> 2, x & 3);
   __syncthreads();
   if (tid < h.n_q_tiles) {          // longest first, stable
-    int rank = 0;
+    int rank = 0, seg_rank = 0;     // among all tiles, among those that hold segment rows
     for (int x = 0; x < h.n_q_tiles; ++x) {
-      const int cx = cost_s[x];
-      rank += (cx > my_cost) || (cx == my_cost && x < tid);
+      const int kx = key_s[x];
+      const int before = (kx >> 1) > (my_key >> 1) || ((kx >> 1) == (my_key >> 1) && x < tid);
+      rank += before;
+      seg_rank += before & kx;
     }
     reinterpret_cast<QTile*>(plan + h.off_work)[rank] = mine;
+    if (my_key & 1) reinterpret_cast<QTile*>(plan + h.off_segwork)[seg_rank] = mine;
   }
 }
 
-// Longest-first order (stable): rank = number of tiles that must run before this one.  One wave per
-// four tiles; its lanes share the comparisons against all other tiles, whose costs they read eight at a
-// time: one read per round trip and one tile per wave left the launch waiting for L2.
+// Longest-first order (stable) of the query tiles and of those that hold segment rows: rank = number of tiles that
+// must run before this one.  One wave per four tiles; its lanes share the comparisons against all other tiles, whose
+// costs they read eight at a time: one read per round trip and one tile per wave left the launch waiting for L2.
+// (Segment rows of 16 ragged requests in the order of the requests: 2472 items of 7 to 78 key tiles on 512 slots
+// leave 21 % of the launch to its tail; sorted, 2 %.)
 constexpr int kSortTiles = 4, kSortReads = 8;
-__global__ __launch_bounds__(256) void k_plan_sort(int32_t* plan, PlanHeader h) {
-  const int n = h.n_q_tiles, lane = threadIdx.x & 63;
-  const int t0 = ((int)blockIdx.x * 4 + ((int)threadIdx.x >> 6)) * kSortTiles;
+__global__ __launch_bounds__(256) void k_plan_sort(int32_t* plan, PlanHeader h, int tile_blocks) {
+  const bool seg = (int)blockIdx.x >= tile_blocks;                 // the blocks behind those of all tiles
+  const int n = seg ? h.n_seg_tiles : h.n_q_tiles, lane = threadIdx.x & 63;
+  const int t0 = (((int)blockIdx.x - (seg ? tile_blocks : 0)) * 4 + ((int)threadIdx.x >> 6)) * kSortTiles;
   if (t0 >= n) return;                          // whole waves leave together
-  const QTile* tiles = reinterpret_cast<const QTile*>(plan + h.off_tiles);
+  QTile* dst = reinterpret_cast<QTile*>(plan + (seg ? h.off_segwork : h.off_work));
+  const QTile* tiles = seg ? dst + n : reinterpret_cast<const QTile*>(plan + h.off_tiles);
   auto cost = [&](int t) { return tiles[t].n_a + (tiles[t].jb1 - tiles[t].jb0); };
   int mine[kSortTiles], rank[kSortTiles];
 #pragma unroll
@@ -323,8 +330,7 @@ __global__ __launch_bounds__(256) void k_plan_sort(int32_t* plan, PlanHeader h) 
     for (int off = 32; off > 0; off >>= 1) rank[i] += __shfl_xor(rank[i], off);
     if (lane == i) my_rank = rank[i];
   }
-  if (lane < kSortTiles && t0 + lane < n)
-    reinterpret_cast<QTile*>(plan + h.off_work)[my_rank] = tiles[t0 + lane];
+  if (lane < kSortTiles && t0 + lane < n) dst[my_rank] = tiles[t0 + lane];
 }
 
 // Dense mask from the stored row descriptors (what the attention kernels consume).
@@ -373,7 +379,9 @@ hipError_t launch_plan_kernels(int32_t* plan_dev, const PlanHeader& h, const int
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_plan_sort<<<dim3((h.n_q_tiles + 4 * kSortTiles - 1) / (4 * kSortTiles)), dim3(256), 0, s>>>(plan_dev, h);
+    constexpr int kPerBlock = 4 * kSortTiles;
+    const int sort_blocks = (h.n_q_tiles + kPerBlock - 1) / kPerBlock, seg_blocks = (h.n_seg_tiles + kPerBlock - 1) / kPerBlock;
+    k_plan_sort<<<dim3(sort_blocks + seg_blocks), dim3(256), 0, s>>>(plan_dev, h, sort_blocks);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

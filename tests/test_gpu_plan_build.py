@@ -2,6 +2,7 @@
 arguments of the launch that uses them or not; tile counts around a workgroup (256), around what a ranking
 pass reads (512) and with a last wave of 1 to 4 tiles; and the single launch at its largest.  Each problem
 states the route that it is here for.  Everything is whole numbers, against the oracle's mask and arrays."""
+import numpy as np
 import pytest
 import torch
 
@@ -9,6 +10,7 @@ import pv_workloads as wl
 from tests.test_gpu_mask_readout import check_plan, check_quad_list, check_work_list
 
 pytestmark = pytest.mark.gpu
+pv = pytest.importorskip("paper_2605_04263_amd.binding")
 
 ARG_INTS, SMALL_TOKENS = 896, 8192       # ints of request data in kernel arguments; tokens of the single launch
 
@@ -49,3 +51,23 @@ def test_plan(name):
         assert ver.sizes.n_q_tiles == int(name.split("tiles_")[1].split("_")[0])
     check_work_list(pr)
     check_quad_list(pr)
+
+
+@pytest.mark.parametrize("name", list(PROBLEMS))
+def test_segment_list(name):
+    """The tiles that hold a segment row, longest first and otherwise in the order of the tile list."""
+    pr, _ = PROBLEMS[name]
+    ver = pv.Verifier(pr.prompt_len, pr.draft_len, pr.num_segments, pr.segment_len, pr.flat_boundaries(), 4, 2, 64,
+                      torch.bfloat16)
+    ver.plan.fill_(-1)
+    ver.build_mask()
+    blob = ver.plan.view(torch.int32).cpu().numpy()
+    n_tiles, off_tiles, n_seg, off_seg = (int(blob[i]) for i in (4, 24, 30, 32))
+    tiles = blob[off_tiles:off_tiles + 8 * n_tiles].reshape(n_tiles, 8)
+    causal = dict(zip(np.cumsum([0] + [pr.seq_len(b) for b in range(pr.batch)]).tolist(),
+                      [p + t for p, t in zip(pr.prompt_len, pr.draft_len)]))
+    holds = np.array([t0 + rows > causal[base] for base, t0, rows in tiles[:, :3].tolist()])
+    cost = tiles[:, 4] + tiles[:, 6] - tiles[:, 5]
+    want = tiles[holds][np.argsort(-cost[holds], kind="stable")]
+    assert n_seg == ver.sizes.n_seg_tiles == len(want)
+    assert np.array_equal(blob[off_seg:off_seg + 8 * n_seg].reshape(n_seg, 8), want)
