@@ -193,7 +193,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   // The probability of a score s is 2^(esc * s - mref): mref, in log2 units, is a per-row reference
   // that is only re-centred when a row sum leaves a safe window (see recentre below); l_run and o
   // are relative to it.  nmref = -mref is what the exponent adds.
-  float nmref = 0.0f, l_run = 0.0f;
+  float l_run = 0.0f;
   const float esc = FOLD ? 1.0f : qscale;   // FOLD: the scale is already in Q
   // FOLD: the exponent is score + nmref with nothing to multiply, and the matrix pipe does that
   // addition: every lane's 16 scores belong to one query row, so S^T accumulates on top of a tile
@@ -203,8 +203,18 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   f32x16 cref;
 #pragma unroll
   for (int r = 0; r < 16; ++r) cref[r] = 0.0f;
+  float nmref_own = 0.0f;                     // (FOLD: nmref is cref's first element, the register file is full)
+  auto nmref = [&]() __attribute__((always_inline)) { return FOLD ? cref[0] : nmref_own; };
+  auto set_nmref = [&](float x) __attribute__((always_inline)) {
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) cref[r] = x;
+    } else {
+      nmref_own = x;
+    }
+  };
   auto prob = [&](float x) {
-    return __builtin_amdgcn_exp2f(FOLD ? x : __builtin_fmaf(x, esc, nmref));
+    return __builtin_amdgcn_exp2f(FOLD ? x : __builtin_fmaf(x, esc, nmref()));
   };
   auto qk = [&](f32x16& acc) {
     if constexpr (FOLD) {
@@ -289,17 +299,17 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     const float l_tot = l_run;
     if (mx > -INFINITY && mx < INFINITY) {      // rows with no visible key keep their reference
       // FOLD: mx is biased, the row maximum itself is mx - nmref
-      float nm_new = FOLD ? nmref - mx : -mx * esc, alpha = 0.0f;   // empty history: nothing to rescale
+      float nm_new = FOLD ? nmref() - mx : -mx * esc, alpha = 0.0f;   // empty history: nothing to rescale
       if (l_tot > 0.0f) {
-        nm_new = fminf(nm_new, nmref - (__builtin_amdgcn_logf(l_tot) - 20.0f));
-        alpha = __builtin_amdgcn_exp2f(nm_new - nmref);
+        nm_new = fminf(nm_new, nmref() - (__builtin_amdgcn_logf(l_tot) - 20.0f));
+        alpha = __builtin_amdgcn_exp2f(nm_new - nmref());
       }
       if constexpr (FOLD) {
-        const float delta = nm_new - nmref;
+        const float delta = nm_new - nmref();
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { sc[r] += delta; other[r] += delta; cref[r] = nm_new; }
+        for (int r = 0; r < 16; ++r) { sc[r] += delta; other[r] += delta; }
       }
-      nmref = nm_new;
+      set_nmref(nm_new);
       l_run *= alpha;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -329,18 +339,34 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     const int rows_m1 = tile.rows - 1;
     const int64_t tok0 = (int64_t)tile.tok_base + tile.t0;
     const unsigned q_area = smem_base + QAREA0 * 16, cs_area = q_area + QCH * 16;
+    constexpr int QN = QCH / 64 / G;                  // 32*CPR/64 instructions per wave
+    static_assert(!QT || QN % 4 == 0, "(QT) the instructions n of every wave cover tile n / (QN / 4)");
+    // global chunk (row of the area, 16-byte piece) that lands at LDS chunk (wave_s + n G) 64 + lane; rows [32 hl,
+    // 32 hl + 32) of the area are head hl of the group, or (QT) tile hl of this head
+    auto q_chunk = [&](int n) {
+      const int P = (wave_s + n * G) * 64 + lane, R = P >> 4;
+      return (R << 4) + ((P & 15) ^ (R & 15));
+    };
+    // the caller's rows, all of them before the first load into LDS: the compiler lets an exchange between lanes wait
+    // for every such load in flight
+    int q_row[QN];
+    {
+      CallerRows rows(plan, h, tok0, rows_m1);
 #pragma unroll
-    for (int n = 0; n < QCH / 64 / G; ++n) {          // 32*CPR/64 instructions per wave
+      for (int n = 0; n < QN; ++n) {
+        if (QT && n > 0 && n % (QN / 4) == 0) {
+          const int first = min(32 * (n / (QN / 4)), rows_m1);
+          rows = CallerRows(plan, h, tok0 + first, rows_m1 - first);
+        }
+        q_row[n] = (int)rows.of((q_chunk(n) / CPR) & 31);
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < QN; ++n) {
       const int c = wave_s + n * G;
-      const int P = c * 64 + lane;
-      const int R = P >> 4, pos = P & 15;
-      const int Pg = (R << 4) + (pos ^ (R & 15));     // global chunk that lands at LDS chunk P
-      const int row = Pg / CPR, ch = Pg % CPR;
-      // rows [32 hl, 32 hl + 32) of the area: head hl of the group, or (QT) tile hl of this head
-      const int hl = row >> 5;
-      const int tok = QT ? min(32 * hl + (row & 31), rows_m1) : min(row & 31, rows_m1);
-      const int src_head = QT ? head : kvh * G + hl;
-      const uint16_t* src = q + (caller_row(plan, h, tok0 + tok) * hq + src_head) * D + (ch << 3);
+      const int row = q_chunk(n) / CPR, ch = q_chunk(n) % CPR;
+      const int src_head = QT ? head : kvh * G + (row >> 5);
+      const uint16_t* src = q + ((int64_t)q_row[n] * hq + src_head) * D + (ch << 3);
       __builtin_amdgcn_global_load_lds(
           (const __attribute__((address_space(1))) void*)src,
           (__attribute__((address_space(3))) void*)(uintptr_t)(q_area + c * 1024), 16, 0, 0);
@@ -457,10 +483,10 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sA[r]);
     mx = pair_max(mx);
-    if (mx > -INFINITY && mx < INFINITY) nmref = -mx * esc;
+    set_nmref(mx > -INFINITY && mx < INFINITY ? -mx * esc : 0.0f);
     if constexpr (FOLD) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { sA[r] += nmref; cref[r] = nmref; }
+      for (int r = 0; r < 16; ++r) sA[r] += nmref();
     }
   }
   l_run = probs(sA, pA);
@@ -545,7 +571,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     float ea[16], ex[16];                              // exponent arguments, exponentials
     auto v_arg = [&](auto i) {
       constexpr int I = decltype(i)::value;
-      if constexpr (I < 16) ea[I] = FOLD ? s_in[I] : __builtin_fmaf(s_in[I], esc, nmref);
+      if constexpr (I < 16) ea[I] = FOLD ? s_in[I] : __builtin_fmaf(s_in[I], esc, nmref());
     };
     auto v_exp = [&](auto i) {
       constexpr int I = decltype(i)::value;
@@ -767,14 +793,16 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     const unsigned stored_rows = (unsigned)__builtin_amdgcn_ballot_w64(
         valid && a_end + own_row() - b_start + 1 > PV_SHORT_ROW_KEYS && (split == 0 || b_start > 0));
     auto stored = [&](int row) { return partial || ((stored_rows >> row) & 1u) != 0; };
+    // (a wave without a row looks up the workgroup's first one)
+    const CallerRows rows(plan, h, mine.rows > 0 ? tok0 : (int64_t)tile.tok_base + tile.t0, max(mine.rows - 1, 0));
     constexpr int RS = 2 * D + 16;                    // row stride: 16 B of padding spreads the banks
     char* tr = reinterpret_cast<char*>(&smem[0]) + (size_t)wave * (32 * RS);
     // where row `row` of this wave's result goes, as fp32: the caller's tensor, or the partial tile
     auto f32_row = [&](int row) {
       return partial ? part_o + row * D
-                     : reinterpret_cast<float*>(out) + (caller_row(plan, h, tok0 + row) * hq + head) * D;
+                     : reinterpret_cast<float*>(out) + (rows.of(row) * hq + head) * D;
     };
-    if (partial && hh == 0) reinterpret_cast<float2*>(part_o + 32 * D)[qrow] = make_float2(nmref, l_tot);
+    if (partial && hh == 0) reinterpret_cast<float2*>(part_o + 32 * D)[qrow] = make_float2(nmref(), l_tot);
     if (out_f32 || partial) {
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
@@ -792,7 +820,8 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
         for (int it = 0; it < 32 * LPR / 64; ++it) {
           const int row = it * (64 / LPR) + lane / LPR, c = lane % LPR;
           const float4 w = *reinterpret_cast<const float4*>(tr + row * RS + c * 16);
-          if (stored(row)) *reinterpret_cast<float4*>(f32_row(row) + half * (D / 2) + c * 4) = w;
+          float* to = f32_row(row);
+          if (stored(row)) *reinterpret_cast<float4*>(to + half * (D / 2) + c * 4) = w;
         }
       }
     } else {
@@ -811,13 +840,14 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       for (int it = 0; it < 32 * LPR / 64; ++it) {
         const int row = it * (64 / LPR) + lane / LPR, c = lane % LPR;
         const uint4 w = *reinterpret_cast<const uint4*>(tr + row * RS + c * 16);
+        const int64_t to = rows.of(row);
         if (stored(row))
-          *reinterpret_cast<uint4*>(op + (caller_row(plan, h, tok0 + row) * hq + head) * D + c * 8) = w;
+          *reinterpret_cast<uint4*>(op + (to * hq + head) * D + c * 8) = w;
       }
     }
     if (lse && !partial && hh == 0 && stored(qrow))
-      lse[(int64_t)head * h.total_tokens + caller_row(plan, h, g)] =
-          (log2f(l_tot) - nmref) * 0.6931471805599453f;
+      lse[(int64_t)head * h.total_tokens + rows.mine] =
+          (log2f(l_tot) - nmref()) * 0.6931471805599453f;
   }
 }
 
