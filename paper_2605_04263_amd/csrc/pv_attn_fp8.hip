@@ -212,7 +212,7 @@ __device__ __forceinline__ void wait_loads() {            // at most N loads of 
 // O^T, the two waves of a SIMD met the barrier in the same phase where they belong to one workgroup.  Passes, us,
 // before / with it: 4 x (2048 + 8192) tokens, 64/8 heads 7057 / 6731; 4000 + 512, 28/4 heads 160.2 / 153.8;
 // 1024 + 4096, 64/8 heads, no rotation 439 / 419; four waves to a workgroup: 512 + 2048, 32/8 heads 78.8 / 79.5, 8
-// ragged requests 575.6 / 574.5, three requests at 40/8 heads 327.4 / 324.8.  Matrix pipe 52 / 56 % busy, 14.6 / 13.7 M
+// ragged requests 575.6 / 574.5, three requests at 40/8 heads 327.4 / 324.8.  Matrix pipe 52 / 59 % busy, 14.6 / 13.1 M
 // cycles for the first of them.
 // QT as in the bf16 kernel: the four waves are four consecutive query tiles of one query head; `tile` is
 // the union of the four (it drives the key loop and the staging), `mine` the wave's own.
@@ -481,7 +481,6 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   };
   using c0 = std::integral_constant<int, 0>;
   using c1 = std::integral_constant<int, 1>;
-  using c16 = std::integral_constant<int, 16>;
   // The sum over a tile's probabilities.  A query's NaN (a NaN in its Q row, or in a key that its neighbour
   // does not see) meets the zeros of the query that shares its column: such a tile is summed from the codes.
   auto sum_codes = [&](const i32x8& p) __attribute__((always_inline)) {

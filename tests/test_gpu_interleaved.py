@@ -66,6 +66,16 @@ def test_attention_bf16(idx):
     check_full(w)
 
 
+# Every arrangement of the main kernel (one wave per head; four query tiles of a head, the last group of a request with
+# one or two tiles, the last tile with one row): each lane looks up one row of a tile and hands it to the others.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("group", range(1, 9))
+def test_rows_of_every_group_size(group, d):
+    pr = inter(wl.Problem([7, 20, 0], [90, 101, 250], [2, 0, 3], [16, 1, 13], [[33, 90], [], [17, 100, 250]]))
+    w = wl.make_custom(pr, group, 1, d, dtype=torch.bfloat16, rope_theta=0.0 if group % 2 else 5e5, seed=90 + group)
+    check_full(w)
+
+
 def interleaved_8b():
     w = wl.make("8b")
     return wl.Workload(**{**w.__dict__, "problem": inter(w.problem)})
