@@ -60,8 +60,11 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   //             piece c of `split` covers the c-th share of the tile's listed key tiles.
   const int piece = split ? (int)blockIdx.x % split : 0;
   const int item = split ? (int)blockIdx.x / split : (int)blockIdx.x;   // (tile, kv head)
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);      // wave index as a scalar
+  const int tid = threadIdx.x, lane = tid & 63;
+  // The wave index as a scalar, for everything that lives through the loops: in a vector register the head and the
+  // address of the partial result took three of them, and with eight and with three waves the mask's row descriptors
+  // went to scratch memory, to be read back in every masked step behind all staging loads in flight.
+  const int wave_s = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qrow = lane & 31, hh = lane >> 5;
   int kvh, head;
   QTile tile, mine;
@@ -78,7 +81,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       mine = reinterpret_cast<const QTile*>(plan + h.off_tiles)[tile.n_full + wave_s];
   } else {
     kvh = item % hkv;
-    head = kvh * G + wave;
+    head = kvh * G + wave_s;
     tile = reinterpret_cast<const QTile*>(
         plan + (split ? h.off_segwork : h.off_work))[dispatch_rank(item / hkv, h.n_q_tiles, order)];
     mine = tile;
@@ -98,7 +101,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   const int n_steps = 2 * n_tiles;
   const int last = n_steps - 1;
   // partial result of this wave (split > 1): float [32][D], then float2 [32] = (nmref, row sum)
-  float* part_o = part + ((int64_t)((int64_t)item * split + piece) * G + wave) * (32 * (D + 2));
+  float* part_o = part + ((int64_t)((int64_t)item * split + piece) * G + wave_s) * (32 * (D + 2));
   if (n_steps == 0) {                       // fewer key tiles than pieces: this piece is empty
     if (hh == 0) reinterpret_cast<float2*>(part_o + 32 * D)[qrow] = make_float2(0.0f, 0.0f);
     return;
@@ -406,7 +409,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     float x[KT][8];
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
-      const uint4 raw = q_lds[swz((wave * 32 + qrow) * CPR + 2 * t + hh)];
+      const uint4 raw = q_lds[swz((wave_s * 32 + qrow) * CPR + 2 * t + hh)];
       const unsigned* pr = reinterpret_cast<const unsigned*>(&raw);
 #pragma unroll
       for (int e = 0; e < 4; ++e) { x[t][2 * e] = bf16_lo(pr[e]); x[t][2 * e + 1] = bf16_hi(pr[e]); }
@@ -796,7 +799,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     // (a wave without a row looks up the workgroup's first one)
     const CallerRows rows(plan, h, mine.rows > 0 ? tok0 : (int64_t)tile.tok_base + tile.t0, max(mine.rows - 1, 0));
     constexpr int RS = 2 * D + 16;                    // row stride: 16 B of padding spreads the banks
-    char* tr = reinterpret_cast<char*>(&smem[0]) + (size_t)wave * (32 * RS);
+    char* tr = reinterpret_cast<char*>(&smem[0]) + (size_t)wave_s * (32 * RS);
     // where row `row` of this wave's result goes, as fp32: the caller's tensor, or the partial tile
     auto f32_row = [&](int row) {
       return partial ? part_o + row * D
