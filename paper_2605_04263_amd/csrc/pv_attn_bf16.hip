@@ -203,7 +203,7 @@ __global__ __launch_bounds__(256) void k_merge_pieces(const int32_t* __restrict_
       const float* p = part + ((int64_t)((int64_t)item * split + c) * G + hl) * (32 * (D + 2));
       const float2 ml = reinterpret_cast<const float2*>(p + 32 * D)[row];
       mref[c] = -ml.x; lsum[c] = ml.y;
-      if (ml.y > 0.0f) M = fmaxf(M, mref[c]);
+      if (ml.y != 0.0f) M = fmaxf(M, mref[c]);
     }
   }
   float acc[FPT];
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256) void k_merge_pieces(const int32_t* __restrict_
   float L = 0.0f;
 #pragma unroll
   for (int c = 0; c < MAXSPLIT; ++c) {
-    if (c < split && lsum[c] > 0.0f) {               // a piece without a visible key holds nothing
+    if (c < split && lsum[c] != 0.0f) {              // a piece without a visible key holds nothing; a NaN is kept
       const float w = exp2f(mref[c] - M);
       L = fmaf(w, lsum[c], L);
       const float* p = part + ((int64_t)((int64_t)item * split + c) * G + hl) * (32 * (D + 2)) +

@@ -85,3 +85,49 @@ def test_fp8(group, name, where):
             rel = 0.0 if where == "v" else 2.4e-4
             assert (np.abs(got[keep] - clean[keep]) <= rel * np.abs(clean[keep])).all(), (b, key)
             assert (np.abs(got_lse[:, keep] - clean_lse[:, keep]) <= rel).all(), (b, key)
+
+
+# The bf16 kernels sum two queries of a tile in one column of a matrix product, so a NaN key that one of them sees
+# reaches the other's sum and has to be taken out again; a row that does see it is NaN, in the whole pass and where the
+# pieces of a segment row are merged.  |V| = 1: a row that is re-centred for its neighbour's sake rounds its
+# probabilities to bf16 anew, 2^-8 of each at most, in either run.
+@pytest.mark.parametrize("segments_only", [False, True])
+@pytest.mark.parametrize("theta", [0.0, 5e5])
+@pytest.mark.parametrize("group,d", [(1, 128), (4, 128), (5, 128), (8, 128), (4, 64), (5, 64)])
+def test_bf16_keys(group, d, theta, segments_only):
+    pr, hkv = PROBLEMS["three"], 2
+    w = wl.make_custom(pr, group * hkv, hkv, d, dtype=torch.bfloat16, rope_theta=theta, seed=85)
+    ver = gc.make_verifier(pv, w)
+    ver.build_mask()
+    dev = ver.device
+    q, v = w.q.to(dev), torch.sign(w.v.float()).to(torch.bfloat16).to(dev)
+
+    def run(k):
+        out = torch.zeros(w.q.shape, dtype=torch.float32, device=dev)
+        lse = torch.zeros(w.q.shape[1], pr.total_tokens, dtype=torch.float32, device=dev)
+        (ver.segment_attention if segments_only else ver.attention)(q, k.to(dev), v, out=out, lse=lse, rope_theta=theta)
+        torch.cuda.synchronize()
+        return out.cpu().numpy(), lse.cpu().numpy()
+
+    clean, clean_lse = run(w.k)
+    assert np.isfinite(clean).all()
+    vis = masks(pr)
+    starts = np.cumsum([0] + [m.shape[0] for m in vis])
+    delta = 2.0 ** -8
+    for b, m in enumerate(vis):
+        n, causal = m.shape[0], pr.prompt_len[b] + pr.draft_len[b]
+        evaluated = np.zeros(pr.total_tokens, bool)
+        for c in range(pr.batch):
+            evaluated[starts[c] + (pr.prompt_len[c] + pr.draft_len[c] if segments_only else 0):starts[c + 1]] = True
+        for key in sorted({20, 70, n // 2 + 5, causal - 1, causal, n - 3} & set(range(n))):
+            bad = w.k.clone()
+            bad[starts[b] + key, :, 33] = float("nan")
+            got, got_lse = run(bad)
+            hit = np.zeros(pr.total_tokens, bool)
+            hit[starts[b]:starts[b + 1]] = m[:, key]
+            hit &= evaluated
+            keep = evaluated & ~hit
+            assert np.isnan(got[hit]).all() and np.isnan(got_lse[:, hit]).all(), (b, key)
+            assert np.isfinite(got[keep]).all() and np.isfinite(got_lse[:, keep]).all(), (b, key)
+            assert np.abs(got[keep] - clean[keep]).max(initial=0) <= 2 * 2 * delta / (1 - delta) + 1e-5, (b, key)
+            assert np.abs(got_lse[:, keep] - clean_lse[:, keep]).max(initial=0) <= -2 * np.log(1 - delta) + 1e-5, (b, key)
