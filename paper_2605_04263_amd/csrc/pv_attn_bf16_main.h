@@ -250,17 +250,22 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   };
   // p rounded to bf16 once; the row sum is taken over the rounded values, so that O is an exact convex
   // combination of V rows with the weights the MFMA sees.
-  // The sum of a step runs on the matrix pipe as two 16 x 16 x 32 products of P^T with `ones`.  Its columns are
-  // l % 16 and its depth blocks l / 16, so the lanes of queries c and c + 16 share a column and fill different
-  // blocks: a row of `ones` that is one in the blocks 0 and 2 sums query c, one in 1 and 3 query c + 16, and row r
-  // takes the parity (r / 4) % 2, which leaves every lane its own query's sum, both half-waves, in all four
+  // kSumByProducts: the sum of a step runs on the matrix pipe as two 16 x 16 x 32 products of P^T with `ones`.  Its
+  // columns are l % 16 and its depth blocks l / 16, so the lanes of queries c and c + 16 share a column and fill
+  // different blocks: a row of `ones` that is one in the blocks 0 and 2 sums query c, one in 1 and 3 query c + 16, and
+  // row r takes the parity (r / 4) % 2, which leaves every lane its own query's sum, both half-waves, in all four
   // accumulators.  32 matrix cycles beside the 512 of a step's products (256 at D = 64), and no VALU; unpacked and
-  // added it was 32 VALU instructions of a step's 56, and every VALU instruction delays the next MFMA.  Passes, us,
-  // before / with these products: 512 + 2048 tokens at 32/8 heads of 128, no segment 73.7 / 70.6; 16 requests of 0.6
-  // to 5 K 1372 / 1334; 5 K at 40/8 heads, no rotation 402 / 376; 32/8 heads of 64, two requests 57.8 / 56.2 (there
-  // two chains of dots before); at the power limit, 4 x 10 K at 64/8 heads, 8287 / 8259.
+  // added it is 32 VALU instructions of a step's 56, and every VALU instruction delays the next MFMA.
+  // Otherwise: unpacked and added.  l_run is then the half-wave's own part of the row's sum.
+  // Both ways, with all else the same, passes, us, products / added: 32/8 heads, no segment 512 + 2048 tokens 71.5 /
+  // 73.1, 16 requests of 0.6 to 5 K 1355 / 1386, 4 x 10 K tokens 4145 / 4261; 40/8 heads, 4 x 10 K 5374 / 5551, 5 K
+  // without rotation 378 / 390; 28/4 heads, 4 x 10 K 3944 / 4162.  Eight waves to a workgroup and rotation are the
+  // exception, there the power limit of the card decides and the products cost more of it than the additions: 64/8 heads,
+  // 4 x 10 K 8319 / 8251 on one card, 8461 / 8264 on another, 2 x 3.8 K at 32/4 heads 301.9 / 298.6, segment rows of 8
+  // requests 359 / 350; without rotation, where every score takes a multiply-add as well, 2 x 3.8 K 577 / 584.
+  constexpr bool kSumByProducts = !(FOLD && D == 128 && G == 8);
   bf16x8 ones;
-  {
+  if constexpr (kSumByProducts) {
     unsigned x = (lane >> 4 & 1) == (lane >> 2 & 1) ? 0x3f803f80u : 0u;
     unsigned w[4];
 #pragma unroll
@@ -275,7 +280,13 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       rs += bf16_lo(pw[e]);
       rs_hi += bf16_hi(pw[e]);
     }
-    return pair_sum(rs + rs_hi);
+    return kSumByProducts ? pair_sum(rs + rs_hi) : rs + rs_hi;
+  };
+  // (Sums added half-wave by half-wave: each half gets half of the row's sum.  The window test below looks at the halves
+  // one by one, and a half whose keys all lie far below the other's would fail it in every step: with outlier channels in
+  // K, 5 K tokens at 64/8 heads, 734 us instead of 552.)
+  auto even_out = [&]() __attribute__((always_inline)) {
+    if constexpr (!kSumByProducts) l_run = 0.5f * pair_sum(l_run);
   };
   // The window test of a step: its row sum `rs` must not exceed 2^16, and the running sum
   // with it must have reached 2^-40.  (2^40 would be safe too: 370 us instead of 376 where outlier channels of K make
@@ -299,7 +310,8 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
     mx = pair_max(mx);
-    const float l_tot = l_run;
+    even_out();
+    const float l_tot = kSumByProducts ? l_run : 2.0f * l_run;
     if (mx > -INFINITY && mx < INFINITY) {      // rows with no visible key keep their reference
       // FOLD: mx is biased, the row maximum itself is mx - nmref
       float nm_new = FOLD ? nmref() - mx : -mx * esc, alpha = 0.0f;   // empty history: nothing to rescale
@@ -493,6 +505,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     }
   }
   l_run = probs(sA, pA);
+  even_out();
   wait_kv();
   qk(sB);                                            // S(1)
   __builtin_amdgcn_sched_barrier(0);
@@ -559,7 +572,8 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     const int slot_ks = ST ? (PH + 2) % NS : sj + 2 >= NS ? sj + 2 - NS : sj + 2;   // (j + 2) % NS
     const bf16x8 pfa = as_bf16x8(make_uint4(p_in[0], p_in[1], p_in[2], p_in[3]));
     const bf16x8 pfb = as_bf16x8(make_uint4(p_in[4], p_in[5], p_in[6], p_in[7]));
-    f32x4 rsum = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 rsum = {0.0f, 0.0f, 0.0f, 0.0f};           // (kSumByProducts)
+    float rs_lo = 0.0f, rs_hi = 0.0f;                 // (otherwise) over the low and the high halves of the pairs
     constexpr unsigned SBV = ST ? ((PH + 1) % NS) * SLOT_BYTES : 0, SBK = ST ? ((PH + 3) % NS) * SLOT_BYTES : 0;
     const unsigned sbv = ST ? 0u : (unsigned)slot_v * SLOT_BYTES, sbk = ST ? 0u : (unsigned)slot_k * SLOT_BYTES;
     // The step is 2 KT groups of one MFMA, at most one operand refill and a share of the VALU
@@ -567,9 +581,12 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     // the MFMAs, and the VALU work then runs while the matrix pipe idles.)  The wave issues in
     // order, so a VALU instruction waiting for its input also holds back the next MFMA: the
     // softmax work of a score is therefore spread over consecutive groups,
-    //   exponent argument -> exp2 -> (pair) bf16 pack -> (pair) row sum,
-    // each stage one group after the stage it depends on.
+    //   exponent argument -> exp2 -> (pair) bf16 pack (-> sums of the low, then of the high halves, unless products
+    //   form them), each stage one group after the stage it depends on.
     constexpr int NG = 2 * KT, SPG = 16 / NG;          // groups; scores entering per group
+    constexpr int GHI = SPG == 1 ? 2 : 1;              // groups from the pack to the sum of the high halves
+    constexpr int AHEAD = kSumByProducts ? 2 : 1;      // groups that exp2 runs ahead (2: the last pair is packed one
+                                                       // group before the end, in front of the second product)
     constexpr int HB = KT / 4;                         // k-steps issued before the barrier
     float ea[16], ex[16];                              // exponent arguments, exponentials
     auto v_arg = [&](auto i) {
@@ -585,14 +602,15 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     };
     auto valu_group = [&](auto g) {                    // the VALU share of group g (g = -1: before)
       constexpr int GI = decltype(g)::value;
-      // exp2 runs two groups ahead, so that the last pair is packed one group before the end
-      constexpr int I0 = GI < 0 ? 0 : (GI + 2) * SPG, IN = GI < 0 ? 2 * SPG : SPG;
+      constexpr int I0 = GI < 0 ? 0 : (GI + AHEAD) * SPG, IN = GI < 0 ? AHEAD * SPG : SPG;
       static_for<0, IN>([&](auto k) { v_exp(std::integral_constant<int, I0 + decltype(k)::value>{}); });
       static_for<0, SPG>([&](auto k) { v_arg(std::integral_constant<int, I0 + IN + decltype(k)::value>{}); });
       static_for<0, 8>([&](auto e) {
         constexpr int E = decltype(e)::value;
-        constexpr int GC = (2 * E + 1) / SPG > 1 ? (2 * E + 1) / SPG - 1 : 0;   // group after the pair's second exp2
+        constexpr int GX = (2 * E + 1) / SPG - (AHEAD - 1), GC = GX > 0 ? GX : 0;   // the group after the pair's second exp2
         if constexpr (GC == GI) p_out[E] = pack_bf16(ex[2 * E], ex[2 * E + 1]);
+        if constexpr (!kSumByProducts && GC + 1 == GI) rs_lo += bf16_lo(p_out[E]);
+        if constexpr (!kSumByProducts && GC + GHI == GI) rs_hi += bf16_hi(p_out[E]);
       });
     };
     auto mfma_sum = [&](auto half) {                   // row sum of the step's first or second 16 keys
@@ -673,7 +691,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       lds_refill_b128<T * 1024 + SBK>(kf[t], k_off + sbk);
     };
 
-    static_for<0, 2 * SPG>([&](auto k) { v_arg(k); });
+    static_for<0, AHEAD * SPG>([&](auto k) { v_arg(k); });
     valu_group(std::integral_constant<int, -1>{});
     __builtin_amdgcn_sched_barrier(0);
     // Head: the first MFMAs need nothing from LDS, so they are issued before the barrier and run
@@ -726,8 +744,8 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       if constexpr (STEADY) stage_part2(std::integral_constant<int, 2 * R>{});
       __builtin_amdgcn_sched_barrier(0);
       // the first half's packs are done after group NG / 2 - 2, the second's after NG - 2
-      if constexpr (2 * T + 1 == NG / 2 + 1) mfma_sum(std::integral_constant<int, 0>{});
-      if constexpr (2 * T + 1 == NG - 1) mfma_sum(std::integral_constant<int, 1>{});
+      if constexpr (kSumByProducts && 2 * T + 1 == NG / 2 + 1) mfma_sum(std::integral_constant<int, 0>{});
+      if constexpr (kSumByProducts && 2 * T + 1 == NG - 1) mfma_sum(std::integral_constant<int, 1>{});
       __builtin_amdgcn_sched_barrier(0);
       mfma_qk(t);
       __builtin_amdgcn_sched_barrier(0);
@@ -736,7 +754,8 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
       if constexpr (STEADY) stage_part2(std::integral_constant<int, 2 * R + 1>{});
       __builtin_amdgcn_sched_barrier(0);
     });
-    float rs = rsum[0];
+    if constexpr (!kSumByProducts) static_for<NG, NG + GHI>([&](auto g) { valu_group(g); });   // the last terms
+    float rs = kSumByProducts ? rsum[0] : rs_lo + rs_hi;
     asm volatile("" : "+v"(rs));                      // the row sum belongs to this block
     __builtin_amdgcn_sched_barrier(0);
     if (have1) {
@@ -784,7 +803,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
 
   // ---- epilogue: normalise, then transpose through LDS so that every output row leaves as one
   // contiguous run (2 D bytes in bf16; fp32 goes in two halves of D/2 features to bound the area)
-  const float l_tot = l_run;
+  const float l_tot = kSumByProducts ? l_run : pair_sum(l_run);
   __syncthreads();                                    // every wave is done with the stages
   {
     const bool partial = split > 1;                   // this piece's result goes to the workspace

@@ -238,33 +238,69 @@ def test_softmax_scale(d, group, scale, theta):
     check_full(w, softmax_scale=scale, max_abs=MAX_ABS * grow, mean_abs=MEAN_ABS * grow, lse_abs=LSE_ABS * grow)
 
 
-# Scores that rise by `octaves` at chosen keys, for every second query only: at the sizes around which the row sum
-# leaves the kernel's window (2^16) or does not, and far beyond fp32's range.  The queries c and c + 16 of a tile,
-# whose sums come out of one column of the matrix product, go opposite ways.  With |V| <= 1 the rounding of the
-# probabilities to bf16 (8 significant bits: 2^-8 of the value at most) moves an output by at most
-# 2 * 2^-8 / (1 - 2^-8) and the normaliser by -log(1 - 2^-8); Q and K enter the products exactly (no rotation).
-@pytest.mark.parametrize("octaves", [15, 16, 17, 39, 41, 130])
-@pytest.mark.parametrize("hq,hkv,d", [(4, 1, 128), (5, 1, 128), (8, 1, 64)])
-def test_rising_scores(hq, hkv, d, octaves):
+# Scores that rise by `octaves` at chosen keys, for every second query only, and fall as far for the others: 15 to 17,
+# around which the row sum leaves the kernel's window (2^16) or does not; 39 and 41, far beyond it, where the history is
+# scaled to above and to below the sum's lower bound (2^-40); 130, where nothing is left of it in fp32.  The queries c
+# and c + 16 of a tile, whose sums may come out of one column of a matrix product, go opposite ways.  With |V| <= 1 the
+# rounding of the probabilities to bf16 (8 significant bits: 2^-8 of the value at most) moves an output by at most
+# 2 * 2^-8 / (1 - 2^-8) and the normaliser by -log(1 - 2^-8).
+RISES = (70, 200, 201, 330, 470)                            # from each of these keys on one step more
+
+
+def rising_workload(hq, hkv, d, octaves, theta, channels):
+    """Scores in octaves (softmax scale log 2).  Only the features `channels` of Q and K hold anything; the step sits
+    in the last of them, the others hold N(0,1) K and Q of a quarter of that."""
     pr = wl.Problem([50], [400], [2], [40], [[130, 400]])
-    w = wl.make_custom(pr, hq, hkv, d, dtype=torch.bfloat16, rope_theta=0.0, seed=77)
+    w = wl.make_custom(pr, hq, hkv, d, dtype=torch.bfloat16, rope_theta=theta, seed=77)
     n = pr.total_tokens
     rise = torch.zeros(n)
-    for key in (70, 200, 201, 330, 470):                    # each one `octaves` above the one before it
+    for key in RISES:
         rise[key:] += 1.0
-    w.k[:, :, 0] = rise[:, None].to(torch.bfloat16)
-    w.q[:, :, 0] = torch.where(torch.arange(n) % 32 < 16, 1.0, -1.0)[:, None].to(torch.bfloat16) * octaves
+    keep = torch.zeros(d)
+    keep[list(channels)] = 1.0
+    w.q.mul_(0.25 * keep.to(torch.bfloat16))
+    w.k.mul_(keep.to(torch.bfloat16))
+    w.k[:, :, channels[-1]] = rise[:, None].to(torch.bfloat16)
+    w.q[:, :, channels[-1]] = torch.where(torch.arange(n) % 32 < 16, 1.0, -1.0)[:, None].to(torch.bfloat16) * octaves
     w.v.copy_(torch.sign(w.v.float()).to(torch.bfloat16))
-    w.q[:, :, 1:] *= 0.25
+    return w
+
+
+def check_rising(w, octaves, score_err):
+    """`score_err`: how far a score may be off, in octaves, before its exponential is taken."""
     scale = math.log(2.0)
-    ver = gc.make_verifier(pv, w)
-    ver.build_mask()
-    out, lse = gc.run_gpu_attention(pv, w, out_dtype=torch.float32, lse=True, ver=ver, softmax_scale=scale)
+    out, lse = gc.run_gpu_attention(pv, w, out_dtype=torch.float32, lse=True, softmax_scale=scale)
     ref, ref_lse = gc.oracle_attention(w, return_lse=True, scale=scale)
     delta = 2.0 ** -8
-    assert np.abs(out.double().cpu().numpy() - ref).max() <= 2 * delta / (1 - delta) + 1e-5
-    # the score itself: fp32 sums of D products and one fma, relative to the largest term (4 * octaves at most)
-    assert np.abs(lse.double().cpu().numpy().T - ref_lse).max() <= -math.log(1 - delta) + 4 * octaves * 2.0 ** -21
+    weight = (1 + delta) * 2.0 ** score_err - 1             # what a weight, and so the sum of them, may be off by
+    assert np.abs(out.double().cpu().numpy() - ref).max() <= 2 * weight / (1 - weight) + 1e-5
+    # fp32 sums of D products and one fma, relative to the largest term: five steps at most
+    fp32 = len(RISES) * octaves * 2.0 ** -21
+    assert np.abs(lse.double().cpu().numpy().T - ref_lse).max() <= -math.log(1 - weight) + fp32
+
+
+@pytest.mark.parametrize("octaves", [15, 16, 17, 39, 41, 130])
+@pytest.mark.parametrize("hq,hkv,d", [(4, 1, 128), (5, 1, 128), (8, 1, 64), (8, 1, 128)])
+def test_rising_scores(hq, hkv, d, octaves):
+    # Q and K enter the products exactly (no rotation)
+    check_rising(rising_workload(hq, hkv, d, octaves, 0.0, [*range(1, d), 0]), octaves, 0.0)
+
+
+# With rotation the features are those of the slowest pairs, the first half of each pair only.  Over the test's 530
+# positions their angles a stay so small that q cos a and k cos a round to q and k themselves in bf16 (1 - cos a is below
+# a quarter of 2^-8), and the other halves, q sin a and k sin a, round by 2^-8 of themselves at most: a pair's share
+# q k cos(a - b) of a score is off by less than |q k| a^2, a the largest angle.
+@pytest.mark.parametrize("octaves", [15, 16, 17, 39, 41, 130])
+@pytest.mark.parametrize("hq,hkv,d", [(1, 1, 128), (3, 1, 128), (4, 1, 128), (5, 1, 128), (7, 1, 128), (8, 1, 128),
+                                      (4, 1, 64), (8, 1, 64)])
+def test_rising_scores_rotated(hq, hkv, d, octaves):
+    theta = 5e5
+    channels = list(range(d // 2 - 6, d // 2))
+    w = rising_workload(hq, hkv, d, octaves, theta, channels)
+    angle = w.problem.total_tokens * theta ** (-2.0 * np.arange(d) / d)
+    assert 1 - math.cos(angle[channels[0]]) < 2.0 ** -10
+    q, k = (x.double().abs().numpy().max((0, 1)) for x in (w.q, w.k))
+    check_rising(w, octaves, float((q * k * angle ** 2)[channels].sum()))
 
 
 def test_segment_isolation_and_determinism():
