@@ -172,8 +172,14 @@ def _device(t: Optional[torch.Tensor]) -> int:
     return torch.cuda.current_device() if t is None or t.is_cuda else -1
 
 
-def _stream(dev: int) -> int:
-    return torch._C._cuda_getCurrentRawStream(dev)
+def _stream_getter():
+    """The current stream's handle by device index.  torch keeps the direct accessor under a private name: where a
+    release does not have it, the Stream object is built after all."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw or (lambda dev: torch.cuda.current_stream(dev).cuda_stream)
+
+
+_stream = _stream_getter()
 
 
 def pv_build_mask(problem: HostProblem, sizes: PvSizes, plan: torch.Tensor,

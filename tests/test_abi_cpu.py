@@ -270,3 +270,17 @@ def test_prepared_key_calls_validate_on_the_host():
     assert s.n_short_seg_rows == 6 and s.n_short_rows == 16 + 6         # 4 + 9 + 3 = 16 keys at most
     far = q(pv.make_problem([4], [60], [2], [3], [30, 60]), 8, 2, 128)[1]
     assert far.n_short_seg_rows == 0 and far.n_short_rows == 16
+
+
+def test_stream_handle_without_the_private_accessor(monkeypatch):
+    import torch
+    seen = []
+
+    class Stream:
+        cuda_stream = 77
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev: seen.append(dev) or Stream)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert pv._stream_getter()(3) == 77 and seen == [3]
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: 100 + dev, raising=False)
+    assert pv._stream_getter()(3) == 103
