@@ -15,6 +15,7 @@ channels), mean-abs 6e-4 to 2.8e-3, normaliser 1e-2 to 3.2e-2.  The bf16 path's 
 claimed for this storage format.  Rows with at most PV_SHORT_ROW_KEYS keys are evaluated in fp32 and
 must meet 1e-4."""
 import dataclasses
+import math
 
 import numpy as np
 import pytest
@@ -119,6 +120,46 @@ def test_query_tiles_ragged_batch(group, layout):
                        rope_theta=0.0 if group == 2 else 5e5, seed=660 + group)
     _, _, ver = run_fp8(w, label=f"ragged, group {group}, layout {layout}")
     assert ver.sizes.n_quads == 4 + 2 + 5 + 3
+
+
+# Scores that rise (for every second query fall) by `octaves` in every key tile, so also in the second, the next-to-last
+# and the last tile of items with odd and even numbers of tiles: the reference is raised there, and O and the row sum
+# follow a step later.  Q is a power of two throughout and so exact in its first term, K and V are what their codes say;
+# what is left is the rounding of the probabilities: 2^-4 of each, or, below E4M3's smallest normal, half its smallest
+# step, 2^-10, where the largest of the row is 2^8.  With |V| = 1 that moves an output by at most 2 w / (1 - w) and the
+# normaliser by -log(1 - w) = 0.067.  Steps of more octaves test the instruction instead, whose sum of products drops what
+# lies some 15 bits below the largest of them: measured, the normaliser is off by 0.025 where nothing rises, by 0.031 at
+# 32 octaves a step, 0.07 at 64 and 0.18 at 128, as often up as down.
+@pytest.mark.parametrize("octaves", [1, 8, 32])
+@pytest.mark.parametrize("group", [4, 5, 7, 8])
+def test_rising_scores(group, octaves):
+    pr = wl.Problem([50], [400], [2], [40], [[130, 400]])
+    w = wl.make_custom(pr, group, 1, 128, dtype=torch.bfloat16, rope_theta=0.0, seed=690 + group)
+    n = pr.total_tokens
+    rise = ((torch.arange(n) + 59) // 64).float()                         # one step more from keys 5, 69, 133, ...
+    w.q.copy_(0.25 * torch.sign(w.q.float()))
+    w.q[:, :, 0] = torch.where(torch.arange(n) % 32 < 16, 1.0, -1.0)[:, None].to(torch.bfloat16) * octaves
+    w.k[:, :, 0] = rise[:, None].to(torch.bfloat16)
+    w.v.copy_(torch.where(w.v.float() < 0, -1.0, 1.0))
+    kc, ksc = wl.quantize_fp8(w.k)
+    vc, vsc = wl.quantize_fp8(w.v)
+    ver = gc.make_verifier(pv, w)
+    ver.build_mask()
+    dev = ver.device
+    out = torch.zeros(w.q.shape, dtype=torch.float32, device=dev)
+    lse = torch.zeros(group, n, dtype=torch.float32, device=dev)
+    scale = math.log(2.0)
+    pv.pv_masked_attention_fp8kv(ver.sizes, ver.plan, w.q.to(dev), kc.to(dev), vc.to(dev), ksc.to(dev), vsc.to(dev), out,
+                                 ver.workspace, lse, softmax_scale=scale)
+    torch.cuda.synchronize()
+    ref, ref_lse = orc.masked_attention_fp8kv(pr.prompt_len, pr.draft_len, pr.num_segments, pr.segment_len,
+                                              pr.boundaries, w.q.double().numpy(), kc.numpy(), vc.numpy(), ksc.numpy(),
+                                              vsc.numpy(), scale=scale, return_lse=True)
+    weight = 2.0 ** -4 + n * 2.0 ** -18
+    assert np.abs(out.double().cpu().numpy() - ref).max() <= 2 * weight / (1 - weight)
+    # fp32: sums of D products and one fma, relative to the largest score (9 steps)
+    fp32 = 9 * octaves * 2.0 ** -21
+    assert np.abs(lse.double().cpu().numpy().T - ref_lse).max() <= -math.log(1 - weight) + fp32
 
 
 def test_8b_every_row():
