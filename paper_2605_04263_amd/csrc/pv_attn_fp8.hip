@@ -48,10 +48,9 @@ __device__ __forceinline__ float fp8_byte(unsigned word, int byte) {
     default: return __builtin_amdgcn_cvt_f32_fp8((int)word, 3);
   }
 }
-// four floats -> four E4M3 codes in one dword (round to nearest even; callers keep |x| <= 448).  `old` is
-// overwritten: a dead value that already sits in the result's register saves clearing it first.
-__device__ __forceinline__ unsigned pack_fp8x4(float a, float b, float c, float d, int old = 0) {
-  int w = old;
+// four floats -> four E4M3 codes in one dword (round to nearest even; callers keep |x| <= 448)
+__device__ __forceinline__ unsigned pack_fp8x4(float a, float b, float c, float d) {
+  int w = 0;
   w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, w, false);
   w = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
   return (unsigned)w;
