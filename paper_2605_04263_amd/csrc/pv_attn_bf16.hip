@@ -26,14 +26,33 @@
 namespace pv {
 
 // ---------------------------------------------------------------- K/V preparation
+template <bool STREAM>
+__device__ __forceinline__ uint4 load_16(const uint16_t* p) {
+  typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+  if constexpr (!STREAM) return *reinterpret_cast<const uint4*>(p);
+  const u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  return make_uint4(x[0], x[1], x[2], x[3]);
+}
+
 // grid = one block per (short row, kv head) first (they take longest, so they start first), then
-// blocks of 16 keys x 2 kv heads.  Pad rows (beyond the request) are written as 0 so that masked
+// blocks of 16 keys x HG kv heads.  Pad rows (beyond the request) are written as 0 so that masked
 // probabilities (exactly 0) never meet a non-finite value.
 //   n_short_blocks  short-row blocks in this launch (0: none)
 //   key_blocks      whether the launch has key blocks at all (a launch of short rows only has none)
 //   tok_first/last  key blocks that hold no token of the packed range [tok_first, tok_last) leave
 //                   their part of the workspace as it is (keys prepared by an earlier call)
-template <int D>
+// HG and STREAM by the size of the launch (prep_heads).  A launch that the chip holds at once is bound by one block's
+// chain plan -> loads -> angles -> stores and by where its lines lie: one head to a block is the shortest chain, and
+// the block of head h runs on the XCD whose main-kernel workgroups read h (both count heads first, block b on XCD b % 8)
+// and whose L2 still holds the lines that it overwrites.  Passes, us, two heads to a block / one: 32/8 heads of 128, 3 K
+// tokens 87.9 / 84.6, no segment 2.5 K 74.4 / 70.1, 2 K 63.2 / 59.1, 352 tokens 22.7 / 21.4; 16/4 heads, 6 K 91.4 /
+// 88.3; more blocks than that: 4.4 K 168.4 / 167.3, 6 K 144.8 / 146.2, 12 K 274 / 278, 55 K 1355 / 1363 (every block
+// forms the angles of its keys anew).  A large launch is bound by memory: four heads to a block form the angles half as
+// often, and K and V, read once, don't push the prepared keys out of the caches (loads marked as streaming; four
+// heads without the mark are 0.5 to 1.5 % slower): 12 ragged requests of 2.8 K, segment rows 223 / 219, 16 of them 289 /
+// 284, ragged 55 K 398 / 392, whole pass 1355 / 1349; below 80 MB of prepared keys, segment rows of 5 and 6 such
+// requests 102.9 / 106.0 and 122.9 / 127.5.
+template <int D, int HG, bool STREAM>
 __global__ __launch_bounds__(256) void k_prep_kv(const int32_t* __restrict__ plan, PlanHeader h,
                                                  KvSource src, RopeFreq f,
                                                  float2* __restrict__ cs, int hkv, bool rope,
@@ -42,11 +61,10 @@ __global__ __launch_bounds__(256) void k_prep_kv(const int32_t* __restrict__ pla
                                                  int n_short_blocks, int tok_first, int tok_last) {
   constexpr int HALF = D / 2;
   constexpr int KB = 16;                       // keys per block
-  constexpr int HG = 2;                        // kv heads per block
   // one LDS area, used either by a short-row block or by a key block
   constexpr int CS_BYTES = KB * HALF * 8, VS_BYTES = HG * KB * (D / 8 + 1) * 16;
-  static_assert(2 * PV_SHORT_ROW_KEYS * D * 4 <= CS_BYTES + VS_BYTES, "short-row tiles must fit");
-  __shared__ uint4 lds[(CS_BYTES + VS_BYTES) / 16];
+  constexpr int SHORT_BYTES = 2 * PV_SHORT_ROW_KEYS * D * 4;
+  __shared__ uint4 lds[(CS_BYTES + VS_BYTES > SHORT_BYTES ? CS_BYTES + VS_BYTES : SHORT_BYTES) / 16];
   if ((int)blockIdx.x < n_short_blocks) {      // one (short row, kv head) each
     const int idx = (int)blockIdx.x;
     const int4 desc = reinterpret_cast<const int4*>(plan + h.off_short)[idx / hkv];
@@ -62,22 +80,13 @@ __global__ __launch_bounds__(256) void k_prep_kv(const int32_t* __restrict__ pla
   const int row0 = (mb / n_hg) * KB;           // first padded key row of this block
   const int h0 = (mb % n_hg) * HG;             // first kv head of this block
   const int nh = min(HG, hkv - h0);
-  // owner request of the block (requests are padded to multiples of 64 keys)
-  const int32_t* kp = plan + h.off_kpad_start;
-  int lo = 0, hi = h.batch;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (kp[mid] <= row0) lo = mid; else hi = mid;
-  }
-  const int b = lo;
-  const int tok_base = plan[h.off_tok_start + b];
-  const int n_b = plan[h.off_tok_start + b + 1] - tok_base;
-  const int key0 = row0 - kp[b];               // first local key of the block
+  const KeyBlock own = key_block(plan, h, row0);
+  const int tok_base = own.tok_base, n_b = own.n, key0 = own.key0;
   const int tid = threadIdx.x;
   // Uniform over the workgroup: rows beyond the request's padding (a head stride larger than this
   // plan's key count) are never read; a block with tokens runs if one of them is in the requested
   // range; a block of padding only (zeros, see above) goes with the request's last token.
-  if (row0 >= kp[b + 1]) return;
+  if (key0 >= own.n_padded) return;
   const int first_tok = tok_base + min(key0, n_b - 1), end_tok = tok_base + min(key0 + KB, n_b);
   if (first_tok >= tok_last || end_tok <= tok_first) return;
 
@@ -92,7 +101,7 @@ __global__ __launch_bounds__(256) void k_prep_kv(const int32_t* __restrict__ pla
     const int ch = item % (D / 8), hl = (item / (D / 8)) % nh, key = item / ((D / 8) * nh);
     v_reg[it] = make_uint4(0, 0, 0, 0);
     if (item < nh * KB * (D / 8) && key0 + key < n_b)
-      v_reg[it] = *reinterpret_cast<const uint4*>(
+      v_reg[it] = load_16<STREAM>(
           src.v + (src.row(caller_row(plan, h, tok_base + key0 + key)) * hkv + h0 + hl) * D + ch * 8);
   }
 #pragma unroll
@@ -103,8 +112,8 @@ __global__ __launch_bounds__(256) void k_prep_kv(const int32_t* __restrict__ pla
     k_hi[it] = make_uint4(0, 0, 0, 0);
     if (item < nh * KB * (HALF / 8) && key0 + key < n_b) {
       const uint16_t* kr = src.k + (src.row(caller_row(plan, h, tok_base + key0 + key)) * hkv + h0 + hl) * D;
-      k_lo[it] = *reinterpret_cast<const uint4*>(kr + c0);
-      k_hi[it] = *reinterpret_cast<const uint4*>(kr + c0 + HALF);
+      k_lo[it] = load_16<STREAM>(kr + c0);
+      k_hi[it] = load_16<STREAM>(kr + c0 + HALF);
     }
   }
   // cos/sin of the rotary angles (fp64 angle reduced to a fraction of a turn, fp32 result), also
@@ -279,6 +288,13 @@ static hipError_t dispatch_g(int G, const int32_t* plan, const PlanHeader& h, co
   return hipErrorInvalidValue;
 }
 
+// kv heads to a block of the preparation launch: one while the chip holds the whole launch at once (256 compute units
+// of eight such workgroups), four (streaming loads) from 80 MB of prepared keys on; both sides at the kernel.
+static int prep_heads(int64_t padded_keys, int hkv, int d) {
+  if (padded_keys / 16 * hkv <= 256 * 8) return 1;
+  return padded_keys * hkv * d * 4 < (80ll << 20) ? 2 : 4;
+}
+
 // K/V preparation (key blocks of the token range, and the short rows unless sr.q is null).
 hipError_t launch_prep_bf16(const int32_t* plan_dev, const PlanHeader& h, const KvArgs& kv, int hkv, int d,
                             const RopeFreq& freq, bool rope, char* ws, const AttnWorkspace& wl,
@@ -297,13 +313,19 @@ hipError_t launch_prep_bf16(const int32_t* plan_dev, const PlanHeader& h, const 
   sr.q = reinterpret_cast<const uint16_t*>(q); sr.out = out; sr.lse = lse; sr.hq = hq; sr.scale = scale;
   sr.out_f32 = out_f32; sr.seg_only = segments_only; sr.table = nullptr;
   const int64_t n_short = q ? (int64_t)h.n_short_rows * hkv : 0;
-  const int64_t n_key = key_blocks ? (int64_t)(h.padded_keys / 16) * ((hkv + 1) / 2) : 0;
+  const int hg = prep_heads(h.padded_keys, hkv, d);
+  const int64_t n_key = key_blocks ? (int64_t)(h.padded_keys / 16) * ((hkv + hg - 1) / hg) : 0;
   if (n_short + n_key == 0) return hipSuccess;
   dim3 grid;
   if (!grid_1d(n_short + n_key, 256, &grid) || n_short > 0x7fffffff) return hipErrorInvalidConfiguration;
   const int t0 = (int)tok_first, t1 = (int)tok_last;
-  if (d == 64) k_prep_kv<64><<<grid, dim3(256), 0, s>>>(plan_dev, h, src, freq, cs, hkv, rope, krot, vt, sr, (int)n_short, t0, t1);
-  else k_prep_kv<128><<<grid, dim3(256), 0, s>>>(plan_dev, h, src, freq, cs, hkv, rope, krot, vt, sr, (int)n_short, t0, t1);
+#define PV_PREP(D, HG, STREAM) k_prep_kv<D, HG, STREAM><<<grid, dim3(256), 0, s>>>(plan_dev, h, src, freq, cs, hkv, rope, krot, vt, sr, (int)n_short, t0, t1)
+  if (d == 64) {
+    if (hg == 1) PV_PREP(64, 1, false); else if (hg == 2) PV_PREP(64, 2, false); else PV_PREP(64, 4, true);
+  } else {
+    if (hg == 1) PV_PREP(128, 1, false); else if (hg == 2) PV_PREP(128, 2, false); else PV_PREP(128, 4, true);
+  }
+#undef PV_PREP
   return hipGetLastError();
 }
 

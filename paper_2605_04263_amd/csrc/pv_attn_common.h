@@ -118,6 +118,26 @@ struct CallerRows {
   __device__ __forceinline__ int64_t of(int row) const { return __shfl(mine, row); }
 };
 
+// The request that owns padded key row `row0` (requests are padded to multiples of 64 keys), for a preparation block.
+// One request: everything is in the header, and a block starts with its loads instead of a round trip to the plan
+// (passes, us, 352 tokens 22.8 / 21.4, 2.5 K tokens 70.8 / 70.1).
+struct KeyBlock {
+  int tok_base, n;        // first packed row of the request, its tokens
+  int key0;               // row0 in the request
+  int n_padded;           // its padded keys
+};
+__device__ __forceinline__ KeyBlock key_block(const int32_t* plan, const PlanHeader& h, int row0) {
+  if (h.batch == 1) return {0, h.total_tokens, row0, (h.total_tokens + kTileN - 1) / kTileN * kTileN};
+  const int32_t* kp = plan + h.off_kpad_start;
+  int lo = 0, hi = h.batch;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (kp[mid] <= row0) lo = mid; else hi = mid;
+  }
+  const int tok_base = plan[h.off_tok_start + lo];
+  return {tok_base, plan[h.off_tok_start + lo + 1] - tok_base, row0 - kp[lo], kp[lo + 1] - kp[lo]};
+}
+
 // s_waitcnt immediate (gfx9 encoding) that waits for vmcnt <= n only.
 __host__ __device__ constexpr int vmcnt_imm(int n) { return 0x0f70 | (n & 15) | ((n >> 4) << 14); }
 

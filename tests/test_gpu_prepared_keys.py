@@ -1,0 +1,97 @@
+"""The prepared keys in the workspace, element by element: each number of kv heads to a block of the preparation (one
+for a launch that the chip holds at once, two, four from 80 MB of keys on) with heads left over and requests that end
+inside a block; FP8 blocks of half a key tile, whose share of the angles depends on the number of heads.  Codes and
+unrotated values are copies and have to be the same bits; the table holds cos and sin of fp32 angles reduced in fp64,
+2.6e-7 from fp64 at most."""
+import numpy as np
+import pytest
+import torch
+
+import pv_workloads as wl
+
+pytestmark = pytest.mark.gpu
+pv = pytest.importorskip("paper_2605_04263_amd.binding")
+
+
+def problem(lengths):
+    """Requests of the given lengths, one segment of 5 tokens where it fits."""
+    k = [1 if n > 12 else 0 for n in lengths]
+    return wl.Problem([3 if x else 0 for x in k], [n - 8 if x else n for n, x in zip(lengths, k)], k, [5] * len(k),
+                      [[(n - 8) // 2] if x else [] for n, x in zip(lengths, k)])
+
+
+def padded(pr, x):
+    """x [tokens, ...] with every request padded with zeros to a multiple of 64 rows."""
+    cu, parts = pr.token_offsets(), []
+    for b in range(pr.batch):
+        n = pr.seq_len(b)
+        parts += [x[cu[b]:cu[b] + n], torch.zeros((-n % 64, *x.shape[1:]), dtype=x.dtype, device=x.device)]
+    return torch.cat(parts)
+
+
+def area(ws, at, like):
+    return ws[at:at + like.numel() * like.element_size()].view(like.dtype).view(like.shape)
+
+
+def up(n):
+    return (n + 255) // 256 * 256
+
+
+def check_table(ws, pr, theta, d):
+    pos = np.concatenate([np.r_[np.arange(p + t), np.concatenate([[]] + [p + x + np.arange(s) for x in b])]
+                          for p, t, s, b in zip(pr.prompt_len, pr.draft_len, pr.segment_len, pr.boundaries)])
+    angle = pos[:, None] * theta ** (-2.0 * np.arange(d // 2) / d)
+    got = ws[:pr.total_tokens * d * 4].view(torch.float32).view(pr.total_tokens, d // 2, 2).double().cpu().numpy()
+    assert np.abs(got[..., 0] - np.cos(angle)).max() < 3e-7 and np.abs(got[..., 1] - np.sin(angle)).max() < 3e-7
+
+
+@pytest.mark.parametrize("hkv,d,lengths,heads", [
+    (1, 64, [1], 1), (3, 128, [33, 64, 65, 16, 17], 1), (8, 64, [4096], 1),
+    (8, 128, [4097], 2), (5, 64, [6000, 1, 700], 2), (3, 128, [11000], 2),
+    (5, 128, [30000, 31, 2800], 4), (6, 128, [27400], 4),
+])
+def test_bf16(hkv, d, lengths, heads):
+    pr = problem(lengths)
+    keys = sum((n + 63) // 64 * 64 for n in lengths)
+    assert heads == (1 if keys // 16 * hkv <= 2048 else 2 if keys * hkv * d * 4 < 80 << 20 else 4)
+    n = pr.total_tokens
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    k, v = (torch.randn(n, hkv, d, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    ver = pv.Verifier(pr.prompt_len, pr.draft_len, pr.num_segments, pr.segment_len, pr.flat_boundaries(), hkv, hkv, d,
+                      torch.bfloat16)
+    ver.build_mask()
+    ws = torch.full((pv.pv_prepared_workspace_bytes(ver.sizes),), 0x7f, dtype=torch.uint8, device="cuda")
+    pv.pv_prepare_kv(ver.sizes, ver.plan, k, v, ws, 0.0)
+    # K: chunk (t, hh, key) of a block of 32 keys; V^T: [hh][feature][m], key 8 (m / 4) + 4 hh + m % 4 of a slab of 16
+    want_k = padded(pr, k).view(keys // 32, 32, hkv, d // 16, 2, 8).permute(2, 0, 3, 4, 1, 5).contiguous()
+    want_v = padded(pr, v).view(keys // 16, 2, 2, 4, hkv, d).permute(4, 0, 2, 5, 1, 3).contiguous()
+    at = up(n * d * 4)
+    assert torch.equal(area(ws, at, want_k).view(torch.int16), want_k.view(torch.int16))
+    assert torch.equal(area(ws, at + up(hkv * keys * d * 2), want_v).view(torch.int16), want_v.view(torch.int16))
+    pv.pv_prepare_kv(ver.sizes, ver.plan, k, v, ws, 5e5)
+    check_table(ws, pr, 5e5, d)
+
+
+@pytest.mark.parametrize("hkv,lengths", [(1, [40]), (3, [33, 64, 65, 31, 127]), (8, [300]), (16, [97, 1]), (20, [64])])
+def test_fp8(hkv, lengths):
+    pr = problem(lengths)
+    n, d, keys = pr.total_tokens, 128, sum((n + 63) // 64 * 64 for n in lengths)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    k, v = (torch.randint(0, 120, (n, hkv, d), device="cuda", generator=gen, dtype=torch.uint8) for _ in range(2))
+    q = torch.randn(n, hkv, d, device="cuda", generator=gen).to(torch.bfloat16)
+    scale = torch.full((hkv,), 0.01, device="cuda")
+    ver = pv.Verifier(pr.prompt_len, pr.draft_len, pr.num_segments, pr.segment_len, pr.flat_boundaries(), hkv, hkv, d,
+                      torch.bfloat16)
+    ver.build_mask()
+    ver.workspace.view(torch.uint8).fill_(0x7f)
+    pv.pv_masked_attention_fp8kv(ver.sizes, ver.plan, q, k, v, scale, scale, torch.empty_like(q), ver.workspace,
+                                 rope_theta=5e5)
+    ws = ver.workspace.view(torch.uint8)
+    # K: chunk (u, t, c, hh, key) = features 64 t + 32 hh + 16 c of key 32 u + key; V^T: chunk (db, c, hh, feature) =
+    # the keys 32 c + 8 i + 4 hh + e, byte 4 i + e
+    want_k = padded(pr, k).view(keys // 64, 2, 32, hkv, 2, 2, 2, 16).permute(3, 0, 1, 4, 6, 5, 2, 7).contiguous()
+    want_v = padded(pr, v).view(keys // 64, 2, 4, 2, 4, hkv, 4, 32).permute(5, 0, 6, 1, 3, 7, 2, 4).contiguous()
+    at = up(n * d * 4)
+    assert torch.equal(area(ws, at, want_k), want_k)
+    assert torch.equal(area(ws, at + up(hkv * keys * d * 2), want_v), want_v)
+    check_table(ws, pr, 5e5, d)
