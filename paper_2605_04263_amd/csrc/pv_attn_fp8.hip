@@ -57,13 +57,18 @@ __device__ __forceinline__ unsigned pack_fp8x4(float a, float b, float c, float 
 }
 
 // ---------------------------------------------------------------- preparation
-// One workgroup per (64-key tile, kv head).  Workspace per kv head and tile (8 KB each for D = 128):
+// One workgroup per (32 keys, kv head).  Workspace per kv head and tile (8 KB each for D = 128):
 //   K:    16-byte chunk ((u * 2 + t) * 2 + c) * 64 + l  = features 64 t + 32 (l / 32) + 16 c .. + 15
 //         of key 32 u + l % 32           (u: 32-key half, t: 64-feature half)
 //   V^T:  16-byte chunk (db * 2 + c) * 64 + l            = feature 32 db + l % 32 at the 16 keys
 //         32 c + 8 i + 4 (l / 32) + e, byte 4 i + e      (the key order in which the accumulator
 //         registers of S^T hold keys, so probabilities go into the second product in place)
-// Pad keys (beyond the request) are zero codes.
+// Pad keys (beyond the request) are zero codes.  Latency bounds a small launch: half a tile to a workgroup is one load
+// of K and of V and one chunk of V^T a thread, and the angles of its keys are shared out among the heads' workgroups and
+// formed while the loads fly, where a whole tile with all its angles at the end of the first head's workgroups was
+// a chain of its own.  Passes, us,
+// before / with it: 3 K tokens at 32/8 heads 80.3 / 77.6, 4.5 K at 28/4 heads 138.7 / 136.3, ragged 23 K 518.5 / 519.5,
+// 4 x 14 K at 64/8 heads 7132 / 7074.
 template <int D>
 __global__ __launch_bounds__(256) void k_prep_fp8(const int32_t* __restrict__ plan, PlanHeader h,
                                                   const uint8_t* __restrict__ k8,
@@ -72,61 +77,48 @@ __global__ __launch_bounds__(256) void k_prep_fp8(const int32_t* __restrict__ pl
                                                   uint8_t* __restrict__ kw, uint8_t* __restrict__ vw) {
   static_assert(D == 128, "the FP8 path is built for head_dim 128");
   constexpr int CPR = D / 16;                              // 16-byte chunks per key row
-  __shared__ uint4 v_s[kStepKeys][CPR + 1];                // V rows of the tile, padded
-  const int tile = (int)blockIdx.x / hkv, kvh = (int)blockIdx.x % hkv;
-  const int row0 = tile * kStepKeys;                       // first padded key row
-  const int32_t* kp = plan + h.off_kpad_start;
-  int lo = 0, hi = h.batch;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (kp[mid] <= row0) lo = mid; else hi = mid;
-  }
-  const int b = lo;
-  const int tok_base = plan[h.off_tok_start + b];
-  const int n_b = plan[h.off_tok_start + b + 1] - tok_base;
-  const int key0 = row0 - kp[b];
+  constexpr int KB = 32;                                   // keys per block
+  static_assert(KB * CPR == 256 && (D / 32) * 64 == 256, "one chunk of K, V and V^T a thread");
+  __shared__ uint4 v_s[KB][CPR + 1];                       // V rows of the block, padded
+  const int kvh = (int)blockIdx.x % hkv;
+  const int row0 = (int)blockIdx.x / hkv * KB;             // first padded key row
+  const KeyBlock own = key_block(plan, h, row0);
+  const int tok_base = own.tok_base, n_b = own.n, key0 = own.key0;
   const int tid = threadIdx.x;
-  uint8_t* k_out = kw + ((int64_t)kvh * h.padded_keys + row0) * D;
-  uint8_t* v_out = vw + ((int64_t)kvh * h.padded_keys + row0) * D;
-#pragma unroll
-  for (int it = 0; it < kStepKeys * CPR / 256; ++it) {
-    const int ch = tid + it * 256, key = ch / CPR, c16 = ch % CPR;
-    uint4 kx = make_uint4(0, 0, 0, 0), vx = make_uint4(0, 0, 0, 0);
-    if (key0 + key < n_b) {
-      const int64_t src = (caller_row(plan, h, tok_base + key0 + key) * hkv + kvh) * D + c16 * 16;
-      kx = *reinterpret_cast<const uint4*>(k8 + src);
-      vx = *reinterpret_cast<const uint4*>(v8 + src);
-    }
-    const int u = key >> 5, t = c16 >> 2, hh = (c16 >> 1) & 1, c = c16 & 1;
-    reinterpret_cast<uint4*>(k_out)[((u * 2 + t) * 2 + c) * 64 + hh * 32 + (key & 31)] = kx;
-    v_s[key][c16] = vx;
+  const int half = (row0 / KB) & 1;                        // which half of the 64-key tile
+  const int64_t tile_at = ((int64_t)kvh * h.padded_keys + (row0 & ~(kStepKeys - 1))) * D;
+  const int key = tid / CPR, c16 = tid % CPR;
+  uint4 kx = make_uint4(0, 0, 0, 0), vx = make_uint4(0, 0, 0, 0);
+  if (key0 + key < n_b) {
+    const int64_t src = (caller_row(plan, h, tok_base + key0 + key) * hkv + kvh) * D + c16 * 16;
+    kx = *reinterpret_cast<const uint4*>(k8 + src);
+    vx = *reinterpret_cast<const uint4*>(v8 + src);
   }
-  __syncthreads();
-  const uint8_t* vb = reinterpret_cast<const uint8_t*>(&v_s[0][0]);
-  constexpr int VROW = (CPR + 1) * 16;
-#pragma unroll
-  for (int it = 0; it < (D / 32) * 2 * 64 / 256; ++it) {
-    const int ch = tid + it * 256, l = ch & 63, c = (ch >> 6) & 1, db = ch >> 7;
-    const int feat = 32 * db + (l & 31), hh = l >> 5;
-    unsigned w[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      w[i] = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        w[i] |= (unsigned)vb[(32 * c + 8 * i + 4 * hh + e) * VROW + feat] << (8 * e);
-    }
-    reinterpret_cast<uint4*>(v_out)[(db * 2 + c) * 64 + l] = make_uint4(w[0], w[1], w[2], w[3]);
-  }
-  if (rope && kvh == 0) {
-    for (int item = tid; item < kStepKeys * (D / 2); item += 256) {
-      const int key = item / (D / 2), c = item % (D / 2);
-      if (key0 + key < n_b) {
-        const int64_t g = tok_base + key0 + key;
+  if (rope) {
+    for (int item = kvh * 256 + tid; item < KB * (D / 2); item += hkv * 256) {
+      const int rkey = item / (D / 2), c = item % (D / 2);
+      if (key0 + rkey < n_b) {
+        const int64_t g = tok_base + key0 + rkey;
         cs[g * (D / 2) + c] = rotary_cos_sin(plan[h.off_pos + g], f.inv_freq[c]);
       }
     }
   }
+  const int t = c16 >> 2, hh = (c16 >> 1) & 1, c = c16 & 1;
+  reinterpret_cast<uint4*>(kw + tile_at)[((half * 2 + t) * 2 + c) * 64 + hh * 32 + key] = kx;
+  v_s[key][c16] = vx;
+  __syncthreads();
+  const uint8_t* vb = reinterpret_cast<const uint8_t*>(&v_s[0][0]);
+  constexpr int VROW = (CPR + 1) * 16;
+  const int l = tid & 63, db = tid >> 6;
+  const int feat = 32 * db + (l & 31), vhh = l >> 5;
+  unsigned w[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    w[i] = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[i] |= (unsigned)vb[(8 * i + 4 * vhh + e) * VROW + feat] << (8 * e);
+  }
+  reinterpret_cast<uint4*>(vw + tile_at)[(db * 2 + half) * 64 + l] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // ---------------------------------------------------------------- rows with few keys, fp32
@@ -730,7 +722,7 @@ hipError_t launch_attn_fp8(const int32_t* plan_dev, const PlanHeader& h, const v
   const uint16_t* kq = reinterpret_cast<const uint16_t*>(q);
   const bool out_f32 = out_dtype == PV_F32;
   dim3 grid;
-  if (!grid_1d((int64_t)(h.padded_keys / kStepKeys) * hkv, 256, &grid)) return hipErrorInvalidConfiguration;
+  if (!grid_1d((int64_t)(h.padded_keys / 32) * hkv, 256, &grid)) return hipErrorInvalidConfiguration;
   k_prep_fp8<128><<<grid, dim3(256), 0, s>>>(plan_dev, h, (const uint8_t*)k8, (const uint8_t*)v8, freq, cs, hkv, rope, kw, vw);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
