@@ -356,6 +356,7 @@ pv_status pv_build_mask(const pv_problem* problem, const pv_sizes* sizes, void* 
   if (st != PV_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = launch_plan_kernels((int32_t*)plan_dev, h, img.data(), (int)img.size(),
+                                     t.short_seg_rows == 0 && t.short_rows == (int64_t)B * PV_SHORT_ROW_KEYS,
                                      dense_mask_dev, s);
   if (e != hipSuccess) return hip_fail(e);
   return PV_OK;

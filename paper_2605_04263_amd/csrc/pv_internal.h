@@ -98,9 +98,10 @@ AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, i
                                     int hq, int hkv, int d, int in_dtype);
 
 // --- launchers (each returns the hipError_t of its launches) ---
-// Uploads the host image (n_img ints at the start of the plan) and builds the device part.
+// Uploads the host image (n_img ints at the start of the plan) and builds the device part.  causal_short: the rows
+// with few keys are the first PV_SHORT_ROW_KEYS rows of every request and no others.
 hipError_t launch_plan_kernels(int32_t* plan_dev, const PlanHeader& h, const int32_t* host_ints,
-                               int n_img, uint8_t* dense_mask, hipStream_t s);
+                               int n_img, bool causal_short, uint8_t* dense_mask, hipStream_t s);
 hipError_t launch_plan_export(const int32_t* plan_dev, const PlanHeader& h, int32_t* pos,
                               int32_t* aend, int32_t* bstart, int32_t* judge, hipStream_t s);
 hipError_t launch_first_reject(const int32_t* plan_dev, const PlanHeader& h, const float* logits,

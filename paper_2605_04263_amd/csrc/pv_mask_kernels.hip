@@ -96,8 +96,13 @@ __device__ inline int find_owner(const int32_t* start, int n, int x) {
 }
 
 // Row g of the packed batch (and, for g < total_segments, judge row g).  `img` is where the
-// uploaded part of the plan is read from (the plan itself, or a copy in LDS).
-__device__ inline void plan_token(int32_t* plan, const int32_t* img, const PlanHeader& h, int g) {
+// uploaded part of the plan is read from (the plan itself, or a copy in LDS).  causal_short: the rows with few
+// keys are the first PV_SHORT_ROW_KEYS rows of every request and their list is written here.
+__device__ inline void plan_token(int32_t* plan, const int32_t* img, const PlanHeader& h, int g, bool causal_short) {
+  if (causal_short && g < h.n_short_rows) {
+    const int base = img[h.off_tok_start + g / PV_SHORT_ROW_KEYS];
+    reinterpret_cast<int4*>(plan + h.off_short)[g] = make_int4(base + g % PV_SHORT_ROW_KEYS, base, 0, 0);
+  }
   if (g < h.total_tokens) {
     const int b = find_owner(img + h.off_tok_start, h.batch, g);
     const Req r = load_req(img, h, b);
@@ -202,95 +207,108 @@ __device__ inline void plan_quad(int32_t* plan, const int32_t* img, const PlanHe
   reinterpret_cast<QTile*>(plan + h.off_quadwork)[q0 + (nq - 1 - ql)] = u;
 }
 
-// Larger problems: per-token arrays, tiles and groups of tiles in one launch, a range of workgroups for
-// each; all of them read the request data only (`img` as in plan_token).
-__device__ inline void plan_build(int32_t* plan, const int32_t* img, const PlanHeader& h, int tile_blocks,
-                                  int quad_blocks) {
+// The whole plan in one launch.  The request data (in the kernel arguments, or uploaded before) are copied to LDS by
+// every workgroup, and no workgroup reads what another writes: a workgroup that ranks kRankTiles tiles, a wave each,
+// forms the costs of all tiles itself.  That is two tiles a thread at 1 766 tiles (a tile is a chain of LDS reads and
+// divisions of 0.7 us: with 256 threads to a workgroup and seven tiles a thread the launch took 11.5 us), against a
+// launch of its own for the ranking and its wait for the tiles.  Longest first, ties in the order of the tiles: the cost, the tile's index from
+// the end and whether it holds segment rows make one number.  Launches, us, in two or three kernels / with it: 16 ragged
+// requests of 55 K tokens 22.5 / 7.3 (16 lanes to a tile 9.8: too few compute units with work); one workgroup that
+// ranked all tiles / with it: 208 tiles 11.9 / 5.1, 96 tiles 5.6 / 5.0.
+constexpr int kPlanThreads = 1024, kRankTiles = kPlanThreads / 64, kPlanTiles = 4096, kPlanData = 4096;   // (tiles and ints of request data in LDS)
+__device__ inline void plan_all(int32_t* plan, const int32_t* img, unsigned* key_s, const PlanHeader& h, int rank_blocks,
+                                int quad_blocks, bool causal_short) {
+  const int blk = (int)blockIdx.x, tid = (int)threadIdx.x;
+  if (blk >= rank_blocks + quad_blocks) {
+    plan_token(plan, img, h, (blk - rank_blocks - quad_blocks) * kPlanThreads + tid, causal_short);
+    return;
+  }
+  if (blk >= rank_blocks) {
+    const int qd = (blk - rank_blocks) * (kPlanThreads / 4) + (tid >> 2);
+    if (qd < h.n_quads) plan_quad(plan, img, h, qd, tid & 3);
+    return;
+  }
+  const int n = h.n_q_tiles, n_padded = (n + 255) & ~255;
+  static_assert((1 << 24) / kTileN + 8 < 1 << 19 && kPlanTiles <= 1 << 12, "cost, tile and flag fit 32 bits");
+  __shared__ QTile mine_s[kRankTiles];
+  for (int t = tid; t < n_padded; t += kPlanThreads) {
+    unsigned key = 0u;               // a cost is at least 1: zero comes behind every tile
+    if (t < n) {
+      int seg_slot;
+      const QTile q = plan_tile(img, h, t, &seg_slot);
+      key = (unsigned)(q.n_a + (q.jb1 - q.jb0)) << 13 | (unsigned)(kPlanTiles - 1 - t) << 1 | (unsigned)(seg_slot >= 0);
+      if (t / kRankTiles == blk) mine_s[t % kRankTiles] = q;
+    }
+    key_s[t] = key;
+  }
+  __syncthreads();
+  const int t = blk * kRankTiles + (tid >> 6), lane = tid & 63;
+  if (t >= n) return;
+  const unsigned my_key = key_s[t];
+  int rank = 0, seg_rank = 0;      // among all tiles, among those that hold segment rows
+  for (int x = lane * 4; x < n_padded; x += 256) {
+    const uint4 k4 = *reinterpret_cast<const uint4*>(key_s + x);
+    const unsigned ks[4] = {k4.x, k4.y, k4.z, k4.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const unsigned before = ks[e] > my_key;
+      rank += before;
+      seg_rank += before & ks[e];
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    rank += __shfl_xor(rank, off);
+    seg_rank += __shfl_xor(seg_rank, off);
+  }
+  if (lane == 0) {
+    const QTile mine = mine_s[tid >> 6];
+    reinterpret_cast<QTile*>(plan + h.off_tiles)[t] = mine;
+    reinterpret_cast<QTile*>(plan + h.off_work)[rank] = mine;
+    if (my_key & 1u) reinterpret_cast<QTile*>(plan + h.off_segwork)[seg_rank] = mine;
+  }
+}
+// n_img ints of the arguments are the start of the plan (its last workgroup, one of tokens, writes them there).
+__global__ __launch_bounds__(kPlanThreads) void k_plan_args(int32_t* plan, PlanHeader h, UploadChunk c, int n_img, int rank_blocks,
+                                                   int quad_blocks, bool causal_short) {
+  __shared__ int32_t img_s[kUploadInts];
+  __shared__ __align__(16) unsigned key_s[kPlanTiles];
+  for (int i = threadIdx.x; i < n_img; i += kPlanThreads) {
+    const int32_t x = c.v[i];
+    if (blockIdx.x == gridDim.x - 1) plan[i] = x;
+    img_s[i] = x;
+  }
+  __syncthreads();
+  plan_all(plan, img_s, key_s, h, rank_blocks, quad_blocks, causal_short);
+}
+// The request data are in the plan already.
+__global__ __launch_bounds__(kPlanThreads) void k_plan_uploaded(int32_t* plan, PlanHeader h, int n_data, int rank_blocks,
+                                                       int quad_blocks, bool causal_short) {
+  __shared__ int32_t img_s[kPlanData];
+  __shared__ __align__(16) unsigned key_s[kPlanTiles];
+  for (int i = threadIdx.x; i < n_data; i += kPlanThreads) img_s[i] = plan[i];
+  __syncthreads();
+  plan_all(plan, img_s, key_s, h, rank_blocks, quad_blocks, causal_short);
+}
+
+// Beyond those limits (a workgroup for every 16 tiles would form too many costs): per-token arrays, tiles and groups
+// of tiles in one launch, a range of workgroups for each, then the ranking.
+__global__ __launch_bounds__(256) void k_plan_build(int32_t* plan, PlanHeader h, int tile_blocks, int quad_blocks,
+                                                    bool causal_short) {
   const int blk = (int)blockIdx.x, tid = (int)threadIdx.x;
   if (blk < tile_blocks) {
     const int t = blk * 256 + tid;
     if (t < h.n_q_tiles) {
       int seg_slot;
-      const QTile q = plan_tile(img, h, t, &seg_slot);
+      const QTile q = plan_tile(plan, h, t, &seg_slot);
       reinterpret_cast<QTile*>(plan + h.off_tiles)[t] = q;
       if (seg_slot >= 0) reinterpret_cast<QTile*>(plan + h.off_segwork)[h.n_seg_tiles + seg_slot] = q;   // sorted below
     }
   } else if (blk < tile_blocks + quad_blocks) {
     const int qd = (blk - tile_blocks) * 64 + (tid >> 2);
-    if (qd < h.n_quads) plan_quad(plan, img, h, qd, tid & 3);
+    if (qd < h.n_quads) plan_quad(plan, plan, h, qd, tid & 3);
   } else {
-    plan_token(plan, img, h, (blk - tile_blocks - quad_blocks) * 256 + tid);
-  }
-}
-
-// The request data in the kernel arguments: every workgroup has it without a launch before this one
-// (workgroup 0 writes it to the plan) and looks its requests up in LDS.
-__global__ __launch_bounds__(256) void k_plan_build_args(int32_t* plan, PlanHeader h, UploadChunk c, int n_img,
-                                                         int tile_blocks, int quad_blocks) {
-  __shared__ int32_t img_s[kUploadInts];
-  for (int i = threadIdx.x; i < n_img; i += 256) {
-    const int32_t x = c.v[i];
-    if (blockIdx.x == 0) plan[i] = x;
-    img_s[i] = x;
-  }
-  __syncthreads();
-  plan_build(plan, img_s, h, tile_blocks, quad_blocks);
-}
-// The request data uploaded before (too many requests or segments for the arguments).
-__global__ __launch_bounds__(256) void k_plan_build(int32_t* plan, PlanHeader h, int tile_blocks, int quad_blocks) {
-  plan_build(plan, plan, h, tile_blocks, quad_blocks);
-}
-
-// Small problems: the whole plan in one launch.  The host image arrives in the kernel arguments, so
-// every workgroup has it without waiting for another: workgroup 0 writes it to the plan and builds the
-// tile lists (phases separated by workgroup barriers), the other workgroups share the per-token
-// arrays among them.  Nothing written by one workgroup is read by another inside the launch.
-constexpr int kSmallTokens = 8192, kSmallTiles = 1024;
-__global__ __launch_bounds__(1024) void k_plan_small(int32_t* plan, PlanHeader h, UploadChunk c,
-                                                     int n_img) {
-  __shared__ int key_s[kSmallTiles];
-  __shared__ int32_t img_s[kUploadInts];       // the request data is read from here, not from HBM
-  const int tid = threadIdx.x;
-  const bool first = blockIdx.x == 0;
-  for (int i = tid; i < n_img; i += 1024) {
-    const int32_t x = c.v[i];
-    if (first) plan[i] = x;
-    img_s[i] = x;
-  }
-  __syncthreads();
-  const int n1 = h.total_tokens > h.total_segments ? h.total_tokens : h.total_segments;
-  if (gridDim.x == 1 || !first) {              // tokens: all workgroups but the first, if there are others
-    const int nb = gridDim.x == 1 ? 1 : (int)gridDim.x - 1, me = gridDim.x == 1 ? 0 : (int)blockIdx.x - 1;
-    for (int g = me * 1024 + tid; g < n1; g += nb * 1024) plan_token(plan, img_s, h, g);
-  }
-  if (!first) return;
-  QTile mine;
-  int my_key = 0;              // 2 x cost, + 1 if the tile holds segment rows
-  if (tid < h.n_q_tiles) {
-    int seg_slot;
-    mine = plan_tile(img_s, h, tid, &seg_slot);
-    const int my_cost = mine.n_a + (mine.jb1 - mine.jb0);
-    reinterpret_cast<QTile*>(plan + h.off_tiles)[tid] = mine;
-    my_key = 2 * my_cost + (seg_slot >= 0 ? 1 : 0);
-    key_s[tid] = my_key;
-  }
-  // The groups of four tiles (four lanes each) go to the waves after those of the tiles.  There is room for both:
-  // a request takes at least 16 ints of the image, so there are at most 56, with at most 8192 / 32 + 56 = 312
-  // tiles and 312 / 4 + 56 = 134 groups, and 320 + 4 * 134 threads are fewer than 1024.
-  static_assert(kUploadInts / 16 == 56 && kSmallTokens / 32 == 256, "the bound above");
-  const int x = tid - ((h.n_q_tiles + 63) & ~63);
-  if (x >= 0 && x < 4 * h.n_quads) plan_quad(plan, img_s, h, x >> 2, x & 3);
-  __syncthreads();
-  if (tid < h.n_q_tiles) {          // longest first, stable
-    int rank = 0, seg_rank = 0;     // among all tiles, among those that hold segment rows
-    for (int x = 0; x < h.n_q_tiles; ++x) {
-      const int kx = key_s[x];
-      const int before = (kx >> 1) > (my_key >> 1) || ((kx >> 1) == (my_key >> 1) && x < tid);
-      rank += before;
-      seg_rank += before & kx;
-    }
-    reinterpret_cast<QTile*>(plan + h.off_work)[rank] = mine;
-    if (my_key & 1) reinterpret_cast<QTile*>(plan + h.off_segwork)[seg_rank] = mine;
+    plan_token(plan, plan, h, (blk - tile_blocks - quad_blocks) * 256 + tid, causal_short);
   }
 }
 
@@ -349,34 +367,38 @@ __global__ __launch_bounds__(256) void k_dense_mask(const int32_t* plan, PlanHea
 }
 
 hipError_t launch_plan_kernels(int32_t* plan_dev, const PlanHeader& h, const int32_t* host_ints,
-                               int n_img, uint8_t* dense_mask, hipStream_t s) {
-  hipError_t e;
+                               int n_img, bool causal_short, uint8_t* dense_mask, hipStream_t s) {
+  hipError_t e = hipSuccess;
   const int n1 = h.total_tokens > h.total_segments ? h.total_tokens : h.total_segments;
-  if (n_img <= kUploadInts && n1 <= kSmallTokens && h.n_q_tiles <= kSmallTiles) {
-    UploadChunk c;
-    for (int i = 0; i < n_img; ++i) c.v[i] = host_ints[i];
-    for (int i = n_img; i < kUploadInts; ++i) c.v[i] = 0;
-    const int token_groups = (n1 + 1023) / 1024;                 // at most three extra workgroups
-    k_plan_small<<<dim3(1 + (token_groups < 3 ? token_groups : 3)), dim3(1024), 0, s>>>(plan_dev, h, c, n_img);
-    e = hipGetLastError();
+  // The host image: all of it in the arguments of the launch that uses it, or the request data there and the rows
+  // with few keys behind them written by the launch (the first ones of every request) or uploaded, or all uploaded.
+  const bool in_args = h.off_short <= kUploadInts;
+  const int n_args = n_img <= kUploadInts ? n_img : in_args ? h.off_short : 0;
+  if (n_img <= kUploadInts) causal_short = false;
+  const bool one_launch = h.n_q_tiles <= kPlanTiles && h.off_short <= kPlanData;
+  const int n_upload = causal_short ? h.off_short : n_img, uploaded = one_launch ? n_args : 0;
+  if (uploaded < n_upload) {
+    e = launch_upload(plan_dev + uploaded, host_ints + uploaded, n_upload - uploaded, s);
     if (e != hipSuccess) return e;
-  } else {
-    // The request data go with the launch that uses them where they fit its arguments; the rows with few
-    // keys, behind them in the image, are for later calls only.
-    const bool in_args = h.off_short <= kUploadInts;
-    const int n_args = in_args ? h.off_short : 0;
-    e = launch_upload(plan_dev + n_args, host_ints + n_args, n_img - n_args, s);
-    if (e != hipSuccess) return e;
-    const int tile_blocks = (h.n_q_tiles + 255) / 256, quad_blocks = (h.n_quads + 63) / 64;
-    const dim3 grid(tile_blocks + quad_blocks + (n1 + 255) / 256);
-    if (in_args) {
+  }
+  if (one_launch) {
+    const int rank_blocks = (h.n_q_tiles + kRankTiles - 1) / kRankTiles;
+    const int quad_blocks = (4 * h.n_quads + kPlanThreads - 1) / kPlanThreads;
+    const dim3 grid(rank_blocks + quad_blocks + (n1 + kPlanThreads - 1) / kPlanThreads);
+    if (n_args > 0) {
       UploadChunk c;
       for (int i = 0; i < n_args; ++i) c.v[i] = host_ints[i];
       for (int i = n_args; i < kUploadInts; ++i) c.v[i] = 0;
-      k_plan_build_args<<<grid, dim3(256), 0, s>>>(plan_dev, h, c, n_args, tile_blocks, quad_blocks);
+      k_plan_args<<<grid, dim3(kPlanThreads), 0, s>>>(plan_dev, h, c, n_args, rank_blocks, quad_blocks, causal_short);
     } else {
-      k_plan_build<<<grid, dim3(256), 0, s>>>(plan_dev, h, tile_blocks, quad_blocks);
+      k_plan_uploaded<<<grid, dim3(kPlanThreads), 0, s>>>(plan_dev, h, h.off_short, rank_blocks, quad_blocks, causal_short);
     }
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  } else {
+    const int tile_blocks = (h.n_q_tiles + 255) / 256, quad_blocks = (h.n_quads + 63) / 64;
+    k_plan_build<<<dim3(tile_blocks + quad_blocks + (n1 + 255) / 256), dim3(256), 0, s>>>(plan_dev, h, tile_blocks,
+                                                                                         quad_blocks, causal_short);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     constexpr int kPerBlock = 4 * kSortTiles;
