@@ -34,7 +34,7 @@ static inline int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * 
 
 void plan_layout(int batch, int64_t total_tokens, int64_t total_segments, int64_t n_q_tiles,
                  int64_t padded_keys, int64_t n_short_rows, int layout, int64_t n_seg_tiles,
-                 int64_t n_quads, PlanHeader* h) {
+                 int64_t n_quads, int64_t n_seg_units, PlanHeader* h) {
   std::memset(h, 0, sizeof(*h));
   h->magic = kPlanMagic;
   h->batch = batch;
@@ -48,6 +48,7 @@ void plan_layout(int batch, int64_t total_tokens, int64_t total_segments, int64_
   h->layout = layout;
   h->n_seg_tiles = (int32_t)n_seg_tiles;
   h->n_quads = (int32_t)n_quads;
+  h->n_seg_units = (int32_t)n_seg_units;
   int64_t o = sizeof(PlanHeader) / 4;
   auto take = [&](int64_t n) { int64_t r = o; o = align_up(o + n, 4); return (int32_t)r; };
   h->off_prompt = take(batch);
@@ -73,23 +74,14 @@ void plan_layout(int batch, int64_t total_tokens, int64_t total_segments, int64_
   h->off_map = layout == PV_LAYOUT_INTERLEAVED ? take(total_tokens) : 0;
   h->off_segwork = take(2 * n_seg_tiles * 8);
   h->off_quadwork = take(n_quads * 8);
+  h->off_segunit = take(n_seg_units * 12);
   h->total_ints = (int32_t)o;
 }
 
-// Pieces per work item of the segment-only call: enough to give every workgroup slot of the chip
-// (256 compute units x 2) an item, at most 8.
-static int segment_split(int64_t n_seg_tiles, int hkv) {
-  const int64_t items = n_seg_tiles * hkv;
-  if (items <= 0) return 1;
-  int64_t c = (512 + items - 1) / items;
-  return (int)(c < 1 ? 1 : (c > 8 ? 8 : c));
-}
-
-AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, int64_t n_seg_tiles,
+AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, int64_t n_seg_units,
                                     int hq, int hkv, int d, int in_dtype) {
   AttnWorkspace w;
   w.off_part = 0;
-  w.split = 1;
   int64_t o = 0;
   w.off_cs = o;
   o = align_up(o + total_tokens * (d / 2) * 8, 256);
@@ -98,10 +90,9 @@ AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, i
     o = align_up(o + (int64_t)hkv * padded_keys * d * 2, 256);
     w.off_vt = o;
     o = align_up(o + (int64_t)hkv * padded_keys * d * 2, 256);
-    w.split = segment_split(n_seg_tiles, hkv);
     w.off_part = o;
     w.total_full = o;
-    if (w.split > 1) o = align_up(o + n_seg_tiles * hq * w.split * 32 * (d + 2) * 4, 256);
+    o = align_up(o + n_seg_units * hq * 32 * (d + 2) * 4, 256);
   } else {
     o = align_up(o + total_tokens * hkv * d * 4, 256);
     w.off_vt = o;
@@ -187,7 +178,8 @@ static void fill_sizes(const pv_problem* p, const Totals& t, int hq, int hkv, in
   s->padded_keys = t.padded_keys;
   PlanHeader h;
   plan_layout(p->batch, t.tokens, t.segments, t.q_tiles, t.padded_keys, t.short_rows, p->layout,
-              t.seg_tiles, group_uses_query_tiles(hq / hkv) ? t.quads : 0, &h);
+              t.seg_tiles, group_uses_query_tiles(hq / hkv) ? t.quads : 0,
+              seg_unit_places(t.seg_tiles, t.tokens, p->batch, hq, hkv), &h);
   s->n_seg_tiles = (int32_t)t.seg_tiles;
   s->n_quads = h.n_quads;
   s->n_short_rows = (int32_t)t.short_rows;
@@ -196,7 +188,7 @@ static void fill_sizes(const pv_problem* p, const Totals& t, int hq, int hkv, in
   s->plan_bytes = (int64_t)h.total_ints * 4;
   s->dense_mask_bytes = t.mask_bytes;
   s->attn_workspace_bytes =
-      attn_workspace_layout(t.tokens, t.padded_keys, t.seg_tiles, hq, hkv, d, in_dtype).total;
+      attn_workspace_layout(t.tokens, t.padded_keys, h.n_seg_units, hq, hkv, d, in_dtype).total;
   s->n_q_heads = hq;
   s->n_kv_heads = hkv;
   s->head_dim = d;
@@ -222,7 +214,8 @@ static pv_status check_sizes(const pv_sizes* s, PlanHeader* h) {
     return PV_ERR_SHAPE;
   if (s->layout != PV_LAYOUT_APPENDED && s->layout != PV_LAYOUT_INTERLEAVED) return PV_ERR_SHAPE;
   plan_layout((int)s->batch, s->total_tokens, s->total_segments, s->n_q_tiles, s->padded_keys,
-              s->n_short_rows, s->layout, s->n_seg_tiles, s->n_quads, h);
+              s->n_short_rows, s->layout, s->n_seg_tiles, s->n_quads,
+              seg_unit_places(s->n_seg_tiles, s->total_tokens, s->batch, s->n_q_heads, s->n_kv_heads), h);
   if (s->plan_bytes != (int64_t)h->total_ints * 4) return PV_ERR_SHAPE;
   return PV_OK;
 }
@@ -402,7 +395,7 @@ static pv_status attention_call(const pv_sizes* sizes, const void* plan_dev, con
   const int hq = sizes->n_q_heads, hkv = sizes->n_kv_heads, d = sizes->head_dim;
   const AttnWorkspace wl =
       attn_workspace_layout(own_stride ? key_capacity : sizes->total_tokens, key_capacity,
-                            sizes->n_seg_tiles, hq, hkv, d, sizes->in_dtype);
+                            h.n_seg_units, hq, hkv, d, sizes->in_dtype);
   h.padded_keys = (int32_t)key_capacity;          // the kernels take the head stride from their copy of the header
   // a caller's workspace must have the size pv_query_sizes reports (which also covers the
   // segment-only call); the library's own fixed array only has to hold what the whole pass uses
@@ -517,7 +510,7 @@ pv_status pv_static_workspace_needed(const pv_sizes* sizes, int64_t* bytes_out) 
   PlanHeader h;
   pv_status st = check_sizes(sizes, &h);
   if (st != PV_OK) return st;
-  *bytes_out = attn_workspace_layout(sizes->total_tokens, sizes->padded_keys, sizes->n_seg_tiles,
+  *bytes_out = attn_workspace_layout(sizes->total_tokens, sizes->padded_keys, h.n_seg_units,
                                      sizes->n_q_heads, sizes->n_kv_heads, sizes->head_dim,
                                      sizes->in_dtype).total_full;
   return PV_OK;
@@ -548,7 +541,7 @@ pv_status pv_masked_attention_fp8kv(const pv_sizes* sizes, const void* plan_dev,
   if (!(rope_theta >= 0.0f) || !std::isfinite(rope_theta)) return PV_ERR_SHAPE;
   const int hq = sizes->n_q_heads, hkv = sizes->n_kv_heads, d = sizes->head_dim;
   const AttnWorkspace wl = attn_workspace_layout(sizes->total_tokens, sizes->padded_keys,
-                                                 sizes->n_seg_tiles, hq, hkv, d, PV_BF16);
+                                                 h.n_seg_units, hq, hkv, d, PV_BF16);
   if (workspace_bytes < wl.total) return PV_ERR_WORKSPACE;
   if (misaligned(plan_dev) || misaligned(q) || misaligned(k_fp8) || misaligned(v_fp8) || misaligned(out) ||
       misaligned(workspace) || ((uintptr_t)lse & 3u) || ((uintptr_t)k_scale_dev & 3u) ||
@@ -603,7 +596,7 @@ pv_status pv_prepared_workspace_bytes(const pv_sizes* sizes, int64_t key_capacit
   if (key_capacity < sizes->padded_keys || key_capacity % kTileN != 0 || key_capacity > (1ll << 27))
     return PV_ERR_SHAPE;
   *bytes_out = attn_workspace_layout(own_stride ? key_capacity : sizes->total_tokens, key_capacity,
-                                     sizes->n_seg_tiles, sizes->n_q_heads, sizes->n_kv_heads,
+                                     h.n_seg_units, sizes->n_q_heads, sizes->n_kv_heads,
                                      sizes->head_dim, sizes->in_dtype).total;
   return PV_OK;
 }

@@ -11,8 +11,8 @@
 //   k_attn_bf16        flash-style fused Q K^T / online softmax / P V.  One workgroup = one query
 //                      tile (32 tokens) x one kv head; wave w owns query head kvh*G + w, so the
 //                      G query heads of a GQA group share every K/V tile staged in LDS.
-// The segment-only call launches the same kernel over the tiles that hold segment rows, each cut
-// along the keys into pieces, and then
+// The segment-only call launches the same kernel over the tiles that hold segment rows, cut along the
+// keys into pieces where the tiles alone leave workgroup slots empty, and then
 //   k_merge_pieces     combines the pieces' unnormalised results.
 //
 // The product S^T = K Q^T is formed (keys x queries) so that a lane owns one query column:
@@ -182,78 +182,68 @@ __global__ __launch_bounds__(256) void k_prep_kv(const int32_t* __restrict__ pla
   }
 }
 
-// Merge of the key pieces of the segment-only call.  One workgroup per (tile holding segment rows,
-// query head); 8 threads per row, each D/8 features.  Piece c holds, relative to its own reference
+// Merge of the key pieces of the segment-only call.  Piece c holds, relative to its own reference
 // mref_c = -nmref_c (log2 units), the unnormalised O_c and the row sum l_c; with M = max mref_c over
 // the pieces that saw a key, O = sum_c 2^(mref_c - M) O_c / sum_c 2^(mref_c - M) l_c.
+// One workgroup per (piece, query head), for that piece's share of the tile's rows: as many workgroups as the pieces
+// had, in the order of heads that they had, and all loads of a thread (4 features of one row in every piece) in one
+// round trip: bound by latency and by the partial results, 16.6 KB a wave.
 template <int D>
 __global__ __launch_bounds__(256) void k_merge_pieces(const int32_t* __restrict__ plan, PlanHeader h,
-                                                      const float* __restrict__ part, int split,
+                                                      const float* __restrict__ part,
                                                       void* __restrict__ out, float* __restrict__ lse,
                                                       int hq, int hkv, bool out_f32) {
-  constexpr int MAXSPLIT = 8, FPT = D / 8;           // features per thread
-  const int G = hq / hkv;
-  const int item = (int)blockIdx.x / G, hl = (int)blockIdx.x % G;     // (tile, kv head), head of group
-  const int kvh = item % hkv, head = kvh * G + hl;
-  const QTile tile = reinterpret_cast<const QTile*>(plan + h.off_segwork)[item / hkv];
-  const int row = threadIdx.x >> 3, sub = threadIdx.x & 7;
-  if (row >= tile.rows) return;
-  const int64_t g = (int64_t)tile.tok_base + tile.t0 + row;
-  const int a_end = plan[h.off_aend + g], b_start = plan[h.off_bstart + g];
-  const int i_loc = tile.t0 + row;
-  // segment rows only; rows with few keys come from the preparation kernel
-  if (b_start == 0 || a_end + i_loc - b_start + 1 <= PV_SHORT_ROW_KEYS) return;
-  float mref[MAXSPLIT], lsum[MAXSPLIT];
-  float M = -INFINITY;
+  constexpr int TPR = D / 4, RPP = 256 / TPR;        // threads per row, rows per pass
+  const int G = hq / hkv, kvh = (int)blockIdx.x % hkv, hl = (int)blockIdx.x / hkv % G, head = kvh * G + hl;
+  const int u = (int)blockIdx.x / hq;
+  const SegUnit unit = reinterpret_cast<const SegUnit*>(plan + h.off_segunit)[u];
+  const int pieces = unit.pieces;
+  if (unit.n_kt == 0 || pieces == 1) return;
+  const int row_end = min(32 * (unit.piece + 1) / pieces, unit.tile.rows), sub = threadIdx.x % TPR;
+  const float* part0 = part + ((int64_t)((u - unit.piece) * hkv + kvh) * G + hl) * (32 * (D + 2));   // the first piece's
+  const int64_t stride = (int64_t)hkv * G * (32 * (D + 2));
+  for (int row = 32 * unit.piece / pieces + (int)threadIdx.x / TPR; row < row_end; row += RPP) {
+    const int64_t g = (int64_t)unit.tile.tok_base + unit.tile.t0 + row;
+    const int a_end = plan[h.off_aend + g], b_start = plan[h.off_bstart + g];
+    const int64_t to = caller_row(plan, h, g);
+    float2 ml[kMaxPieces];
+    float4 x[kMaxPieces];
 #pragma unroll
-  for (int c = 0; c < MAXSPLIT; ++c) {
-    mref[c] = 0.0f; lsum[c] = 0.0f;
-    if (c < split) {
-      const float* p = part + ((int64_t)((int64_t)item * split + c) * G + hl) * (32 * (D + 2));
-      const float2 ml = reinterpret_cast<const float2*>(p + 32 * D)[row];
-      mref[c] = -ml.x; lsum[c] = ml.y;
-      if (ml.y != 0.0f) M = fmaxf(M, mref[c]);
-    }
-  }
-  float acc[FPT];
-#pragma unroll
-  for (int e = 0; e < FPT; ++e) acc[e] = 0.0f;
-  float L = 0.0f;
-#pragma unroll
-  for (int c = 0; c < MAXSPLIT; ++c) {
-    if (c < split && lsum[c] != 0.0f) {              // a piece without a visible key holds nothing; a NaN is kept
-      const float w = exp2f(mref[c] - M);
-      L = fmaf(w, lsum[c], L);
-      const float* p = part + ((int64_t)((int64_t)item * split + c) * G + hl) * (32 * (D + 2)) +
-                       row * D + sub * FPT;
-#pragma unroll
-      for (int e = 0; e < FPT; e += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(p + e);
-        acc[e] = fmaf(w, x.x, acc[e]); acc[e + 1] = fmaf(w, x.y, acc[e + 1]);
-        acc[e + 2] = fmaf(w, x.z, acc[e + 2]); acc[e + 3] = fmaf(w, x.w, acc[e + 3]);
+    for (int c = 0; c < kMaxPieces; ++c) {
+      if (c < pieces) {
+        ml[c] = reinterpret_cast<const float2*>(part0 + c * stride + 32 * D)[row];
+        x[c] = reinterpret_cast<const float4*>(part0 + c * stride + row * D)[sub];
       }
     }
-  }
-  const float inv = 1.0f / L;
-  const int64_t orow = (caller_row(plan, h, g) * hq + head) * D + sub * FPT;
-  if (out_f32) {
-    float* op = reinterpret_cast<float*>(out) + orow;
+    // segment rows only; rows with few keys come from the preparation kernel
+    if (b_start == 0 || a_end + unit.tile.t0 + row - b_start + 1 <= PV_SHORT_ROW_KEYS) continue;
+    float M = -INFINITY, L = 0.0f;
+    float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-    for (int e = 0; e < FPT; e += 4)
-      *reinterpret_cast<float4*>(op + e) =
-          make_float4(acc[e] * inv, acc[e + 1] * inv, acc[e + 2] * inv, acc[e + 3] * inv);
-  } else {
-    uint16_t* op = reinterpret_cast<uint16_t*>(out) + orow;
+    for (int c = 0; c < kMaxPieces; ++c)
+      if (c < pieces && ml[c].y != 0.0f) M = fmaxf(M, -ml[c].x);
 #pragma unroll
-    for (int e = 0; e < FPT; e += 4) {
-      uint2 w;
-      w.x = pack_bf16(acc[e] * inv, acc[e + 1] * inv);
-      w.y = pack_bf16(acc[e + 2] * inv, acc[e + 3] * inv);
-      *reinterpret_cast<uint2*>(op + e) = w;
+    for (int c = 0; c < kMaxPieces; ++c) {
+      if (c < pieces && ml[c].y != 0.0f) {             // a piece without a visible key holds nothing; a NaN is kept
+        const float w = exp2f(-ml[c].x - M);
+        L = fmaf(w, ml[c].y, L);
+        acc.x = fmaf(w, x[c].x, acc.x); acc.y = fmaf(w, x[c].y, acc.y);
+        acc.z = fmaf(w, x[c].z, acc.z); acc.w = fmaf(w, x[c].w, acc.w);
+      }
     }
+    const float inv = 1.0f / L;
+    const int64_t o = (to * hq + head) * D + sub * 4;
+    if (out_f32) {
+      *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + o) =
+          make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+    } else {
+      uint2 w;
+      w.x = pack_bf16(acc.x * inv, acc.y * inv);
+      w.y = pack_bf16(acc.z * inv, acc.w * inv);
+      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + o) = w;
+    }
+    if (lse && sub == 0) lse[(int64_t)head * h.total_tokens + to] = (log2f(L) + M) * 0.6931471805599453f;
   }
-  if (lse && sub == 0)
-    lse[(int64_t)head * h.total_tokens + caller_row(plan, h, g)] = (log2f(L) + M) * 0.6931471805599453f;
 }
 
 // The main kernel's launchers: defined in pv_attn_bf16_main.h, instantiated in the translation units
@@ -352,7 +342,7 @@ hipError_t launch_main_bf16(const int32_t* plan_dev, const PlanHeader& h, const 
   const bool out_f32 = out_dtype == PV_F32;
   hipError_t e;
   const float qscale = scale * 1.4426950408889634f;
-  const int split = segments_only ? wl.split : 0;
+  const int split = !segments_only ? 0 : h.n_seg_units > 0 ? 2 : 1;      // (2: the plan's key pieces)
   KvSource raw_kv = {nullptr, nullptr, nullptr, 1};
   int64_t n_short = 0;
   if (short_rows_kv) {
@@ -368,11 +358,11 @@ hipError_t launch_main_bf16(const int32_t* plan_dev, const PlanHeader& h, const 
   else e = dispatch_g<128>(hq / hkv, plan_dev, h, kq, krot, vt, cs, out, lse, hq, hkv, qscale, rope, out_f32, split, part, raw_kv, scale, (int)n_short, s);
   if (e != hipSuccess) return e;
   if (ev1) { e = hipEventRecord(ev1, s); if (e != hipSuccess) return e; }
-  if (split > 1) {
+  if (split == 2) {
     dim3 grid;
-    if (!grid_1d((int64_t)h.n_seg_tiles * hq, 256, &grid)) return hipErrorInvalidConfiguration;
-    if (d == 64) k_merge_pieces<64><<<grid, dim3(256), 0, s>>>(plan_dev, h, part, split, out, lse, hq, hkv, out_f32);
-    else k_merge_pieces<128><<<grid, dim3(256), 0, s>>>(plan_dev, h, part, split, out, lse, hq, hkv, out_f32);
+    if (!grid_1d((int64_t)h.n_seg_units * hq, 256, &grid)) return hipErrorInvalidConfiguration;
+    if (d == 64) k_merge_pieces<64><<<grid, dim3(256), 0, s>>>(plan_dev, h, part, out, lse, hq, hkv, out_f32);
+    else k_merge_pieces<128><<<grid, dim3(256), 0, s>>>(plan_dev, h, part, out, lse, hq, hkv, out_f32);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -56,10 +56,11 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   }
 
   // split == 0: the whole pass, one workgroup per entry of the work list and kv head.
-  // split >= 1: segment rows only, one workgroup per (tile holding segment rows, kv head, piece);
-  //             piece c of `split` covers the c-th share of the tile's listed key tiles.
-  const int piece = split ? (int)blockIdx.x % split : 0;
-  const int item = split ? (int)blockIdx.x / split : (int)blockIdx.x;   // (tile, kv head)
+  // split == 1: segment rows only, one workgroup per (tile holding segment rows, kv head).
+  // split == 2: the same, one workgroup per (key piece of such a tile, kv head): the plan's list of pieces.
+  // The kv head runs fastest in all three, so that a head's keys go through the L2 of the same XCDs (segment rows of
+  // one request, us, pieces of a tile next to each other / heads next to each other: 54.2 / 52.4).
+  const int item = (int)blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63;
   // The wave index as a scalar, for everything that lives through the loops: in a vector register the head and the
   // address of the partial result took three of them, and with eight and with three waves the mask's row descriptors
@@ -68,6 +69,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   const int qrow = lane & 31, hh = lane >> 5;
   int kvh, head;
   QTile tile, mine;
+  int kt0 = 0, n_tiles = -1;                  // first listed key tile, number of them (-1: all)
   if constexpr (QT) {
     static_assert(G == 4, "query-tile workgroups have four waves");
     head = (int)blockIdx.x % hq;
@@ -82,8 +84,16 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   } else {
     kvh = item % hkv;
     head = kvh * G + wave_s;
-    tile = reinterpret_cast<const QTile*>(
-        plan + (split ? h.off_segwork : h.off_work))[dispatch_rank(item / hkv, h.n_q_tiles, order)];
+    if (split == 2) {
+      const SegUnit unit = reinterpret_cast<const SegUnit*>(plan + h.off_segunit)[item / hkv];
+      if (unit.n_kt == 0) return;             // a place that the plan did not need
+      tile = unit.tile;
+      kt0 = unit.kt0;
+      n_tiles = unit.n_kt;
+    } else {
+      tile = reinterpret_cast<const QTile*>(
+          plan + (split ? h.off_segwork : h.off_work))[dispatch_rank(item / hkv, h.n_q_tiles, order)];
+    }
     mine = tile;
   }
   const bool valid = qrow < mine.rows;
@@ -95,17 +105,9 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
 
   // ---- key steps.  A key tile of the plan (64 keys) is two steps of 32 keys; tiles run over
   // [0, n_a) then [jb0, jb1).  The number of steps is even.
-  const int n_listed = tile.n_a + (tile.jb1 - tile.jb0);
-  const int kt0 = split ? piece * n_listed / split : 0;                 // first listed key tile
-  const int n_tiles = (split ? (piece + 1) * n_listed / split : n_listed) - kt0;
+  if (n_tiles < 0) n_tiles = tile.n_a + (tile.jb1 - tile.jb0);
   const int n_steps = 2 * n_tiles;
   const int last = n_steps - 1;
-  // partial result of this wave (split > 1): float [32][D], then float2 [32] = (nmref, row sum)
-  float* part_o = part + ((int64_t)((int64_t)item * split + piece) * G + wave_s) * (32 * (D + 2));
-  if (n_steps == 0) {                       // fewer key tiles than pieces: this piece is empty
-    if (hh == 0) reinterpret_cast<float2*>(part_o + 32 * D)[qrow] = make_float2(0.0f, 0.0f);
-    return;
-  }
   const int64_t head_base = ((int64_t)kvh * h.padded_keys + tile.kpad_base) * D;   // elements
   auto step_key0 = [&](int j) {           // first key (request-local) of step j
     const int idx = (j >> 1) + kt0;
@@ -229,6 +231,11 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
 #pragma unroll
     for (int t = 0; t < KT; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[t], acc, 0, 0, 0);
   };
+  // Lanes that have had no visible key so far.  Their sum of 0 is right, and the window test below leaves them out: the
+  // rows of a tile with an early boundary see nothing of a later piece of its keys, and re-centred for their sake every
+  // step of it cost twice its time (segment rows at 32/8 heads, us, with / without
+  // it: 2 x 2.8 K tokens 82.6 / 67.0, 9 K tokens 85.0 / 77.4).
+  unsigned long long unseen = ~0ull;
   // The 16 scores of a lane are keys key0 + 4 hh + c, c = 8 (r / 4) + r % 4, of one query row: the row's
   // visible keys among the step's 32 become a bit mask (three clamped "low n bits" masks), and every
   // score is kept or replaced by -inf with a bit-field extract and a bit-field insert.
@@ -242,6 +249,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     };
     const int i_loc = own_row();
     const unsigned vis = low_bits(a_end - base) | (low_bits(i_loc - base + 1) & ~low_bits(b_start - base));
+    unseen &= __builtin_amdgcn_ballot_w64((vis & 0x0f0f0f0fu) == 0u);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const unsigned keep = (unsigned)__builtin_amdgcn_sbfe((int)vis, 8 * (r / 4) + (r % 4), 1);   // all ones or zero
@@ -294,8 +302,11 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   // exactly, and with 2^16 the normaliser there is 5.3e-4 from fp64 instead of 7.1e-4.)  The lower bound is on the
   // total, not on the step: a step whose keys are all masked for a lane, every step of a diagonal tile for some
   // lane, or whose scores lie 40 octaves below a healthy history adds nothing, and nothing needs correcting.
-  auto out_of_window = [&](float rs) {
-    return __builtin_amdgcn_ballot_w64(!(l_run + rs >= 0x1p-40f && rs <= 0x1p16f)) != 0;
+  // Failing lanes whose row has seen nothing yet are sorted out behind the branch: beside the test, where every step
+  // would pay for two scalar instructions between the compare and its branch, 0.8 % of a long pass (1358 / 1369 us).
+  auto failing = [&](float rs) { return __builtin_amdgcn_ballot_w64(!(l_run + rs >= 0x1p-40f && rs <= 0x1p16f)); };
+  auto out_of_window = [&](float rs) __attribute__((always_inline)) {
+    return __builtin_expect(failing(rs) != 0, 0) && (failing(rs) & ~unseen) != 0;
   };
   // One exact online-softmax step for the whole wave: taken when the window test fails (it also
   // catches inf/NaN, also a NaN that came over from the query sharing the column, and a running sum still at 0);
@@ -492,6 +503,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   __builtin_amdgcn_sched_barrier(0);
   load_k(min(1, last) % NS);
   if (step_key0(0) >= mine.n_full * 64) apply_mask(sA, step_key0(0));
+  else unseen = 0;
   {   // the reference starts at the maximum of the row's first step: that weight is then exact in bf16, and few
       // rows leave the window later (started at 0 instead: 4 x 10 K tokens at 64/8 heads 8700 us, now 8350)
     float mx = sA[0];
@@ -759,7 +771,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     asm volatile("" : "+v"(rs));                      // the row sum belongs to this block
     __builtin_amdgcn_sched_barrier(0);
     if (have1) {
-      if (__builtin_expect(out_of_window(rs), 0)) rs = recentre(s_in, p_out, s_out);
+      if (out_of_window(rs)) rs = recentre(s_in, p_out, s_out);
       l_run += rs;
     }
     if constexpr (!ST) {     // (a whole period leaves them as they are)
@@ -806,7 +818,11 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
   const float l_tot = kSumByProducts ? l_run : pair_sum(l_run);
   __syncthreads();                                    // every wave is done with the stages
   {
-    const bool partial = split > 1;                   // this piece's result goes to the workspace
+    // the result of one of several pieces goes to the workspace (looked up here: nothing of it lives through the loops):
+    // float [32][D] of this wave, then float2 [32] = (nmref, row sum)
+    bool partial = false;
+    if (split == 2) partial = reinterpret_cast<const SegUnit*>(plan + h.off_segunit)[item / hkv].pieces > 1;
+    float* part_o = part + ((int64_t)item * G + wave_s) * (32 * (D + 2));
     const float inv = partial ? 1.0f : 1.0f / l_tot;
     const int64_t tok0 = (int64_t)mine.tok_base + mine.t0;
     // rows with few visible keys are produced in fp32 by the preparation kernel: not stored here
@@ -880,7 +896,7 @@ hipError_t launch_main(const int32_t* plan, const PlanHeader& h, const uint16_t*
                               int split, float* part, const KvSource& raw_kv, float scale, int n_short,
                               hipStream_t s) {
   dim3 grid;
-  const int64_t blocks = (split ? (int64_t)h.n_seg_tiles * hkv * split : (int64_t)h.n_q_tiles * hkv) + n_short;
+  const int64_t blocks = (int64_t)(split == 2 ? h.n_seg_units : split ? h.n_seg_tiles : h.n_q_tiles) * hkv + n_short;
   if (!grid_1d(blocks, G * 64, &grid)) return hipErrorInvalidConfiguration;
   const int order = split ? 0 : dispatch_order(h.n_q_tiles, hkv, G);
   if (rope)

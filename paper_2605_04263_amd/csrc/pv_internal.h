@@ -42,8 +42,11 @@ struct PlanHeader {
   int32_t n_quads;                                       // groups of four consecutive query tiles of a request
   int32_t off_quad_start;                                // [B+1] first such group of a request
   int32_t off_quadwork;                                  // [n_quads][8], per request last group first
+  int32_t n_seg_units;                                   // places for key pieces of those tiles (seg_unit_places), 0: not cut
+  int32_t off_segunit;                                   // [n_seg_units][12]: SegUnit, used places first
+  int32_t reserved[2];
 };
-static_assert(sizeof(PlanHeader) == 36 * 4, "PlanHeader must be 36 ints");
+static_assert(sizeof(PlanHeader) == 40 * 4, "PlanHeader must be 40 ints (a multiple of 4)");
 
 // One-dimensional grid of `blocks` workgroups of `threads` threads.  A launch may not span 2^32
 // threads or more: a grid that large is reported as an error and never truncated.
@@ -81,6 +84,28 @@ struct QTile {
   int32_t kpad_base;   // first padded key row of the request in the rotated-K / V^T workspace
 };
 
+// One key piece of a tile that holds segment rows, a work item (per kv head) of the segment-only call (12 ints).
+struct SegUnit {
+  QTile tile;
+  int32_t kt0, n_kt;     // its key tiles: n_kt from the kt0-th of the tile's listed ones; n_kt = 0: place not used
+  int32_t piece, pieces; // which piece of the tile, of how many (in neighbouring places); 1: the whole tile
+};
+constexpr int kMaxPieces = 8;
+
+// Places for key pieces: one for each workgroup slot of the chip that a kv head has (two workgroups of up to four
+// waves to a compute unit, one of more), at most kMaxPieces to a tile; 0: the tiles are not cut.  Cutting pays where the
+// longest item gets shorter by more than the merge launch takes (16 us asked for, 1.24 us a key tile of an item alone on
+// its unit, 1.5 beside another).  Passes with segment rows, us, uncut / cut: 32/8 heads of 128, 2.8 K tokens, 26 tiles for
+// 64 slots 75 / 67; 39 tiles 77 / 82; 52 tiles 88 / 98; 3 K tokens at 64/8 heads, 17 tiles for 32 slots 66 / 61; at 40/8
+// heads 64 / 55; 16/8 heads of 64, 41 tiles for 64 slots, 5.8 K tokens 77 / 59; 528 tokens, 5 tiles 26 / 28.
+inline int64_t seg_unit_places(int64_t n_seg_tiles, int64_t total_tokens, int64_t batch, int hq, int hkv) {
+  const int64_t slots = (hq / hkv <= 4 ? 512 : 256) / hkv;
+  const int64_t key_tiles = total_tokens / (batch * kTileN);          // of an average request
+  if (n_seg_tiles <= 0 || n_seg_tiles >= slots) return 0;
+  if (key_tiles * (124 * slots - 150 * n_seg_tiles) <= 1600 * slots) return 0;
+  return n_seg_tiles * kMaxPieces < slots ? n_seg_tiles * kMaxPieces : slots;
+}
+
 struct RopeFreq { double inv_freq[64]; };   // theta^(-2c/D), c < D/2 <= 64
 
 // Workspace of the attention call (byte offsets), derived from pv_sizes.
@@ -89,12 +114,11 @@ struct AttnWorkspace {
   int64_t off_krot;    // bf16 path: [Hkv][padded_keys][D] bf16; fp32 path: [total_tokens][Hkv][D] float
   int64_t off_vt;      // bf16 path: V^T slabs, [Hkv][padded_keys/16][2][D][8] bf16
   int64_t off_part;    // bf16 path, segment-only call: partial results of the key pieces, per
-                       // (segment tile, kv head, piece, head of the group): float [32][D] then float2 [32]
-  int split;           // pieces per work item of the segment-only call (1: no partial results)
+                       // (place, kv head, head of the group): float [32][D] then float2 [32]
   int64_t total_full;  // bytes the whole-pass call uses (everything before the partial results)
   int64_t total;
 };
-AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, int64_t n_seg_tiles,
+AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, int64_t n_seg_units,
                                     int hq, int hkv, int d, int in_dtype);
 
 // --- launchers (each returns the hipError_t of its launches) ---
@@ -146,7 +170,7 @@ hipError_t launch_attn_fp8(const int32_t* plan_dev, const PlanHeader& h, const v
 // Host-side layout of the plan; shared by pv_query_sizes and pv_build_mask.
 void plan_layout(int batch, int64_t total_tokens, int64_t total_segments, int64_t n_q_tiles,
                  int64_t padded_keys, int64_t n_short_rows, int layout, int64_t n_seg_tiles,
-                 int64_t n_quads, PlanHeader* h);
+                 int64_t n_quads, int64_t n_seg_units, PlanHeader* h);
 
 }  // namespace pv
 #endif

@@ -125,11 +125,10 @@ __device__ inline void plan_token(int32_t* plan, const int32_t* img, const PlanH
   }
 }
 
-// Query tile t: the union of its rows' visible key sets, in key-tile units.  *seg_slot is the
+// Query tile t (of request b): the union of its rows' visible key sets, in key-tile units.  *seg_slot is the
 // tile's place in the list of tiles that hold segment rows (request after request), -1 if it
 // holds none.
-__device__ inline QTile plan_tile(const int32_t* plan, const PlanHeader& h, int t, int* seg_slot) {
-  const int b = find_owner(plan + h.off_qtile_start, h.batch, t);
+__device__ inline QTile plan_tile_of(const int32_t* plan, const PlanHeader& h, int b, int t, int* seg_slot) {
   const Req r = load_req(plan, h, b);
   const int t0 = (t - plan[h.off_qtile_start + b]) * h.tile_m;
   const int rows = min(h.tile_m, r.N - t0);
@@ -172,6 +171,10 @@ __device__ inline QTile plan_tile(const int32_t* plan, const PlanHeader& h, int 
   return q;
 }
 
+__device__ inline QTile plan_tile(const int32_t* plan, const PlanHeader& h, int t, int* seg_slot) {
+  return plan_tile_of(plan, h, find_owner(plan + h.off_qtile_start, h.batch, t), t, seg_slot);
+}
+
 // Group qd of four consecutive query tiles of a request (the last group of a request may hold
 // fewer): the union of their key-tile lists, for the launch whose workgroups take four query tiles
 // of one head.  Every wave of such a workgroup masks with its own tile's descriptor, so key tiles
@@ -207,6 +210,100 @@ __device__ inline void plan_quad(int32_t* plan, const int32_t* img, const PlanHe
   reinterpret_cast<QTile*>(plan + h.off_quadwork)[q0 + (nq - 1 - ql)] = u;
 }
 
+// Inclusive sum over the lanes of a wave, and sum and maximum over all of them, in every lane (non-negative numbers):
+// shifts inside the rows of 16 lanes, then the rows' last lanes handed on.  A tenth of the time of exchanges through LDS,
+// of which a plan would have a dozen in its longest chain.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);     // row_shr 1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);    // row_bcast 15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);    // row_bcast 31 into rows 2 and 3
+  return x;
+}
+__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_scan(x), 63); }
+__device__ __forceinline__ int wave_max(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
+// The key pieces of the segment-only call, for a plan whose segment tiles alone would leave workgroup slots empty:
+// pieces of nearly equal length, the shortest length L (at least kMinPiece key tiles) whose pieces fit the places.
+// One workgroup of kPlanThreads; thread i has the i-th tile with segment rows, the waves try 64 lengths at a time.
+// (Every tile in the same number of pieces leaves long ones, and a number rounded up so that they fill the slots a second
+// round of workgroups.  Passes, us, before / with it: 64/8 heads, 3 K tokens 76.4 / 61.0; 28/4 heads 62.6 / 46.8; 40/8
+// heads 65.4 / 55.5; 32/8 heads 54.3 / 48.2, 9 K tokens 90.5 / 77.5.  Pieces of 2 to 9 key tiles at least: the same.)
+constexpr int kPlanThreads = 1024, kMinPiece = 4;
+__device__ inline void plan_seg_units(int32_t* plan, const int32_t* img, const PlanHeader& h) {
+  constexpr int W = kPlanThreads / 64, TRIES = 4 * W;  // lengths tried in a round, four a wave
+  static_assert(TRIES == 64, "a lane each");
+  __shared__ int cost_s[512], sum_s[TRIES];
+  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, n = h.n_seg_tiles, cap = h.n_seg_units;   // n < 512
+  QTile q = {};
+  int cost = 0;
+  if (tid < n) {
+    const int b = find_owner(img + h.off_segtile_start, h.batch, tid);
+    const int c = img[h.off_prompt + b] + img[h.off_draft + b];
+    int unused;
+    q = plan_tile_of(img, h, b, img[h.off_qtile_start + b] + c / h.tile_m + (tid - img[h.off_segtile_start + b]), &unused);
+    cost = q.n_a + (q.jb1 - q.jb0);
+  }
+  if (tid < 512) cost_s[tid] = cost;
+  __syncthreads();
+  // min(ceil(c / len), 8) by the reciprocal: (c - 1/2) / len is at least 1 / (2 len) from a whole number, and below 8
+  // the product's error is less for every len under 2^18 and c under len * 8
+  auto pieces_of = [](int c, float rcp) { return min((int)(((float)c - 0.5f) * rcp) + 1, kMaxPieces); };
+  int hi = 1;
+  for (int i = lane; i < n; i += 64) hi = max(hi, cost_s[i]);
+  hi = wave_max(hi);
+  int lo = min(kMinPiece, hi);                       // the answer is in [lo, hi]: pieces of length hi are the n tiles
+  while (lo < hi) {
+    const int step = (hi - lo + TRIES - 1) / TRIES;
+    int total[2] = {0, 0};                           // two sums of at most 8 * 512 in a number
+    float rcp[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) rcp[k] = __builtin_amdgcn_rcpf((float)min(lo + (4 * wave + k) * step, hi));
+    for (int i = lane; i < n; i += 64) {
+      const int c = cost_s[i];
+      total[0] += pieces_of(c, rcp[0]) + (pieces_of(c, rcp[1]) << 16);
+      total[1] += pieces_of(c, rcp[2]) + (pieces_of(c, rcp[3]) << 16);
+    }
+    const int sum0 = wave_sum(total[0]), sum1 = wave_sum(total[1]);
+    if (lane < 4) sum_s[4 * wave + lane] = ((lane & 2 ? sum1 : sum0) >> (16 * (lane & 1))) & 0xffff;
+    __syncthreads();
+    const int first = __popcll(__builtin_amdgcn_ballot_w64(sum_s[lane] > cap));   // the lengths that don't fit come first
+    __syncthreads();
+    const int lo0 = lo;
+    lo = first > 0 ? min(lo0 + (first - 1) * step + 1, hi) : lo0;
+    hi = first < TRIES ? min(lo0 + first * step, hi) : hi;
+  }
+  const int p = tid < n ? pieces_of(cost, __builtin_amdgcn_rcpf((float)lo)) : 0;
+  const int at = wave_scan(p);                       // inclusive sum over the threads
+  if (lane == 63) sum_s[wave] = at;
+  __syncthreads();
+  const int sum = lane < W ? sum_s[lane & (W - 1)] : 0;
+  const int used = wave_sum(sum), before = wave_sum(lane < wave ? sum : 0);
+  SegUnit* units = reinterpret_cast<SegUnit*>(plan + h.off_segunit);
+  SegUnit u;
+  u.tile = q;
+  u.pieces = p;
+  for (int c = 0; c < p; ++c) {
+    u.piece = c;
+    u.kt0 = c * cost / p;
+    u.n_kt = (c + 1) * cost / p - u.kt0;
+    units[before + at - p + c] = u;
+  }
+  for (int i = used + tid; i < cap; i += kPlanThreads) units[i].n_kt = 0;
+}
+// (a plan too large for plan_all)
+__global__ __launch_bounds__(kPlanThreads) void k_plan_units(int32_t* plan, PlanHeader h) { plan_seg_units(plan, plan, h); }
+
 // The whole plan in one launch.  The request data (in the kernel arguments, or uploaded before) are copied to LDS by
 // every workgroup, and no workgroup reads what another writes: a workgroup that ranks kRankTiles tiles, a wave each,
 // forms the costs of all tiles itself.  That is two tiles a thread at 1 766 tiles (a tile is a chain of LDS reads and
@@ -215,10 +312,15 @@ __device__ inline void plan_quad(int32_t* plan, const int32_t* img, const PlanHe
 // the end and whether it holds segment rows make one number.  Launches, us, in two or three kernels / with it: 16 ragged
 // requests of 55 K tokens 22.5 / 7.3 (16 lanes to a tile 9.8: too few compute units with work); one workgroup that
 // ranked all tiles / with it: 208 tiles 11.9 / 5.1, 96 tiles 5.6 / 5.0.
-constexpr int kPlanThreads = 1024, kRankTiles = kPlanThreads / 64, kPlanTiles = 4096, kPlanData = 4096;   // (tiles and ints of request data in LDS)
+constexpr int kRankTiles = kPlanThreads / 64, kPlanTiles = 4096, kPlanData = 4096;   // (tiles and ints of request data in LDS)
 __device__ inline void plan_all(int32_t* plan, const int32_t* img, unsigned* key_s, const PlanHeader& h, int rank_blocks,
                                 int quad_blocks, bool causal_short) {
-  const int blk = (int)blockIdx.x, tid = (int)threadIdx.x;
+  const int tid = (int)threadIdx.x;
+  int blk = (int)blockIdx.x;
+  if (h.n_seg_units > 0 && blk-- == 0) {             // the longest chain first
+    plan_seg_units(plan, img, h);
+    return;
+  }
   if (blk >= rank_blocks + quad_blocks) {
     plan_token(plan, img, h, (blk - rank_blocks - quad_blocks) * kPlanThreads + tid, causal_short);
     return;
@@ -256,11 +358,8 @@ __device__ inline void plan_all(int32_t* plan, const int32_t* img, unsigned* key
       seg_rank += before & ks[e];
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    rank += __shfl_xor(rank, off);
-    seg_rank += __shfl_xor(seg_rank, off);
-  }
+  rank = wave_sum(rank);
+  seg_rank = wave_sum(seg_rank);
   if (lane == 0) {
     const QTile mine = mine_s[tid >> 6];
     reinterpret_cast<QTile*>(plan + h.off_tiles)[t] = mine;
@@ -384,7 +483,7 @@ hipError_t launch_plan_kernels(int32_t* plan_dev, const PlanHeader& h, const int
   if (one_launch) {
     const int rank_blocks = (h.n_q_tiles + kRankTiles - 1) / kRankTiles;
     const int quad_blocks = (4 * h.n_quads + kPlanThreads - 1) / kPlanThreads;
-    const dim3 grid(rank_blocks + quad_blocks + (n1 + kPlanThreads - 1) / kPlanThreads);
+    const dim3 grid((h.n_seg_units > 0 ? 1 : 0) + rank_blocks + quad_blocks + (n1 + kPlanThreads - 1) / kPlanThreads);
     if (n_args > 0) {
       UploadChunk c;
       for (int i = 0; i < n_args; ++i) c.v[i] = host_ints[i];
@@ -406,6 +505,11 @@ hipError_t launch_plan_kernels(int32_t* plan_dev, const PlanHeader& h, const int
     k_plan_sort<<<dim3(sort_blocks + seg_blocks), dim3(256), 0, s>>>(plan_dev, h, sort_blocks);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (h.n_seg_units > 0) {
+      k_plan_units<<<dim3(1), dim3(kPlanThreads), 0, s>>>(plan_dev, h);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   }
   if (dense_mask) {
     dim3 grid;

@@ -1,0 +1,68 @@
+"""Segment rows over few tiles: the key pieces that the plan lists (they cover every tile's key list once, in pieces of
+nearly equal length, as many as there are places) and their merged result against the oracle, at the group sizes of both
+numbers of places, with odd rows per piece, pieces of which some rows see nothing, and the limits of the rule."""
+import numpy as np
+import pytest
+import torch
+
+import pv_workloads as wl
+from tests.test_gpu_segment_attention import check_segments
+
+pytestmark = pytest.mark.gpu
+pv = pytest.importorskip("paper_2605_04263_amd.binding")
+
+
+def places(tiles, tokens, batch, hq, hkv):
+    slots = (512 if hq // hkv <= 4 else 256) // hkv
+    if not 0 < tiles < slots or tokens // (64 * batch) * (124 * slots - 150 * tiles) <= 1600 * slots:
+        return 0
+    return min(8 * tiles, slots)
+
+
+PROBLEMS = {
+    "long_prompt": wl.Problem([3000], [40], [3], [17], [[0, 11, 40]]),
+    "early_and_late": wl.Problem([5], [3000], [4], [17], [[1, 3, 2990, 3000]]),     # rows that see nothing of most pieces
+    "no_prompt": wl.Problem([0], [2100], [3], [40], [[0, 1000, 2000]]),
+    "two_requests": wl.Problem([700, 64], [1500, 3100], [3, 2], [32, 33], [[100, 101, 1500], [7, 3100]]),
+    "many_tiles": wl.Problem([130], [2500], [33], [32], [[75 * (i + 1) for i in range(33)]]),
+}
+
+
+@pytest.mark.parametrize("name", list(PROBLEMS))
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (64, 8), (40, 8), (8, 8), (14, 2), (3, 3)])
+def test_units(name, hq, hkv):
+    pr = PROBLEMS[name]
+    ver = pv.Verifier(pr.prompt_len, pr.draft_len, pr.num_segments, pr.segment_len, pr.flat_boundaries(), hq, hkv, 128,
+                      torch.bfloat16)
+    ver.plan.fill_(-1)
+    ver.build_mask()
+    blob = ver.plan.view(torch.int32).cpu().numpy()
+    n, off, n_units, off_units = (int(blob[i]) for i in (30, 32, 36, 37))
+    assert n_units == places(n, pr.total_tokens, pr.batch, hq, hkv)
+    if n_units == 0:
+        return
+    units = blob[off_units:off_units + 12 * n_units].reshape(n_units, 12)
+    seg = {tuple(t): 0 for t in blob[off:off + 8 * n].reshape(n, 8).tolist()}
+    used = units[units[:, 9] > 0]
+    assert (units[:len(used), 9] > 0).all()
+    lengths = {}
+    for *tile, kt0, n_kt, piece, pieces in used.tolist():
+        assert kt0 == seg[tuple(tile)] and 0 <= piece < pieces <= 8
+        seg[tuple(tile)] += n_kt
+        lengths.setdefault(tuple(tile), []).append(n_kt)
+        assert piece == len(lengths[tuple(tile)]) - 1
+    cost = {t: t[4] + t[6] - t[5] for t in seg}
+    assert all(seg[t] == cost[t] and max(x) - min(x) <= 1 for t, x in lengths.items())
+    length = min(x for x in range(min(4, max(cost.values())), max(cost.values()) + 1)
+                 if sum(min(8, -(-c // x)) for c in cost.values()) <= n_units)
+    assert all(len(lengths[t]) == min(8, -(-cost[t] // length)) for t in seg)
+
+
+@pytest.mark.parametrize("hq,hkv,d,name", [(8, 2, 128, "long_prompt"), (8, 1, 128, "early_and_late"), (5, 1, 128, "no_prompt"),
+                                           (2, 2, 64, "early_and_late"), (7, 1, 64, "two_requests"), (3, 1, 128, "two_requests")])
+@pytest.mark.parametrize("theta", [0.0, 5e5])
+def test_parity(hq, hkv, d, name, theta):
+    pr = PROBLEMS[name]
+    w = wl.make_custom(pr, hq, hkv, d, dtype=torch.bfloat16, seed=3, rope_theta=theta)
+    assert places(5, pr.total_tokens, pr.batch, hq, hkv) > 0
+    check_segments(w)
