@@ -75,6 +75,7 @@ void plan_layout(int batch, int64_t total_tokens, int64_t total_segments, int64_
   h->off_segwork = take(2 * n_seg_tiles * 8);
   h->off_quadwork = take(n_quads * 8);
   h->off_segunit = take(n_seg_units * 12);
+  h->off_segtile = take(n_seg_tiles > 0 && n_seg_units == 0 ? padded_keys / kTileM * 8 : 0);
   h->total_ints = (int32_t)o;
 }
 

@@ -93,6 +93,10 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     } else {
       tile = reinterpret_cast<const QTile*>(
           plan + (split ? h.off_segwork : h.off_work))[dispatch_rank(item / hkv, h.n_q_tiles, order)];
+      if (split) {                            // the list gives the order, this the rows
+        tile = reinterpret_cast<const QTile*>(plan + h.off_segtile)[(tile.kpad_base + tile.t0) / kTileM];
+        if (tile.rows == 0) return;
+      }
     }
     mine = tile;
   }

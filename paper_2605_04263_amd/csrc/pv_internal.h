@@ -44,7 +44,9 @@ struct PlanHeader {
   int32_t off_quadwork;                                  // [n_quads][8], per request last group first
   int32_t n_seg_units;                                   // places for key pieces of those tiles (seg_unit_places), 0: not cut
   int32_t off_segunit;                                   // [n_seg_units][12]: SegUnit, used places first
-  int32_t reserved[2];
+  int32_t off_segtile;                                   // [padded_keys / tile_m][8], at (kpad_base + t0) / tile_m of a listed tile with segment
+                                                         // rows: what the segment-only call evaluates for it (n_seg_units = 0)
+  int32_t reserved;
 };
 static_assert(sizeof(PlanHeader) == 40 * 4, "PlanHeader must be 40 ints (a multiple of 4)");
 
@@ -92,15 +94,22 @@ struct SegUnit {
 };
 constexpr int kMaxPieces = 8;
 
-// Places for key pieces: one for each workgroup slot of the chip that a kv head has (two workgroups of up to four
-// waves to a compute unit, one of more), at most kMaxPieces to a tile; 0: the tiles are not cut.  Cutting pays where the
-// longest item gets shorter by more than the merge launch takes (16 us asked for, 1.24 us a key tile of an item alone on
-// its unit, 1.5 beside another).  Passes with segment rows, us, uncut / cut: 32/8 heads of 128, 2.8 K tokens, 26 tiles for
-// 64 slots 75 / 67; 39 tiles 77 / 82; 52 tiles 88 / 98; 3 K tokens at 64/8 heads, 17 tiles for 32 slots 66 / 61; at 40/8
-// heads 64 / 55; 16/8 heads of 64, 41 tiles for 64 slots, 5.8 K tokens 77 / 59; 528 tokens, 5 tiles 26 / 28.
+// Places for key pieces, at most kMaxPieces to a tile; 0: the tiles are not cut.  One for each workgroup slot of the chip
+// that a kv head has: two workgroups of up to four waves to a compute unit, one of more.  One as well for three or four
+// waves where that makes pieces of moderate length: two such workgroups slow each other down, and half the pieces are
+// half the partial results.  Passes with segment rows at 32/8 heads of 128, us, places for two workgroups / for one:
+// 3 K tokens 50.8 / 47.8 (judge pass), 46.4 / 44.1, 2.8 K 44.1 / 40.1, 9 K with 8 tiles 67.7 / 62.1; at 24/8 heads 45.8 /
+// 44.5, more tiles 57.5 / 61.3, longer pieces (6 K tokens, 17 tiles) 51.4 / 76.0; one and two waves 38.3 / 48.2.
+// Cutting pays where the longest item gets shorter by more than the merge launch takes (16 us asked for, 1.24 us a key
+// tile of an item alone on its unit, 1.5 beside another).  Uncut / cut, us: 32/8 heads, 2.8 K tokens, 26 tiles for 64
+// slots 75 / 67; 39 tiles 77 / 82; 52 tiles 88 / 98; 3 K tokens at 64/8 heads, 17 tiles for 32 slots 66 / 61; at 40/8
+// heads 64 / 55; 16/8 heads of 64, 41 tiles for 64 slots, 5.8 K tokens 74 / 57; 528 tokens, 5 tiles 26 / 28.
 inline int64_t seg_unit_places(int64_t n_seg_tiles, int64_t total_tokens, int64_t batch, int hq, int hkv) {
-  const int64_t slots = (hq / hkv <= 4 ? 512 : 256) / hkv;
+  const int G = hq / hkv;
   const int64_t key_tiles = total_tokens / (batch * kTileN);          // of an average request
+  const int64_t units = 256 / hkv;                                    // compute units of a head
+  const bool one = G > 4 || (G > 2 && 2 * n_seg_tiles <= units && key_tiles * n_seg_tiles <= 45 * units);
+  const int64_t slots = one ? units : 512 / hkv;
   if (n_seg_tiles <= 0 || n_seg_tiles >= slots) return 0;
   if (key_tiles * (124 * slots - 150 * n_seg_tiles) <= 1600 * slots) return 0;
   return n_seg_tiles * kMaxPieces < slots ? n_seg_tiles * kMaxPieces : slots;

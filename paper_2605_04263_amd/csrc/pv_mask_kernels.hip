@@ -125,12 +125,9 @@ __device__ inline void plan_token(int32_t* plan, const int32_t* img, const PlanH
   }
 }
 
-// Query tile t (of request b): the union of its rows' visible key sets, in key-tile units.  *seg_slot is the
-// tile's place in the list of tiles that hold segment rows (request after request), -1 if it
-// holds none.
-__device__ inline QTile plan_tile_of(const int32_t* plan, const PlanHeader& h, int b, int t, int* seg_slot) {
-  const Req r = load_req(plan, h, b);
-  const int t0 = (t - plan[h.off_qtile_start + b]) * h.tile_m;
+// The up to h.tile_m rows from local row t0 of request b on as a query tile: the union of their visible key sets, in
+// key-tile units.
+__device__ inline QTile tile_at(const int32_t* plan, const PlanHeader& h, int b, const Req& r, int t0) {
   const int rows = min(h.tile_m, r.N - t0);
   const int bn = h.tile_n;
   int min_prefix = 0x7fffffff;   // min over rows of the length of the fully visible key prefix
@@ -141,7 +138,6 @@ __device__ inline QTile plan_tile_of(const int32_t* plan, const PlanHeader& h, i
   // first row, both non-decreasing in k because the boundaries are sorted.  The extremes over the
   // tile therefore sit at the first and last row of each kind.
   const int c = r.P + r.T, last = t0 + rows - 1;
-  *seg_slot = last >= c ? plan[h.off_segtile_start + b] + (t0 - c / h.tile_m * h.tile_m) / h.tile_m : -1;
   if (t0 < c) {
     min_prefix = t0 + 1;
     max_low = min(last, c - 1) + 1;
@@ -171,8 +167,37 @@ __device__ inline QTile plan_tile_of(const int32_t* plan, const PlanHeader& h, i
   return q;
 }
 
+// Query tile t.  *seg_slot is its place in the list of tiles that hold segment rows (request after request), -1 if it
+// holds none.
 __device__ inline QTile plan_tile(const int32_t* plan, const PlanHeader& h, int t, int* seg_slot) {
-  return plan_tile_of(plan, h, find_owner(plan + h.off_qtile_start, h.batch, t), t, seg_slot);
+  const int b = find_owner(plan + h.off_qtile_start, h.batch, t);
+  const Req r = load_req(plan, h, b);
+  const int t0 = (t - plan[h.off_qtile_start + b]) * h.tile_m;
+  const QTile q = tile_at(plan, h, b, r, t0);
+  const int c = r.P + r.T;
+  *seg_slot = t0 + q.rows > c ? plan[h.off_segtile_start + b] + t0 / h.tile_m - c / h.tile_m : -1;
+  return q;
+}
+
+// What the segment-only call evaluates in the place of the slot-th tile with segment rows.  Where segments are whole
+// numbers of tiles long, the tiles are cut at the segments' first rows: a tile of two segments masks every key between
+// their boundaries (a step of masked keys takes 0.8 us, one in the open 0.6), and there is one more of them (rows = 0
+// in its place).  Segment rows of 32 tokens at 32/8 heads, us, as listed / cut anew: 16 ragged requests 390 / 361, 8 of
+// 2.8 K tokens 152 / 134, 3 of them 78 / 67, one of 9 K 77 / 67.
+__device__ inline QTile segment_tile(const int32_t* plan, const PlanHeader& h, int slot, int* listed_t0) {
+  const int b = find_owner(plan + h.off_segtile_start, h.batch, slot);
+  const Req r = load_req(plan, h, b);
+  const int c = r.P + r.T, i = slot - plan[h.off_segtile_start + b];
+  *listed_t0 = (c / h.tile_m + i) * h.tile_m;
+  const int t0 = r.S % h.tile_m == 0 ? c + i * h.tile_m : *listed_t0;
+  QTile q = tile_at(plan, h, b, r, min(t0, r.N - 1));
+  if (t0 >= r.N) q.rows = 0;
+  return q;
+}
+__device__ inline void plan_segment_tile(int32_t* plan, const int32_t* img, const PlanHeader& h, int slot) {
+  int listed_t0;
+  const QTile q = segment_tile(img, h, slot, &listed_t0);
+  reinterpret_cast<QTile*>(plan + h.off_segtile)[(q.kpad_base + listed_t0) / h.tile_m] = q;
 }
 
 // Group qd of four consecutive query tiles of a request (the last group of a request may hold
@@ -238,7 +263,7 @@ __device__ __forceinline__ int wave_max(int x) {
 // One workgroup of kPlanThreads; thread i has the i-th tile with segment rows, the waves try 64 lengths at a time.
 // (Every tile in the same number of pieces leaves long ones, and a number rounded up so that they fill the slots a second
 // round of workgroups.  Passes, us, before / with it: 64/8 heads, 3 K tokens 76.4 / 61.0; 28/4 heads 62.6 / 46.8; 40/8
-// heads 65.4 / 55.5; 32/8 heads 54.3 / 48.2, 9 K tokens 90.5 / 77.5.  Pieces of 2 to 9 key tiles at least: the same.)
+// heads 65.4 / 55.5; 32/8 heads, 9 K tokens 90.5 / 77.5.  Pieces of 2 to 9 key tiles at least: the same.)
 constexpr int kPlanThreads = 1024, kMinPiece = 4;
 __device__ inline void plan_seg_units(int32_t* plan, const int32_t* img, const PlanHeader& h) {
   constexpr int W = kPlanThreads / 64, TRIES = 4 * W;  // lengths tried in a round, four a wave
@@ -248,17 +273,15 @@ __device__ inline void plan_seg_units(int32_t* plan, const int32_t* img, const P
   QTile q = {};
   int cost = 0;
   if (tid < n) {
-    const int b = find_owner(img + h.off_segtile_start, h.batch, tid);
-    const int c = img[h.off_prompt + b] + img[h.off_draft + b];
     int unused;
-    q = plan_tile_of(img, h, b, img[h.off_qtile_start + b] + c / h.tile_m + (tid - img[h.off_segtile_start + b]), &unused);
-    cost = q.n_a + (q.jb1 - q.jb0);
+    q = segment_tile(img, h, tid, &unused);
+    cost = q.rows > 0 ? q.n_a + (q.jb1 - q.jb0) : 0;
   }
   if (tid < 512) cost_s[tid] = cost;
   __syncthreads();
   // min(ceil(c / len), 8) by the reciprocal: (c - 1/2) / len is at least 1 / (2 len) from a whole number, and below 8
   // the product's error is less for every len under 2^18 and c under len * 8
-  auto pieces_of = [](int c, float rcp) { return min((int)(((float)c - 0.5f) * rcp) + 1, kMaxPieces); };
+  auto pieces_of = [](int c, float rcp) { return c > 0 ? min((int)(((float)c - 0.5f) * rcp) + 1, kMaxPieces) : 0; };
   int hi = 1;
   for (int i = lane; i < n; i += 64) hi = max(hi, cost_s[i]);
   hi = wave_max(hi);
@@ -312,6 +335,10 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_units(int32_t* plan, Plan
 // the end and whether it holds segment rows make one number.  Launches, us, in two or three kernels / with it: 16 ragged
 // requests of 55 K tokens 22.5 / 7.3 (16 lanes to a tile 9.8: too few compute units with work); one workgroup that
 // ranked all tiles / with it: 208 tiles 11.9 / 5.1, 96 tiles 5.6 / 5.0.
+// (threads, whole waves, in front of those of the tokens: the tiles of the segment-only call where they are not cut)
+__host__ __device__ inline int segment_tile_threads(const PlanHeader& h) {
+  return h.n_seg_units > 0 ? 0 : (h.n_seg_tiles + 63) & ~63;
+}
 constexpr int kRankTiles = kPlanThreads / 64, kPlanTiles = 4096, kPlanData = 4096;   // (tiles and ints of request data in LDS)
 __device__ inline void plan_all(int32_t* plan, const int32_t* img, unsigned* key_s, const PlanHeader& h, int rank_blocks,
                                 int quad_blocks, bool causal_short) {
@@ -322,7 +349,10 @@ __device__ inline void plan_all(int32_t* plan, const int32_t* img, unsigned* key
     return;
   }
   if (blk >= rank_blocks + quad_blocks) {
-    plan_token(plan, img, h, (blk - rank_blocks - quad_blocks) * kPlanThreads + tid, causal_short);
+    const int x = (blk - rank_blocks - quad_blocks) * kPlanThreads + tid;
+    const int seg_tiles = segment_tile_threads(h);
+    if (x >= seg_tiles) plan_token(plan, img, h, x - seg_tiles, causal_short);
+    else if (x < h.n_seg_tiles) plan_segment_tile(plan, img, h, x);
     return;
   }
   if (blk >= rank_blocks) {
@@ -407,7 +437,9 @@ __global__ __launch_bounds__(256) void k_plan_build(int32_t* plan, PlanHeader h,
     const int qd = (blk - tile_blocks) * 64 + (tid >> 2);
     if (qd < h.n_quads) plan_quad(plan, plan, h, qd, tid & 3);
   } else {
-    plan_token(plan, plan, h, (blk - tile_blocks - quad_blocks) * 256 + tid, causal_short);
+    const int x = (blk - tile_blocks - quad_blocks) * 256 + tid, seg_tiles = segment_tile_threads(h);
+    if (x >= seg_tiles) plan_token(plan, plan, h, x - seg_tiles, causal_short);
+    else if (x < h.n_seg_tiles) plan_segment_tile(plan, plan, h, x);
   }
 }
 
@@ -483,7 +515,7 @@ hipError_t launch_plan_kernels(int32_t* plan_dev, const PlanHeader& h, const int
   if (one_launch) {
     const int rank_blocks = (h.n_q_tiles + kRankTiles - 1) / kRankTiles;
     const int quad_blocks = (4 * h.n_quads + kPlanThreads - 1) / kPlanThreads;
-    const dim3 grid((h.n_seg_units > 0 ? 1 : 0) + rank_blocks + quad_blocks + (n1 + kPlanThreads - 1) / kPlanThreads);
+    const dim3 grid((h.n_seg_units > 0 ? 1 : 0) + rank_blocks + quad_blocks + (segment_tile_threads(h) + n1 + kPlanThreads - 1) / kPlanThreads);
     if (n_args > 0) {
       UploadChunk c;
       for (int i = 0; i < n_args; ++i) c.v[i] = host_ints[i];
@@ -496,7 +528,7 @@ hipError_t launch_plan_kernels(int32_t* plan_dev, const PlanHeader& h, const int
     if (e != hipSuccess) return e;
   } else {
     const int tile_blocks = (h.n_q_tiles + 255) / 256, quad_blocks = (h.n_quads + 63) / 64;
-    k_plan_build<<<dim3(tile_blocks + quad_blocks + (n1 + 255) / 256), dim3(256), 0, s>>>(plan_dev, h, tile_blocks,
+    k_plan_build<<<dim3(tile_blocks + quad_blocks + (segment_tile_threads(h) + n1 + 255) / 256), dim3(256), 0, s>>>(plan_dev, h, tile_blocks,
                                                                                          quad_blocks, causal_short);
     e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -1,5 +1,5 @@
-"""Segment rows over few tiles: the key pieces that the plan lists (they cover every tile's key list once, in pieces of
-nearly equal length, as many as there are places) and their merged result against the oracle, at the group sizes of both
+"""Segment rows: the tiles that the segment-only call evaluates, the key pieces that the plan lists where the tiles are
+few (they cover every tile's key list once, in pieces of nearly equal length, as many as there are places) and their merged result against the oracle, at the group sizes of both
 numbers of places, with odd rows per piece, pieces of which some rows see nothing, and the limits of the rule."""
 import numpy as np
 import pytest
@@ -13,8 +13,10 @@ pv = pytest.importorskip("paper_2605_04263_amd.binding")
 
 
 def places(tiles, tokens, batch, hq, hkv):
-    slots = (512 if hq // hkv <= 4 else 256) // hkv
-    if not 0 < tiles < slots or tokens // (64 * batch) * (124 * slots - 150 * tiles) <= 1600 * slots:
+    group, units, key_tiles = hq // hkv, 256 // hkv, tokens // (64 * batch)
+    one = group > 4 or group > 2 and 2 * tiles <= units and key_tiles * tiles <= 45 * units
+    slots = units if one else 512 // hkv
+    if not 0 < tiles < slots or key_tiles * (124 * slots - 150 * tiles) <= 1600 * slots:
         return 0
     return min(8 * tiles, slots)
 
@@ -24,8 +26,31 @@ PROBLEMS = {
     "early_and_late": wl.Problem([5], [3000], [4], [17], [[1, 3, 2990, 3000]]),     # rows that see nothing of most pieces
     "no_prompt": wl.Problem([0], [2100], [3], [40], [[0, 1000, 2000]]),
     "two_requests": wl.Problem([700, 64], [1500, 3100], [3, 2], [32, 33], [[100, 101, 1500], [7, 3100]]),
+    "segments_of_two_tiles": wl.Problem([301, 0], [900, 77], [5, 2], [64, 32], [[1, 300, 301, 899, 900], [30, 77]]),
     "many_tiles": wl.Problem([130], [2500], [33], [32], [[75 * (i + 1) for i in range(33)]]),
 }
+
+
+def segment_tiles(pr):
+    """{(request, first row of the listed tile): tile as the call evaluates it, or None}: the listed tiles with segment
+    rows, cut at the segments' first rows where these are whole numbers of tiles long."""
+    out, base = {}, pr.token_offsets()
+    for b in range(pr.batch):
+        p, t, s, n = pr.prompt_len[b], pr.draft_len[b], pr.segment_len[b], pr.seq_len(b)
+        c = p + t
+        for i, listed in enumerate(range(c // 32 * 32, n if pr.boundaries[b] else 0, 32)):
+            t0 = c + 32 * i if s % 32 == 0 else listed
+            rows = range(t0, min(t0 + 32, n))
+            low = [r + 1 if r < c else p + pr.boundaries[b][(r - c) // s] for r in rows]
+            own = [c + (r - c) // s * s for r in rows if r >= c]
+            if not rows:
+                out[b, listed] = None
+                continue
+            n_a = -(-max(low) // 64)
+            jb0 = max(n_a, own[0] // 64)
+            out[b, listed] = (base[b], t0, len(rows), min(low) // 64, n_a, jb0, max(jb0, rows[-1] // 64 + 1),
+                              sum((pr.seq_len(x) + 63) // 64 * 64 for x in range(b)))
+    return out
 
 
 @pytest.mark.parametrize("name", list(PROBLEMS))
@@ -37,12 +62,18 @@ def test_units(name, hq, hkv):
     ver.plan.fill_(-1)
     ver.build_mask()
     blob = ver.plan.view(torch.int32).cpu().numpy()
-    n, off, n_units, off_units = (int(blob[i]) for i in (30, 32, 36, 37))
+    n, off, n_units, off_units, off_tiles = (int(blob[i]) for i in (30, 32, 36, 37, 38))
     assert n_units == places(n, pr.total_tokens, pr.batch, hq, hkv)
-    if n_units == 0:
+    want = segment_tiles(pr)
+    assert len(want) == n
+    if n_units == 0:                                             # uncut: found by the place of the listed tile
+        for t in blob[off:off + 8 * n].reshape(n, 8).tolist():
+            at = off_tiles + (t[7] + t[1]) // 32 * 8
+            tile = want[pr.token_offsets().index(t[0]), t[1]]
+            assert blob[at + 2] == 0 if tile is None else tuple(blob[at:at + 8].tolist()) == tile
         return
     units = blob[off_units:off_units + 12 * n_units].reshape(n_units, 12)
-    seg = {tuple(t): 0 for t in blob[off:off + 8 * n].reshape(n, 8).tolist()}
+    seg = {t: 0 for t in want.values() if t is not None}
     used = units[units[:, 9] > 0]
     assert (units[:len(used), 9] > 0).all()
     lengths = {}
@@ -59,10 +90,14 @@ def test_units(name, hq, hkv):
 
 
 @pytest.mark.parametrize("hq,hkv,d,name", [(8, 2, 128, "long_prompt"), (8, 1, 128, "early_and_late"), (5, 1, 128, "no_prompt"),
-                                           (2, 2, 64, "early_and_late"), (7, 1, 64, "two_requests"), (3, 1, 128, "two_requests")])
+                                           (2, 2, 64, "early_and_late"), (7, 1, 64, "two_requests"), (3, 1, 128, "two_requests"), (4, 1, 128, "segments_of_two_tiles"),
+                                           (6, 1, 64, "segments_of_two_tiles")])
 @pytest.mark.parametrize("theta", [0.0, 5e5])
 def test_parity(hq, hkv, d, name, theta):
     pr = PROBLEMS[name]
     w = wl.make_custom(pr, hq, hkv, d, dtype=torch.bfloat16, seed=3, rope_theta=theta)
+    if name == "segments_of_two_tiles":                          # (uncut)
+        check_segments(w)
+        return
     assert places(5, pr.total_tokens, pr.batch, hq, hkv) > 0
     check_segments(w)
