@@ -83,9 +83,6 @@ __device__ __forceinline__ float2 rotary_cos_sin(int pos, double inv_freq) {
 // 122.7 / 116.5 - beyond 2 within 1 % either way.  Whole passes, us, at other heads: 16/4 of 64, 0.8: 55.3 /
 // 52.6 - 1.25: 86.5 / 83.6 - 1.6: 113.9 / 114.1 - 1.9: 150.3 / 149.0; 32/8 of 64, 0.8: 36.3 / 34.8 - 1.25:
 // 50.0 / 49.0 - 1.6: 67.2 / 66.9 - 1.9: 86.5 / 86.2; 16/4 of 128, 1.6: 180.2 / 177.3.
-// What it gives back: a pass that writes its keys over those of the pass before pays for them in the preparation
-// launch (1.5 workgroups per slot, 32/8 of 128: k_prep_kv 10.0 / 12.1, k_attn_bf16 73.2 / 69.3; with a workspace
-// that other passes have displaced 8.7 / 8.9).
 // Returned: 0 as listed, a > 0 the second `a` reversed, -a the shortest first behind the first `a`.
 inline int dispatch_order(int n_tiles, int hkv, int G) {
   const int a = 256 / hkv;
