@@ -72,10 +72,12 @@ void plan_layout(int batch, int64_t total_tokens, int64_t total_segments, int64_
   h->off_tiles = take(n_q_tiles * 8);
   h->off_work = take(n_q_tiles * 8);
   h->off_map = layout == PV_LAYOUT_INTERLEAVED ? take(total_tokens) : 0;
+  // The segment-only call's lists: the same places whatever the head counts, so that a plan built with one pair of
+  // them serves this call with another.
   h->off_segwork = take(2 * n_seg_tiles * 8);
+  h->off_segunit = take(seg_unit_list(n_seg_tiles) * 12);
+  h->off_segtile = take(n_seg_tiles > 0 ? padded_keys / kTileM * 8 : 0);
   h->off_quadwork = take(n_quads * 8);
-  h->off_segunit = take(n_seg_units * 12);
-  h->off_segtile = take(n_seg_tiles > 0 && n_seg_units == 0 ? padded_keys / kTileM * 8 : 0);
   h->total_ints = (int32_t)o;
 }
 

@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void k_merge_pieces(const int32_t* __restrict_
   constexpr int TPR = D / 4, RPP = 256 / TPR;        // threads per row, rows per pass
   const int G = hq / hkv, kvh = (int)blockIdx.x % hkv, hl = (int)blockIdx.x / hkv % G, head = kvh * G + hl;
   const int u = (int)blockIdx.x / hq;
-  const SegUnit unit = reinterpret_cast<const SegUnit*>(plan + h.off_segunit)[u];
+  const SegUnit unit = seg_unit(plan, h, u);
   const int pieces = unit.pieces;
   if (unit.n_kt == 0 || pieces == 1) return;
   const int row_end = min(32 * (unit.piece + 1) / pieces, unit.tile.rows), sub = threadIdx.x % TPR;

@@ -85,18 +85,16 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     kvh = item % hkv;
     head = kvh * G + wave_s;
     if (split == 2) {
-      const SegUnit unit = reinterpret_cast<const SegUnit*>(plan + h.off_segunit)[item / hkv];
+      const SegUnit unit = seg_unit(plan, h, item / hkv);
       if (unit.n_kt == 0) return;             // a place that the plan did not need
       tile = unit.tile;
       kt0 = unit.kt0;
       n_tiles = unit.n_kt;
+    } else if (split == 1) {
+      tile = seg_tile(plan, h, item / hkv);
+      if (tile.rows == 0) return;
     } else {
-      tile = reinterpret_cast<const QTile*>(
-          plan + (split ? h.off_segwork : h.off_work))[dispatch_rank(item / hkv, h.n_q_tiles, order)];
-      if (split) {                            // the list gives the order, this the rows
-        tile = reinterpret_cast<const QTile*>(plan + h.off_segtile)[(tile.kpad_base + tile.t0) / kTileM];
-        if (tile.rows == 0) return;
-      }
+      tile = reinterpret_cast<const QTile*>(plan + h.off_work)[dispatch_rank(item / hkv, h.n_q_tiles, order)];
     }
     mine = tile;
   }
@@ -825,7 +823,7 @@ __global__ __launch_bounds__(G * 64, 2) __attribute__((amdgpu_waves_per_eu(2))) 
     // the result of one of several pieces goes to the workspace (looked up here: nothing of it lives through the loops):
     // float [32][D] of this wave, then float2 [32] = (nmref, row sum)
     bool partial = false;
-    if (split == 2) partial = reinterpret_cast<const SegUnit*>(plan + h.off_segunit)[item / hkv].pieces > 1;
+    if (split == 2) partial = seg_unit(plan, h, item / hkv).pieces > 1;
     float* part_o = part + ((int64_t)item * G + wave_s) * (32 * (D + 2));
     const float inv = partial ? 1.0f : 1.0f / l_tot;
     const int64_t tok0 = (int64_t)mine.tok_base + mine.t0;

@@ -43,9 +43,9 @@ struct PlanHeader {
   int32_t off_quad_start;                                // [B+1] first such group of a request
   int32_t off_quadwork;                                  // [n_quads][8], per request last group first
   int32_t n_seg_units;                                   // places for key pieces of those tiles (seg_unit_places), 0: not cut
-  int32_t off_segunit;                                   // [n_seg_units][12]: SegUnit, used places first
+  int32_t off_segunit;                                   // [seg_unit_list(n_seg_tiles)][12]: SegUnit, n_seg_units of them, used places first
   int32_t off_segtile;                                   // [padded_keys / tile_m][8], at (kpad_base + t0) / tile_m of a listed tile with segment
-                                                         // rows: what the segment-only call evaluates for it (n_seg_units = 0)
+                                                         // rows: what the segment-only call evaluates for it
   int32_t reserved;
 };
 static_assert(sizeof(PlanHeader) == 40 * 4, "PlanHeader must be 40 ints (a multiple of 4)");
@@ -113,6 +113,39 @@ inline int64_t seg_unit_places(int64_t n_seg_tiles, int64_t total_tokens, int64_
   if (n_seg_tiles <= 0 || n_seg_tiles >= slots) return 0;
   if (key_tiles * (124 * slots - 150 * n_seg_tiles) <= 1600 * slots) return 0;
   return n_seg_tiles * kMaxPieces < slots ? n_seg_tiles * kMaxPieces : slots;
+}
+
+// Room for them in the plan: whatever the head counts, so that a plan's size and offsets do not depend on these.
+constexpr int kMaxSegUnits = 512;
+inline int64_t seg_unit_list(int64_t n_seg_tiles) {
+  if (n_seg_tiles >= kMaxSegUnits) return 0;         // more tiles than any head count has places: never cut
+  return n_seg_tiles * kMaxPieces < kMaxSegUnits ? n_seg_tiles * kMaxPieces : kMaxSegUnits;
+}
+
+// The i-th tile with segment rows, longest first, as the segment-only call evaluates it (rows = 0: nothing left of it).
+__device__ __forceinline__ QTile seg_tile(const int32_t* plan, const PlanHeader& h, int i) {
+  const QTile t = reinterpret_cast<const QTile*>(plan + h.off_segwork)[i];             // the list gives the order
+  return reinterpret_cast<const QTile*>(plan + h.off_segtile)[(t.kpad_base + t.t0) / kTileM];   // and this the rows
+}
+
+// The key piece in place u of a call with h.n_seg_units places: the plan's list, where the plan was built for as many.
+// A plan serves calls with other head counts too; with another number of places every tile is cut into the same number
+// of pieces here.  (Both loads are in flight together; u is inside the list's room either way.)
+__device__ __forceinline__ SegUnit seg_unit(const int32_t* plan, const PlanHeader& h, int u) {
+  SegUnit unit = reinterpret_cast<const SegUnit*>(plan + h.off_segunit)[u];
+  if (reinterpret_cast<const PlanHeader*>(plan)->n_seg_units == h.n_seg_units) return unit;
+  const int per_tile = h.n_seg_units / h.n_seg_tiles, i = u / per_tile;                // 1 .. kMaxPieces
+  unit.n_kt = 0;
+  if (i >= h.n_seg_tiles) return unit;
+  unit.tile = seg_tile(plan, h, i);
+  const int n = unit.tile.rows > 0 ? unit.tile.n_a + (unit.tile.jb1 - unit.tile.jb0) : 0;
+  unit.piece = u % per_tile;
+  unit.pieces = min(per_tile, n);
+  if (unit.piece < unit.pieces) {
+    unit.kt0 = unit.piece * n / unit.pieces;
+    unit.n_kt = (unit.piece + 1) * n / unit.pieces - unit.kt0;
+  }
+  return unit;
 }
 
 struct RopeFreq { double inv_freq[64]; };   // theta^(-2c/D), c < D/2 <= 64

@@ -335,10 +335,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_units(int32_t* plan, Plan
 // the end and whether it holds segment rows make one number.  Launches, us, in two or three kernels / with it: 16 ragged
 // requests of 55 K tokens 22.5 / 7.3 (16 lanes to a tile 9.8: too few compute units with work); one workgroup that
 // ranked all tiles / with it: 208 tiles 11.9 / 5.1, 96 tiles 5.6 / 5.0.
-// (threads, whole waves, in front of those of the tokens: the tiles of the segment-only call where they are not cut)
-__host__ __device__ inline int segment_tile_threads(const PlanHeader& h) {
-  return h.n_seg_units > 0 ? 0 : (h.n_seg_tiles + 63) & ~63;
-}
+// (threads, whole waves, in front of those of the tokens: the tiles of the segment-only call)
+__host__ __device__ inline int segment_tile_threads(const PlanHeader& h) { return (h.n_seg_tiles + 63) & ~63; }
 constexpr int kRankTiles = kPlanThreads / 64, kPlanTiles = 4096, kPlanData = 4096;   // (tiles and ints of request data in LDS)
 __device__ inline void plan_all(int32_t* plan, const int32_t* img, unsigned* key_s, const PlanHeader& h, int rank_blocks,
                                 int quad_blocks, bool causal_short) {
