@@ -84,7 +84,8 @@ typedef struct {
   int64_t padded_keys;           /* sum_b N_b rounded up to the key tile */
   int64_t plan_bytes;            /* device bytes pv_build_mask writes */
   int64_t dense_mask_bytes;      /* sum_b N_b^2 (uint8), only if the dense mask is requested */
-  int64_t attn_workspace_bytes;  /* device scratch pv_masked_attention needs */
+  int64_t attn_workspace_bytes;  /* device scratch pv_masked_attention needs; a smaller problem can need
+                                    more (partial results of pv_segment_attention) */
   int32_t n_q_heads, n_kv_heads, head_dim, in_dtype;
   int32_t tile_m, tile_n;        /* query tokens per work item, keys per tile */
   int32_t n_short_rows;          /* rows with at most PV_SHORT_ROW_KEYS visible keys (see below) */
@@ -192,8 +193,10 @@ pv_status pv_masked_attention_fp8kv(const pv_sizes* sizes, const void* plan_dev,
  *                    the batch: its rows do not move) keeps its first P + T_p prepared keys when
  *                    both passes use the capacity of the larger one and the second pass
  *                    prepares first_token = P + T_p onwards.  The workspace then needs
- *                    pv_prepared_workspace_bytes(sizes, key_capacity) bytes; 0 means the layout
- *                    and size of pv_segment_attention.
+ *                    pv_prepared_workspace_bytes(sizes, key_capacity) bytes, which does not
+ *                    shrink when a plan's n_seg_tiles grow: what the last pass of a growing draft
+ *                    asks for is enough for the passes before it.  0 means the layout and size of
+ *                    pv_segment_attention.
  *   k, v             device bf16; dense [total_tokens][Hkv][D] (block_table_dev NULL), or a pool of
  *                    pages [n_pages][page_size][Hkv][D] with block_table_dev: device int32
  *                    [ceil(total_tokens / page_size)], token row r of the packed batch (caller's

@@ -81,7 +81,7 @@ void plan_layout(int batch, int64_t total_tokens, int64_t total_segments, int64_
   h->total_ints = (int32_t)o;
 }
 
-AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, int64_t n_seg_units,
+AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, int64_t seg_units,
                                     int hq, int hkv, int d, int in_dtype) {
   AttnWorkspace w;
   w.off_part = 0;
@@ -95,7 +95,7 @@ AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, i
     o = align_up(o + (int64_t)hkv * padded_keys * d * 2, 256);
     w.off_part = o;
     w.total_full = o;
-    o = align_up(o + n_seg_units * hq * 32 * (d + 2) * 4, 256);
+    o = align_up(o + seg_units * hq * 32 * (d + 2) * 4, 256);
   } else {
     o = align_up(o + total_tokens * hkv * d * 4, 256);
     w.off_vt = o;
@@ -363,6 +363,15 @@ pv_status pv_build_mask(const pv_problem* problem, const pv_sizes* sizes, void* 
 // both.
 enum { kPhasePrepare = 1, kPhaseAttend = 2 };
 
+// The workspace of a call whose prepared keys have a head stride of key_capacity.  own_stride: a capacity that the caller
+// named, which calls under other plans share; the room for partial results then covers every plan with as many segment
+// tiles or fewer (at 32/8 heads 46 tiles of a finished draft are not cut and 23 tiles of its first half are: 64 places).
+static AttnWorkspace prepared_layout(const pv_sizes* s, const PlanHeader& h, int64_t key_capacity, bool own_stride) {
+  return attn_workspace_layout(own_stride ? key_capacity : s->total_tokens, key_capacity,
+                               own_stride ? seg_unit_bound(s->n_seg_tiles, s->n_kv_heads) : h.n_seg_units,
+                               s->n_q_heads, s->n_kv_heads, s->head_dim, s->in_dtype);
+}
+
 static pv_status attention_call(const pv_sizes* sizes, const void* plan_dev, const void* q,
                                 const void* k, const void* v, void* out, float* lse,
                                 int32_t out_dtype, float softmax_scale, float rope_theta,
@@ -396,9 +405,7 @@ static pv_status attention_call(const pv_sizes* sizes, const void* plan_dev, con
   if (tok_last < 0) tok_last = sizes->total_tokens;
   if (tok_first < 0 || tok_first > tok_last || tok_last > sizes->total_tokens) return PV_ERR_SHAPE;
   const int hq = sizes->n_q_heads, hkv = sizes->n_kv_heads, d = sizes->head_dim;
-  const AttnWorkspace wl =
-      attn_workspace_layout(own_stride ? key_capacity : sizes->total_tokens, key_capacity,
-                            h.n_seg_units, hq, hkv, d, sizes->in_dtype);
+  const AttnWorkspace wl = prepared_layout(sizes, h, key_capacity, own_stride);
   h.padded_keys = (int32_t)key_capacity;          // the kernels take the head stride from their copy of the header
   // a caller's workspace must have the size pv_query_sizes reports (which also covers the
   // segment-only call); the library's own fixed array only has to hold what the whole pass uses
@@ -598,9 +605,7 @@ pv_status pv_prepared_workspace_bytes(const pv_sizes* sizes, int64_t key_capacit
   if (key_capacity == 0) key_capacity = sizes->padded_keys;
   if (key_capacity < sizes->padded_keys || key_capacity % kTileN != 0 || key_capacity > (1ll << 27))
     return PV_ERR_SHAPE;
-  *bytes_out = attn_workspace_layout(own_stride ? key_capacity : sizes->total_tokens, key_capacity,
-                                     h.n_seg_units, sizes->n_q_heads, sizes->n_kv_heads,
-                                     sizes->head_dim, sizes->in_dtype).total;
+  *bytes_out = prepared_layout(sizes, h, key_capacity, own_stride).total;
   return PV_OK;
 }
 

@@ -121,6 +121,12 @@ inline int64_t seg_unit_list(int64_t n_seg_tiles) {
   if (n_seg_tiles >= kMaxSegUnits) return 0;         // more tiles than any head count has places: never cut
   return n_seg_tiles * kMaxPieces < kMaxSegUnits ? n_seg_tiles * kMaxPieces : kMaxSegUnits;
 }
+// The most places that a plan of up to n_seg_tiles such tiles has: what a workspace for keys that several plans share
+// has room for (the number itself goes down to 0 where a plan has enough tiles).
+inline int64_t seg_unit_bound(int64_t n_seg_tiles, int hkv) {
+  const int64_t slots = 512 / hkv;
+  return n_seg_tiles * kMaxPieces < slots ? n_seg_tiles * kMaxPieces : slots;
+}
 
 // The i-th tile with segment rows, longest first, as the segment-only call evaluates it (rows = 0: nothing left of it).
 __device__ __forceinline__ QTile seg_tile(const int32_t* plan, const PlanHeader& h, int i) {
@@ -160,7 +166,7 @@ struct AttnWorkspace {
   int64_t total_full;  // bytes the whole-pass call uses (everything before the partial results)
   int64_t total;
 };
-AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, int64_t n_seg_units,
+AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, int64_t seg_units,
                                     int hq, int hkv, int d, int in_dtype);
 
 // --- launchers (each returns the hipError_t of its launches) ---
