@@ -94,6 +94,8 @@ typedef struct {
   int32_t n_quads;               /* groups of four consecutive query tiles of a request; 0 unless
                                     Hq/Hkv is a group size whose kernels take them as work items */
   int32_t n_short_seg_rows;      /* those of the n_short_rows that are segment rows */
+  int32_t n_seg_pieces;          /* places for the key pieces into which pv_segment_attention cuts the
+                                    n_seg_tiles, 0: not cut */
 } pv_sizes;
 
 /* Host only: validates the problem and the head configuration and fills `out`.

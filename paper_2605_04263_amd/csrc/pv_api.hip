@@ -108,6 +108,7 @@ AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, i
 struct Totals {
   int64_t tokens = 0, segments = 0, max_len = 0, q_tiles = 0, padded_keys = 0, mask_bytes = 0;
   int64_t short_rows = 0, short_seg_rows = 0, seg_tiles = 0, quads = 0;
+  int64_t seg_longest = 0, seg_sum = 0;         // lengths of the requests with segments, in key tiles: see seg_unit_places
 };
 
 // Rows of request (P, T, S, boundaries) that see at most PV_SHORT_ROW_KEYS keys: the first causal
@@ -154,7 +155,12 @@ static pv_status validate_problem(const pv_problem* p, Totals* t) {
     t->max_len = n > t->max_len ? n : t->max_len;
     t->q_tiles += (n + kTileM - 1) / kTileM;
     t->quads += ((n + kTileM - 1) / kTileM + 3) / 4;
-    if (K > 0) t->seg_tiles += (n + kTileM - 1) / kTileM - (P + T) / kTileM;
+    if (K > 0) {
+      const int64_t tiles = (n + kTileM - 1) / kTileM - (P + T) / kTileM, length = n / kTileN;
+      t->seg_tiles += tiles;
+      t->seg_sum += tiles * length;
+      t->seg_longest = length > t->seg_longest ? length : t->seg_longest;
+    }
     t->padded_keys += align_up(n, kTileN);
     t->mask_bytes += n * n;
   }
@@ -182,9 +188,10 @@ static void fill_sizes(const pv_problem* p, const Totals& t, int hq, int hkv, in
   PlanHeader h;
   plan_layout(p->batch, t.tokens, t.segments, t.q_tiles, t.padded_keys, t.short_rows, p->layout,
               t.seg_tiles, group_uses_query_tiles(hq / hkv) ? t.quads : 0,
-              seg_unit_places(t.seg_tiles, t.tokens, p->batch, hq, hkv), &h);
+              seg_unit_places(t.seg_tiles, t.seg_longest, t.seg_sum, hq, hkv), &h);
   s->n_seg_tiles = (int32_t)t.seg_tiles;
   s->n_quads = h.n_quads;
+  s->n_seg_pieces = h.n_seg_units;
   s->n_short_rows = (int32_t)t.short_rows;
   s->n_short_seg_rows = (int32_t)t.short_seg_rows;
   s->layout = p->layout;
@@ -216,9 +223,13 @@ static pv_status check_sizes(const pv_sizes* s, PlanHeader* h) {
   if (validate_heads(s->n_q_heads, s->n_kv_heads, s->head_dim, s->in_dtype) != PV_OK)
     return PV_ERR_SHAPE;
   if (s->layout != PV_LAYOUT_APPENDED && s->layout != PV_LAYOUT_INTERLEAVED) return PV_ERR_SHAPE;
+  // places for key pieces: none, or at least one a tile and no more than the lists and the kernels' grids are made for
+  if (s->n_seg_pieces != 0 && (s->n_seg_pieces < s->n_seg_tiles || s->n_seg_tiles >= kMaxSegUnits ||
+                               s->n_seg_pieces > seg_unit_bound(s->n_seg_tiles, s->n_kv_heads)))
+    return PV_ERR_SHAPE;
   plan_layout((int)s->batch, s->total_tokens, s->total_segments, s->n_q_tiles, s->padded_keys,
               s->n_short_rows, s->layout, s->n_seg_tiles, s->n_quads,
-              seg_unit_places(s->n_seg_tiles, s->total_tokens, s->batch, s->n_q_heads, s->n_kv_heads), h);
+              s->n_seg_pieces, h);
   if (s->plan_bytes != (int64_t)h->total_ints * 4) return PV_ERR_SHAPE;
   return PV_OK;
 }

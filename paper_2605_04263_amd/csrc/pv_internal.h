@@ -104,15 +104,20 @@ constexpr int kMaxPieces = 8;
 // tile of an item alone on its unit, 1.5 beside another).  Uncut / cut, us: 32/8 heads, 2.8 K tokens, 26 tiles for 64
 // slots 75 / 67; 39 tiles 77 / 82; 52 tiles 88 / 98; 3 K tokens at 64/8 heads, 17 tiles for 32 slots 66 / 61; at 40/8
 // heads 64 / 55; 16/8 heads of 64, 41 tiles for 64 slots, 5.8 K tokens 74 / 57; 528 tokens, 5 tiles 26 / 28.
-inline int64_t seg_unit_places(int64_t n_seg_tiles, int64_t total_tokens, int64_t batch, int hq, int hkv) {
+// The lengths are those of the requests that have such tiles, in key tiles: `longest`, and `sum` over the tiles (a
+// request's length stands for its tiles').  By the batch's average, us, / so: 9 K tokens with 4 tiles beside 15 requests of
+// 50 tokens without a segment 114 / 35 (alone 35).  More tiles than workgroups of five to eight waves run at once, a few
+// of them long: cut too, in as many places as smaller workgroups have.  64/8 heads, 3 tiles of 9 K tokens among 48: 169 /
+// 58.
+inline int64_t seg_unit_places(int64_t n_seg_tiles, int64_t longest, int64_t sum, int hq, int hkv) {
   const int G = hq / hkv;
-  const int64_t key_tiles = total_tokens / (batch * kTileN);          // of an average request
-  const int64_t units = 256 / hkv;                                    // compute units of a head
-  const bool one = G > 4 || (G > 2 && 2 * n_seg_tiles <= units && key_tiles * n_seg_tiles <= 45 * units);
-  const int64_t slots = one ? units : 512 / hkv;
-  if (n_seg_tiles <= 0 || n_seg_tiles >= slots) return 0;
-  if (key_tiles * (124 * slots - 150 * n_seg_tiles) <= 1600 * slots) return 0;
-  return n_seg_tiles * kMaxPieces < slots ? n_seg_tiles * kMaxPieces : slots;
+  const int64_t units = 256 / hkv, most = 512 / hkv;                  // compute units of a head; places
+  const bool one = G > 4 || (G > 2 && 2 * n_seg_tiles <= units && sum <= 45 * units);
+  const int64_t slots = one ? units : most;                           // pieces at work at a time
+  const int64_t places = n_seg_tiles < slots ? slots : most;
+  if (n_seg_tiles <= 0 || n_seg_tiles >= places) return 0;
+  if (124 * longest * slots - 150 * sum <= 1600 * slots) return 0;
+  return n_seg_tiles * kMaxPieces < places ? n_seg_tiles * kMaxPieces : places;
 }
 
 // Room for them in the plan: whatever the head counts, so that a plan's size and offsets do not depend on these.
