@@ -465,7 +465,7 @@ static pv_status attention_call(const pv_sizes* sizes, const void* plan_dev, con
     const bool short_in_main = attend && prepare && tok_first == 0 && tok_last == sizes->total_tokens &&
                                main_kernel_takes_short_rows(h, hq, hkv, segments_only);
     e = launch_prep_bf16((const int32_t*)plan_dev, h, kv, hkv, d, freq, rope, (char*)workspace, wl,
-                         prepare, tok_first, tok_last,
+                         sizes->padded_keys, prepare, tok_first, tok_last,
                          // a segment-only pass has no short rows to do unless a segment sees almost nothing
                          attend && !short_in_main && (!segments_only || sizes->n_short_seg_rows > 0) ? q : nullptr,
                          out, lse, hq, scale, out_dtype == PV_F32, segments_only, s);

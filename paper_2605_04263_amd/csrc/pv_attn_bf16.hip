@@ -39,6 +39,7 @@ __device__ __forceinline__ uint4 load_16(const uint16_t* p) {
 // probabilities (exactly 0) never meet a non-finite value.
 //   n_short_blocks  short-row blocks in this launch (0: none)
 //   key_blocks      whether the launch has key blocks at all (a launch of short rows only has none)
+//   first_key       padded key row of the first key block (prep_range)
 //   tok_first/last  key blocks that hold no token of the packed range [tok_first, tok_last) leave
 //                   their part of the workspace as it is (keys prepared by an earlier call)
 // HG and STREAM by the size of the launch (prep_heads).  A launch that the chip holds at once is bound by one block's
@@ -58,9 +59,9 @@ __global__ __launch_bounds__(256) void k_prep_kv(const int32_t* __restrict__ pla
                                                  float2* __restrict__ cs, int hkv, bool rope,
                                                  uint16_t* __restrict__ krot,
                                                  uint16_t* __restrict__ vt, ShortRowArgs sr,
-                                                 int n_short_blocks, int tok_first, int tok_last) {
+                                                 int n_short_blocks, int first_key, int tok_first, int tok_last) {
   constexpr int HALF = D / 2;
-  constexpr int KB = 16;                       // keys per block
+  constexpr int KB = kPrepKeys;                // keys per block
   // one LDS area, used either by a short-row block or by a key block
   constexpr int CS_BYTES = KB * HALF * 8, VS_BYTES = HG * KB * (D / 8 + 1) * 16;
   constexpr int SHORT_BYTES = 2 * PV_SHORT_ROW_KEYS * D * 4;
@@ -77,16 +78,14 @@ __global__ __launch_bounds__(256) void k_prep_kv(const int32_t* __restrict__ pla
   uint4 (*v_s)[KB][D / 8 + 1] = reinterpret_cast<uint4 (*)[KB][D / 8 + 1]>(&lds[CS_BYTES / 16]);   // V rows of one pass, padded
   const int n_hg = (hkv + HG - 1) / HG;        // head groups
   const int mb = (int)blockIdx.x - n_short_blocks;
-  const int row0 = (mb / n_hg) * KB;           // first padded key row of this block
+  const int row0 = first_key + (mb / n_hg) * KB;   // first padded key row of this block
   const int h0 = (mb % n_hg) * HG;             // first kv head of this block
   const int nh = min(HG, hkv - h0);
   const KeyBlock own = key_block(plan, h, row0);
   const int tok_base = own.tok_base, n_b = own.n, key0 = own.key0;
   const int tid = threadIdx.x;
-  // Uniform over the workgroup: rows beyond the request's padding (a head stride larger than this
-  // plan's key count) are never read; a block with tokens runs if one of them is in the requested
-  // range; a block of padding only (zeros, see above) goes with the request's last token.
-  if (key0 >= own.n_padded) return;
+  // Uniform over the workgroup: a block with tokens runs if one of them is in the requested range; a
+  // block of padding only (zeros, see above) goes with the request's last token.
   const int first_tok = tok_base + min(key0, n_b - 1), end_tok = tok_base + min(key0 + KB, n_b);
   if (first_tok >= tok_last || end_tok <= tok_first) return;
 
@@ -278,16 +277,9 @@ static hipError_t dispatch_g(int G, const int32_t* plan, const PlanHeader& h, co
   return hipErrorInvalidValue;
 }
 
-// kv heads to a block of the preparation launch: one while the chip holds the whole launch at once (256 compute units
-// of eight such workgroups), four (streaming loads) from 80 MB of prepared keys on; both sides at the kernel.
-static int prep_heads(int64_t padded_keys, int hkv, int d) {
-  if (padded_keys / 16 * hkv <= 256 * 8) return 1;
-  return padded_keys * hkv * d * 4 < (80ll << 20) ? 2 : 4;
-}
-
 // K/V preparation (key blocks of the token range, and the short rows unless sr.q is null).
 hipError_t launch_prep_bf16(const int32_t* plan_dev, const PlanHeader& h, const KvArgs& kv, int hkv, int d,
-                            const RopeFreq& freq, bool rope, char* ws, const AttnWorkspace& wl,
+                            const RopeFreq& freq, bool rope, char* ws, const AttnWorkspace& wl, int64_t plan_keys,
                             bool key_blocks, int64_t tok_first, int64_t tok_last, const void* q, void* out,
                             float* lse, int hq, float scale, bool out_f32, bool segments_only,
                             hipStream_t s) {
@@ -303,13 +295,14 @@ hipError_t launch_prep_bf16(const int32_t* plan_dev, const PlanHeader& h, const 
   sr.q = reinterpret_cast<const uint16_t*>(q); sr.out = out; sr.lse = lse; sr.hq = hq; sr.scale = scale;
   sr.out_f32 = out_f32; sr.seg_only = segments_only; sr.table = nullptr;
   const int64_t n_short = q ? (int64_t)h.n_short_rows * hkv : 0;
-  const int hg = prep_heads(h.padded_keys, hkv, d);
-  const int64_t n_key = key_blocks ? (int64_t)(h.padded_keys / 16) * ((hkv + hg - 1) / hg) : 0;
+  const PrepRange keys = prep_range(tok_first, tok_last, h.batch, plan_keys);
+  const int hg = prep_heads(keys.last - keys.first, hkv, d);
+  const int64_t n_key = key_blocks ? (keys.last - keys.first) / kPrepKeys * ((hkv + hg - 1) / hg) : 0;
   if (n_short + n_key == 0) return hipSuccess;
   dim3 grid;
   if (!grid_1d(n_short + n_key, 256, &grid) || n_short > 0x7fffffff) return hipErrorInvalidConfiguration;
-  const int t0 = (int)tok_first, t1 = (int)tok_last;
-#define PV_PREP(D, HG, STREAM) k_prep_kv<D, HG, STREAM><<<grid, dim3(256), 0, s>>>(plan_dev, h, src, freq, cs, hkv, rope, krot, vt, sr, (int)n_short, t0, t1)
+  const int k0 = (int)keys.first, t0 = (int)tok_first, t1 = (int)tok_last;
+#define PV_PREP(D, HG, STREAM) k_prep_kv<D, HG, STREAM><<<grid, dim3(256), 0, s>>>(plan_dev, h, src, freq, cs, hkv, rope, krot, vt, sr, (int)n_short, k0, t0, t1)
   if (d == 64) {
     if (hg == 1) PV_PREP(64, 1, false); else if (hg == 2) PV_PREP(64, 2, false); else PV_PREP(64, 4, true);
   } else {

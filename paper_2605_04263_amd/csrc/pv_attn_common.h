@@ -121,10 +121,9 @@ struct CallerRows {
 struct KeyBlock {
   int tok_base, n;        // first packed row of the request, its tokens
   int key0;               // row0 in the request
-  int n_padded;           // its padded keys
 };
 __device__ __forceinline__ KeyBlock key_block(const int32_t* plan, const PlanHeader& h, int row0) {
-  if (h.batch == 1) return {0, h.total_tokens, row0, (h.total_tokens + kTileN - 1) / kTileN * kTileN};
+  if (h.batch == 1) return {0, h.total_tokens, row0};
   const int32_t* kp = plan + h.off_kpad_start;
   int lo = 0, hi = h.batch;
   while (hi - lo > 1) {
@@ -132,7 +131,7 @@ __device__ __forceinline__ KeyBlock key_block(const int32_t* plan, const PlanHea
     if (kp[mid] <= row0) lo = mid; else hi = mid;
   }
   const int tok_base = plan[h.off_tok_start + lo];
-  return {tok_base, plan[h.off_tok_start + lo + 1] - tok_base, row0 - kp[lo], kp[lo + 1] - kp[lo]};
+  return {tok_base, plan[h.off_tok_start + lo + 1] - tok_base, row0 - kp[lo]};
 }
 
 // s_waitcnt immediate (gfx9 encoding) that waits for vmcnt <= n only.

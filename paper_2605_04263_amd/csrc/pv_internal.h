@@ -191,6 +191,24 @@ hipError_t launch_attn_f32(const int32_t* plan_dev, const PlanHeader& h, const f
                            const float* k, const float* v, float* out, float* lse, int hq,
                            int hkv, int d, float scale, const RopeFreq& freq, bool rope,
                            char* ws, const AttnWorkspace& wl, hipStream_t s);
+// The padded keys [first, last), in whole blocks of kPrepKeys, that hold the packed tokens [tok_first, tok_last) and the
+// padding that goes with them.  Token t lies at key t or behind it, by less than kTileN a request.
+constexpr int kPrepKeys = 16;
+struct PrepRange { int64_t first, last; };
+inline PrepRange prep_range(int64_t tok_first, int64_t tok_last, int64_t batch, int64_t plan_keys) {
+  const int64_t end = tok_last + batch * (kTileN - 1);
+  return {tok_first / kPrepKeys * kPrepKeys, end < plan_keys ? (end + kPrepKeys - 1) / kPrepKeys * kPrepKeys : plan_keys};
+}
+
+// kv heads to a block of the launch that prepares `keys` padded keys: one while the chip holds the whole launch at once
+// (256 compute units of eight such workgroups), four (streaming loads) from 80 MB of prepared keys on; both sides at the
+// kernel.  The keys are those that this launch prepares: new tokens in a large workspace are a small launch (512 tokens at
+// 32/8 heads, us, by the workspace's keys / so: 20 K keys 5.2 / 3.8, 64 K 5.3 / 3.8; 3 K tokens in 20 K keys 7.7 / 7.5).
+inline int prep_heads(int64_t keys, int hkv, int d) {
+  if (keys / kPrepKeys * hkv <= 256 * 8) return 1;
+  return keys * hkv * d * 4 < (80ll << 20) ? 2 : 4;
+}
+
 // The caller's K and V for the preparation: dense tensors, or a pool of pages with a block table.
 struct KvArgs {
   const void* k;
@@ -200,8 +218,9 @@ struct KvArgs {
 };
 // bf16 path, step 1: rotary table, rotated K and transposed V of the tokens [tok_first, tok_last) into
 // the workspace (key_blocks), and the fp32 evaluation of the rows with few keys (q != nullptr).
+// plan_keys: the plan's padded keys (h.padded_keys is the head stride of the workspace, which can be larger).
 hipError_t launch_prep_bf16(const int32_t* plan_dev, const PlanHeader& h, const KvArgs& kv, int hkv, int d,
-                            const RopeFreq& freq, bool rope, char* ws, const AttnWorkspace& wl,
+                            const RopeFreq& freq, bool rope, char* ws, const AttnWorkspace& wl, int64_t plan_keys,
                             bool key_blocks, int64_t tok_first, int64_t tok_last, const void* q, void* out,
                             float* lse, int hq, float scale, bool out_f32, bool segments_only,
                             hipStream_t s);
