@@ -101,3 +101,43 @@ def test_captured_prepared_fp8_and_static_calls_replay_bit_exact():
         assert torch.equal(out_seg[seg_rows].view(torch.int16), want[0].view(torch.int16)), rep
         assert torch.equal(out_fp8.view(torch.int16), want[1].view(torch.int16)), rep
         assert torch.equal(out_static.view(torch.int16), want[2].view(torch.int16)), rep
+
+
+def test_captured_key_pieces_replay_bit_exact():
+    # segment rows that the plan cuts along the keys: plan, whole call, and the two halves under a capacity of their own
+    pr = wl.Problem([300, 7], [2500, 60], [3, 2], [32, 5], [[900, 1700, 2500], [9, 60]])
+    w = wl.make_custom(pr, 8, 2, 128, dtype=torch.bfloat16, rope_theta=5e5, seed=7)
+    ver = gc.make_verifier(pv, w)
+    assert ver.sizes.n_seg_pieces > ver.sizes.n_seg_tiles
+    dev = ver.device
+    q, k, v = w.q.to(dev), w.k.to(dev), w.v.to(dev)
+    capacity = ver.sizes.padded_keys + 640
+    ws = torch.empty(pv.pv_prepared_workspace_bytes(ver.sizes, capacity), dtype=torch.uint8, device=dev)
+    out, prepared = torch.zeros_like(q), torch.zeros_like(q)
+
+    def calls():
+        ver.build_mask()
+        ver.segment_attention(q, k, v, out, rope_theta=w.rope_theta)
+        pv.pv_prepare_kv(ver.sizes, ver.plan, k, v, ws, rope_theta=w.rope_theta, key_capacity=capacity)
+        pv.pv_segment_attention_prepared(ver.sizes, ver.plan, q, k, v, prepared, ws, rope_theta=w.rope_theta,
+                                         key_capacity=capacity)
+
+    calls()                                           # eager: also the one-time device queries of the library
+    torch.cuda.synchronize()
+    want = out.clone()
+    assert torch.equal(prepared.view(torch.int16), want.view(torch.int16))
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        calls()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls()
+    for rep in range(3):
+        out.fill_(0.0); prepared.fill_(0.0); ws.fill_(0x5A); ver.workspace.fill_(0x5A); ver.plan.fill_(-1)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16)), rep
+        assert torch.equal(prepared.view(torch.int16), want.view(torch.int16)), rep

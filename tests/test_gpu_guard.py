@@ -84,6 +84,7 @@ def run_guarded(pr, hq, hkv, d, theta, dense=True):
     # the calls did write: the bodies no longer hold the pattern everywhere
     assert not bool((bufs["out_bf16"].raw[GUARD:GUARD + 64] == PATTERN).all())
     assert bool(torch.isfinite(bufs["out_f32"].body).all())
+    return sz
 
 
 EDGE = [
@@ -106,8 +107,26 @@ def test_guards_edge_shapes(idx, layout):
     run_guarded(dataclasses.replace(pr, layout=layout), hq, hkv, d, theta)
 
 
+# Segment rows cut along the keys: the partial results end where the workspace ends.  Every place used (eight pieces a
+# tile), places left over (fewer key tiles than that), tiles with and without a further tile for the segments' first rows.
+CUT = [
+    (wl.Problem([100], [2600], [3], [17], [[1300, 2000, 2600]]), 8, 2, 128, 5e5),
+    (wl.Problem([300], [1500], [2], [32], [[40, 1500]]), 4, 4, 128, 0.0),
+    (wl.Problem([5, 9], [2900, 40], [4, 0], [33, 1], [[1, 3, 2890, 2900], []]), 5, 1, 128, 1e4),
+    (wl.Problem([0], [2400], [5], [64], [[0, 100, 1000, 2000, 2400]]), 16, 2, 64, 5e5),
+    (wl.Problem([700], [1400], [2], [9], [[700, 1400]]), 6, 2, 64, 5e5),
+]
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("idx", range(len(CUT)))
+def test_guards_cut_segments(idx, layout):
+    pr, hq, hkv, d, theta = CUT[idx]
+    assert run_guarded(dataclasses.replace(pr, layout=layout), hq, hkv, d, theta).n_seg_pieces > 0
+
+
 @pytest.mark.parametrize("layout", [0, 1])
 def test_guards_ragged_batch(layout):
-    # the ragged configuration (16 requests, the multi-kernel plan), without its 250 MB dense mask
+    # the ragged configuration (16 requests), without its 250 MB dense mask
     pr = dataclasses.replace(wl.make("ragged").problem, layout=layout)
     run_guarded(pr, 32, 8, 128, 5e5, dense=False)

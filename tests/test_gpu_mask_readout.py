@@ -81,8 +81,8 @@ def test_readout_named_and_patterns():
 
 
 def test_70b_plan_mask_work_list_readout():
-    # the long configuration (4 requests of 14 336 tokens, 1 792 tiles: the plan comes from the separate
-    # upload / build / ranking kernels): positions and judge rows of every token, the dense
+    # the long configuration (4 requests of 14 336 tokens, 1 792 tiles ranked by
+    # 112 workgroups): positions and judge rows of every token, the dense
     # mask of every request entry by entry (822 MB on the device, one request at a time on the host),
     # the row descriptors (rebuilt into mask rows), the tile classifier and the order of the work
     # list against the oracle's mask, and the readout in both modes
@@ -230,8 +230,7 @@ def test_work_list_8b_single_launch_plan():
 
 
 def test_work_list_multi_kernel_plan():
-    # more than 8192 tokens: the plan is built by the separate upload / build / ranking
-    # kernels instead of the single-workgroup kernel
+    # several requests and hundreds of tiles, ranked by many workgroups
     rng = np.random.default_rng(11)
     B = 6
     P = [int(x) for x in rng.integers(0, 700, B)]
@@ -351,5 +350,5 @@ def test_quad_list_random_and_named():
     for _ in range(25):
         check_quad_list(_random_problem(rng))
     check_quad_list(wl.make("14b").problem)
-    # more than 8192 tokens: the plan is built by the separate kernels, not by the single-workgroup one
+    # a few hundred groups, a short request behind a long one
     check_quad_list(wl.Problem([100, 7], [9000, 300], [3, 2], [40, 5], [[10, 4000, 9000], [0, 300]]))

@@ -1,7 +1,8 @@
-"""Plans that are built by several launches, at the edges of their split: request data that fit the kernel
-arguments of the launch that uses them or not; tile counts around a workgroup (256), around what a ranking
-pass reads (512) and with a last wave of 1 to 4 tiles; and the single launch at its largest.  Each problem
-states the route that it is here for.  Everything is whole numbers, against the oracle's mask and arrays."""
+"""Plans at the edges of the ways to build them: the whole image or the request data alone in the kernel arguments of
+the one launch, the request data uploaded before it, and, for more of them than a workgroup copies to LDS, separate
+launches for the tiles and for their ranking; tile counts around a workgroup (256) and around what a ranking pass reads
+(512), with a last wave of 1 to 4 tiles.  Each problem states the route that it is here for.  Everything is whole
+numbers, against the oracle's mask and arrays."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +13,7 @@ from tests.test_gpu_mask_readout import check_plan, check_quad_list, check_work_
 pytestmark = pytest.mark.gpu
 pv = pytest.importorskip("paper_2605_04263_amd.binding")
 
-ARG_INTS, SMALL_TOKENS = 896, 8192       # ints of request data in kernel arguments; tokens of the single launch
+ARG_INTS, DATA_INTS, MAX_TILES = 896, 4096, 4096     # ints in kernel arguments; of request data, and tiles, in one launch
 
 
 def even(lengths, k, s):
@@ -21,7 +22,7 @@ def even(lengths, k, s):
                       [[(j + 1) * (n - 9 - k * s) // (k + 1) for j in range(k)] for n in lengths])
 
 
-SINGLE, IN_ARGS, UPLOADED = "single launch", "data in the arguments", "data uploaded before"
+WHOLE, IN_ARGS, UPLOADED, SEPARATE = "all in the arguments", "data in the arguments", "data uploaded before", "separate launches"
 PROBLEMS = {
     "few_tokens_many_short_rows": (even([300] * 16, 2, 5), IN_ARGS),
     "few_tokens_data_too_large": (even([420] * 18, 40, 4), UPLOADED),
@@ -29,13 +30,19 @@ PROBLEMS = {
     "one_tile_requests_in_arguments": (even([32] * 45, 1, 3), IN_ARGS),
     "tiles_256_one_workgroup": (even([192] * 16 + [160] * 32, 1, 7), IN_ARGS),
     "tiles_257_two_workgroups": (even([192] * 17 + [160] * 31, 1, 7), IN_ARGS),
-    "tiles_256": (even([2720] * 3 + [32], 3, 7), SINGLE),
-    "tiles_257": (even([2720] * 3 + [33], 3, 7), IN_ARGS),
-    "tiles_512": (even([4096] * 4, 5, 33), IN_ARGS),
-    "tiles_513": (even([4096] * 3 + [4097], 5, 33), IN_ARGS),
-    "tiles_515_no_segments": (even([4096] * 4 + [70], 0, 1), IN_ARGS),
-    "single_launch_256_tiles": (even([8187], 3, 64), SINGLE),        # tiles and groups of four side by side
-    "single_launch_most_requests": (wl.Problem([0] * 50, [1] * 50, [0] * 50, [1] * 50, [[]] * 50), SINGLE),
+    "tiles_256": (even([2720] * 3 + [32], 3, 7), WHOLE),
+    "tiles_257": (even([2720] * 3 + [33], 3, 7), WHOLE),
+    "tiles_512": (even([4096] * 4, 5, 33), WHOLE),
+    "tiles_513": (even([4096] * 3 + [4097], 5, 33), WHOLE),
+    "tiles_515_no_segments": (even([4096] * 4 + [70], 0, 1), WHOLE),
+    "single_launch_256_tiles": (even([8187], 3, 64), WHOLE),         # tiles and groups of four side by side
+    "single_launch_most_requests": (wl.Problem([0] * 50, [1] * 50, [0] * 50, [1] * 50, [[]] * 50), WHOLE),
+    "separate_tiles_256": (even([2048] * 4, 1040, 1), SEPARATE),
+    "separate_tiles_257": (even([2048] * 3 + [2049], 1040, 1), SEPARATE),
+    "separate_tiles_512": (even([4096] * 4, 1040, 2), SEPARATE),
+    "separate_tiles_513": (even([4096] * 3 + [4097], 1040, 2), SEPARATE),
+    "separate_tiles_515": (even([4096] * 3 + [4192], 1040, 1), SEPARATE),
+    "separate_two_tile_requests": (even([42] * 130, 30, 1), SEPARATE),
 }
 
 
@@ -45,8 +52,8 @@ def test_plan(name):
     ver = check_plan(pr)
     head = ver.plan.view(torch.int32)[:36].cpu().tolist()            # off_short at 18, off_device_begin at 19
     in_args, whole_image = head[18] <= ARG_INTS, head[19] <= ARG_INTS
-    single = whole_image and max(pr.total_tokens, pr.total_segments) <= SMALL_TOKENS
-    assert route == (SINGLE if single else IN_ARGS if in_args else UPLOADED), (head[18], head[19], pr.total_tokens)
+    one_launch = ver.sizes.n_q_tiles <= MAX_TILES and head[18] <= DATA_INTS
+    assert route == (SEPARATE if not one_launch else WHOLE if whole_image else IN_ARGS if in_args else UPLOADED), head[18:20]
     if "tiles_" in name and name.split("tiles_")[1].split("_")[0].isdigit():
         assert ver.sizes.n_q_tiles == int(name.split("tiles_")[1].split("_")[0])
     check_work_list(pr)

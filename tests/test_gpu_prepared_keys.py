@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import pv_workloads as wl
+from tests.test_prepare_range import ranges     # noqa: F401  (a fixture)
 
 pytestmark = pytest.mark.gpu
 pv = pytest.importorskip("paper_2605_04263_amd.binding")
@@ -50,11 +51,11 @@ def check_table(ws, pr, theta, d):
     (8, 128, [4097], 2), (5, 64, [6000, 1, 700], 2), (3, 128, [11000], 2),
     (5, 128, [30000, 31, 2800], 4), (6, 128, [27400], 4),
 ])
-def test_bf16(hkv, d, lengths, heads):
+def test_bf16(hkv, d, lengths, heads, ranges):
     pr = problem(lengths)
     keys = sum((n + 63) // 64 * 64 for n in lengths)
-    assert heads == (1 if keys // 16 * hkv <= 2048 else 2 if keys * hkv * d * 4 < 80 << 20 else 4)
     n = pr.total_tokens
+    assert ranges([(0, n, len(lengths), keys, hkv, d)]) == [(0, keys, heads)]
     gen = torch.Generator(device="cuda").manual_seed(7)
     k, v = (torch.randn(n, hkv, d, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
     ver = pv.Verifier(pr.prompt_len, pr.draft_len, pr.num_segments, pr.segment_len, pr.flat_boundaries(), hkv, hkv, d,

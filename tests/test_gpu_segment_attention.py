@@ -176,13 +176,16 @@ def test_prepared_keys_equal_the_unsplit_call(idx, layout):
         assert _same_bits(out, want) and _same_bits(lse, want_lse)
 
 
-def test_prepared_keys_survive_a_grown_draft():
+@pytest.mark.parametrize("P,Tp,T,S,bounds", [
+    (70, 300, 700, 8, [100, 200, 300, 450, 600, 700]),
+    (70, 1600, 3200, 17, [500, 1100, 1600, 1650, 2400, 3200]),       # both passes cut along the keys
+])
+def test_prepared_keys_survive_a_grown_draft(P, Tp, T, S, bounds):
     # Premature verification at T_p draft tokens, then the pass over the finished draft (appendix "Full
     # pipeline", Stage 1 and Stage 4): the second pass prepares only the tokens from P + T_p on and must
     # give the bits of a call that prepares everything; both are checked against the oracle.
-    P, Tp, T, S = 70, 300, 700, 8
-    early = wl.Problem([P], [Tp], [3], [S], [[100, 200, 300]])
-    late = wl.Problem([P], [T], [6], [S], [[100, 200, 300, 450, 600, 700]])
+    early = wl.Problem([P], [Tp], [3], [S], [bounds[:3]])
+    late = wl.Problem([P], [T], [6], [S], [bounds])
     wB = wl.make_custom(late, 8, 2, 128, dtype=torch.bfloat16, rope_theta=5e5, seed=210)
     wA = wl.make_custom(early, 8, 2, 128, dtype=torch.bfloat16, rope_theta=5e5, seed=211)
     # the early pass sees the same prompt and the first T_p draft tokens
@@ -190,9 +193,10 @@ def test_prepared_keys_survive_a_grown_draft():
         getattr(wA, name)[:P + Tp] = getattr(wB, name)[:P + Tp]
     verA, verB = gc.make_verifier(pv, wA), gc.make_verifier(pv, wB)
     verA.build_mask(); verB.build_mask()
+    assert {s.n_seg_pieces > s.n_seg_tiles for s in (verA.sizes, verB.sizes)} == {Tp > 1000}
     dev = verB.device
     cap = verB.sizes.padded_keys
-    nbytes = max(pv.pv_prepared_workspace_bytes(verA.sizes, cap), pv.pv_prepared_workspace_bytes(verB.sizes, cap))
+    nbytes = pv.pv_prepared_workspace_bytes(verB.sizes, cap)
     ws = torch.full((nbytes,), 0x5A, dtype=torch.uint8, device=dev)
     qA, kA, vA = wA.q.to(dev), wA.k.to(dev), wA.v.to(dev)
     qB, kB, vB = wB.q.to(dev), wB.k.to(dev), wB.v.to(dev)

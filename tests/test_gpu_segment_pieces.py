@@ -1,6 +1,8 @@
 """Segment rows: the tiles that the segment-only call evaluates, the key pieces that the plan lists where the tiles are
-few (they cover every tile's key list once, in pieces of nearly equal length, as many as there are places) and their merged result against the oracle, at the group sizes of both
-numbers of places, with odd rows per piece, pieces of which some rows see nothing, and the limits of the rule."""
+few (they cover every tile's key list once, in pieces of nearly equal length, as many as there are places) and their
+merged result against the oracle, at the group sizes of both numbers of places, with odd rows per piece, pieces of which
+some rows see nothing, more tiles than a wave has lanes, lengths that take several rounds to find, and the list that a
+launch of its own writes."""
 import numpy as np
 import pytest
 import torch
@@ -18,6 +20,10 @@ PROBLEMS = {
     "no_prompt": wl.Problem([0], [2100], [3], [40], [[0, 1000, 2000]]),
     "two_requests": wl.Problem([700, 64], [1500, 3100], [3, 2], [32, 33], [[100, 101, 1500], [7, 3100]]),
     "segments_of_two_tiles": wl.Problem([101, 0], [400, 77], [5, 2], [64, 32], [[1, 300, 301, 399, 400], [30, 77]]),   # (too short to cut)
+    "several_rounds": wl.Problem([1000], [12000], [6], [17], [[3, 2000, 2001, 6000, 9000, 12000]]),      # 200 lengths to try
+    "two_rounds_exactly": wl.Problem([60000], [77], [2], [64], [[7, 77]]),
+    "tiles_of_several_waves": wl.Problem([200, 9], [6000, 800], [100, 3], [32, 5], [[60 * (i + 1) for i in range(100)], [1, 9, 800]]),
+    "launch_of_its_own": wl.Problem([100000, 3], [31300, 60], [5, 1], [9, 40], [[1, 9000, 9001, 31000, 31300], [60]]),
     "many_tiles": wl.Problem([130], [2500], [33], [32], [[75 * (i + 1) for i in range(33)]]),
 }
 
@@ -45,7 +51,7 @@ def segment_tiles(pr):
 
 
 @pytest.mark.parametrize("name", list(PROBLEMS))
-@pytest.mark.parametrize("hq,hkv", [(32, 8), (64, 8), (40, 8), (8, 8), (14, 2), (3, 3)])
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (64, 8), (40, 8), (8, 8), (14, 2), (3, 3), (2, 1)])
 def test_units(name, hq, hkv):
     pr = PROBLEMS[name]
     ver = pv.Verifier(pr.prompt_len, pr.draft_len, pr.num_segments, pr.segment_len, pr.flat_boundaries(), hq, hkv, 128,
@@ -55,6 +61,9 @@ def test_units(name, hq, hkv):
     blob = ver.plan.view(torch.int32).cpu().numpy()
     n, off, n_units, off_units, off_tiles = (int(blob[i]) for i in (30, 32, 36, 37, 38))
     assert n_units == ver.sizes.n_seg_pieces
+    assert (ver.sizes.n_q_tiles > 4096) == (name == "launch_of_its_own")
+    if name in ("several_rounds", "two_rounds_exactly", "launch_of_its_own") or name == "tiles_of_several_waves" and hkv in (1, 3):
+        assert n_units > n
     want = segment_tiles(pr)
     assert len(want) == n
     if n_units == 0:                                             # uncut: found by the place of the listed tile
@@ -89,3 +98,9 @@ def test_parity(hq, hkv, d, name, theta):
     w = wl.make_custom(pr, hq, hkv, d, dtype=torch.bfloat16, seed=3, rope_theta=theta)
     ver = check_segments(w)
     assert (ver.sizes.n_seg_pieces > 0) == (name != "segments_of_two_tiles")
+
+
+def test_parity_of_more_tiles_than_lanes():
+    pr = wl.Problem([64], [3000], [80], [32], [[37 * (i + 1) for i in range(80)]])
+    ver = check_segments(wl.make_custom(pr, 4, 1, 128, dtype=torch.bfloat16, seed=4, rope_theta=5e5), sample=160)
+    assert 64 < ver.sizes.n_seg_tiles < ver.sizes.n_seg_pieces
