@@ -184,9 +184,9 @@ __global__ __launch_bounds__(256) void k_prep_kv(const int32_t* __restrict__ pla
 // Merge of the key pieces of the segment-only call.  Piece c holds, relative to its own reference
 // mref_c = -nmref_c (log2 units), the unnormalised O_c and the row sum l_c; with M = max mref_c over
 // the pieces that saw a key, O = sum_c 2^(mref_c - M) O_c / sum_c 2^(mref_c - M) l_c.
-// One workgroup per (piece, query head), for that piece's share of the tile's rows: as many workgroups as the pieces
-// had, in the order of heads that they had, and all loads of a thread (4 features of one row in every piece) in one
-// round trip: bound by latency and by the partial results, 16.6 KB a wave.
+// One workgroup per (piece, query head), one for each wave of the pieces' launch, the kv heads in the order that they had
+// there.  It merges the piece's share of the tile's rows, with all loads of a thread (4 features of one row in every
+// piece) in one round trip: bound by latency and by the partial results, 16.6 KB a wave.
 template <int D>
 __global__ __launch_bounds__(256) void k_merge_pieces(const int32_t* __restrict__ plan, PlanHeader h,
                                                       const float* __restrict__ part,

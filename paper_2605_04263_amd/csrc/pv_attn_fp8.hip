@@ -65,10 +65,9 @@ __device__ __forceinline__ unsigned pack_fp8x4(float a, float b, float c, float 
 //         registers of S^T hold keys, so probabilities go into the second product in place)
 // Pad keys (beyond the request) are zero codes.  Latency bounds a small launch: half a tile to a workgroup is one load
 // of K and of V and one chunk of V^T a thread, and the angles of its keys are shared out among the heads' workgroups and
-// formed while the loads fly, where a whole tile with all its angles at the end of the first head's workgroups was
-// a chain of its own.  Passes, us,
-// before / with it: 3 K tokens at 32/8 heads 80.3 / 77.6, 4.5 K at 28/4 heads 138.7 / 136.3, ragged 23 K 518.5 / 519.5,
-// 4 x 14 K at 64/8 heads 7132 / 7074.
+// formed while the loads fly, where a whole tile with all its angles at the end of the first head's workgroups was a
+// chain of its own.  Passes, us, before / with it: 3 K tokens at 32/8 heads 80.3 / 77.6, 4.5 K at 28/4 heads 138.7 /
+// 136.3, ragged 23 K 518.5 / 519.5, 4 x 14 K at 64/8 heads 7132 / 7074.
 template <int D>
 __global__ __launch_bounds__(256) void k_prep_fp8(const int32_t* __restrict__ plan, PlanHeader h,
                                                   const uint8_t* __restrict__ k8,

@@ -327,16 +327,17 @@ __device__ inline void plan_seg_units(int32_t* plan, const int32_t* img, const P
 // (a plan too large for plan_all)
 __global__ __launch_bounds__(kPlanThreads) void k_plan_units(int32_t* plan, PlanHeader h) { plan_seg_units(plan, plan, h); }
 
+// Threads, whole waves, in front of those of the tokens: the tiles of the segment-only call.
+__host__ __device__ inline int segment_tile_threads(const PlanHeader& h) { return (h.n_seg_tiles + 63) & ~63; }
+
 // The whole plan in one launch.  The request data (in the kernel arguments, or uploaded before) are copied to LDS by
 // every workgroup, and no workgroup reads what another writes: a workgroup that ranks kRankTiles tiles, a wave each,
 // forms the costs of all tiles itself.  That is two tiles a thread at 1 766 tiles (a tile is a chain of LDS reads and
 // divisions of 0.7 us: with 256 threads to a workgroup and seven tiles a thread the launch took 11.5 us), against a
-// launch of its own for the ranking and its wait for the tiles.  Longest first, ties in the order of the tiles: the cost, the tile's index from
-// the end and whether it holds segment rows make one number.  Launches, us, in two or three kernels / with it: 16 ragged
-// requests of 55 K tokens 22.5 / 7.3 (16 lanes to a tile 9.8: too few compute units with work); one workgroup that
-// ranked all tiles / with it: 208 tiles 11.9 / 5.1, 96 tiles 5.6 / 5.0.
-// (threads, whole waves, in front of those of the tokens: the tiles of the segment-only call)
-__host__ __device__ inline int segment_tile_threads(const PlanHeader& h) { return (h.n_seg_tiles + 63) & ~63; }
+// launch of its own for the ranking and its wait for the tiles.  Longest first, ties in the order of the tiles: the
+// cost, the tile's index from the end and whether it holds segment rows make one number.  Launches, us, in two or
+// three kernels / with it: 16 ragged requests of 55 K tokens 22.5 / 7.3 (16 lanes to a tile 9.8: too few compute units
+// with work); one workgroup that ranked all tiles / with it: 208 tiles 11.9 / 5.1, 96 tiles 5.6 / 5.0.
 constexpr int kRankTiles = kPlanThreads / 64, kPlanTiles = 4096, kPlanData = 4096;   // (tiles and ints of request data in LDS)
 __device__ inline void plan_all(int32_t* plan, const int32_t* img, unsigned* key_s, const PlanHeader& h, int rank_blocks,
                                 int quad_blocks, bool causal_short) {
@@ -396,8 +397,8 @@ __device__ inline void plan_all(int32_t* plan, const int32_t* img, unsigned* key
   }
 }
 // n_img ints of the arguments are the start of the plan (its last workgroup, one of tokens, writes them there).
-__global__ __launch_bounds__(kPlanThreads) void k_plan_args(int32_t* plan, PlanHeader h, UploadChunk c, int n_img, int rank_blocks,
-                                                   int quad_blocks, bool causal_short) {
+__global__ __launch_bounds__(kPlanThreads) void k_plan_args(int32_t* plan, PlanHeader h, UploadChunk c, int n_img,
+                                                            int rank_blocks, int quad_blocks, bool causal_short) {
   __shared__ int32_t img_s[kUploadInts];
   __shared__ __align__(16) unsigned key_s[kPlanTiles];
   for (int i = threadIdx.x; i < n_img; i += kPlanThreads) {
@@ -409,8 +410,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_args(int32_t* plan, PlanH
   plan_all(plan, img_s, key_s, h, rank_blocks, quad_blocks, causal_short);
 }
 // The request data are in the plan already.
-__global__ __launch_bounds__(kPlanThreads) void k_plan_uploaded(int32_t* plan, PlanHeader h, int n_data, int rank_blocks,
-                                                       int quad_blocks, bool causal_short) {
+__global__ __launch_bounds__(kPlanThreads) void k_plan_uploaded(int32_t* plan, PlanHeader h, int n_data,
+                                                                int rank_blocks, int quad_blocks, bool causal_short) {
   __shared__ int32_t img_s[kPlanData];
   __shared__ __align__(16) unsigned key_s[kPlanTiles];
   for (int i = threadIdx.x; i < n_data; i += kPlanThreads) img_s[i] = plan[i];
@@ -513,21 +514,23 @@ hipError_t launch_plan_kernels(int32_t* plan_dev, const PlanHeader& h, const int
   if (one_launch) {
     const int rank_blocks = (h.n_q_tiles + kRankTiles - 1) / kRankTiles;
     const int quad_blocks = (4 * h.n_quads + kPlanThreads - 1) / kPlanThreads;
-    const dim3 grid((h.n_seg_units > 0 ? 1 : 0) + rank_blocks + quad_blocks + (segment_tile_threads(h) + n1 + kPlanThreads - 1) / kPlanThreads);
+    const int token_blocks = (segment_tile_threads(h) + n1 + kPlanThreads - 1) / kPlanThreads;
+    const dim3 grid((h.n_seg_units > 0 ? 1 : 0) + rank_blocks + quad_blocks + token_blocks);
     if (n_args > 0) {
       UploadChunk c;
       for (int i = 0; i < n_args; ++i) c.v[i] = host_ints[i];
       for (int i = n_args; i < kUploadInts; ++i) c.v[i] = 0;
       k_plan_args<<<grid, dim3(kPlanThreads), 0, s>>>(plan_dev, h, c, n_args, rank_blocks, quad_blocks, causal_short);
     } else {
-      k_plan_uploaded<<<grid, dim3(kPlanThreads), 0, s>>>(plan_dev, h, h.off_short, rank_blocks, quad_blocks, causal_short);
+      k_plan_uploaded<<<grid, dim3(kPlanThreads), 0, s>>>(plan_dev, h, h.off_short, rank_blocks, quad_blocks,
+                                                          causal_short);
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   } else {
     const int tile_blocks = (h.n_q_tiles + 255) / 256, quad_blocks = (h.n_quads + 63) / 64;
-    k_plan_build<<<dim3(tile_blocks + quad_blocks + (segment_tile_threads(h) + n1 + 255) / 256), dim3(256), 0, s>>>(plan_dev, h, tile_blocks,
-                                                                                         quad_blocks, causal_short);
+    const dim3 grid(tile_blocks + quad_blocks + (segment_tile_threads(h) + n1 + 255) / 256);
+    k_plan_build<<<grid, dim3(256), 0, s>>>(plan_dev, h, tile_blocks, quad_blocks, causal_short);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     constexpr int kPerBlock = 4 * kSortTiles;
