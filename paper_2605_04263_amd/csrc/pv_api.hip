@@ -1,5 +1,6 @@
 // C ABI of the library: argument validation on the host, then kernel launches on the caller's
 // stream.  Nothing here allocates device memory or synchronises (pv_profile_read excepted).
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -223,9 +224,10 @@ static pv_status check_sizes(const pv_sizes* s, PlanHeader* h) {
   if (validate_heads(s->n_q_heads, s->n_kv_heads, s->head_dim, s->in_dtype) != PV_OK)
     return PV_ERR_SHAPE;
   if (s->layout != PV_LAYOUT_APPENDED && s->layout != PV_LAYOUT_INTERLEAVED) return PV_ERR_SHAPE;
-  // places for key pieces: none, or at least one a tile and no more than the lists and the kernels' grids are made for
-  if (s->n_seg_pieces != 0 && (s->n_seg_pieces < s->n_seg_tiles || s->n_seg_tiles >= kMaxSegUnits ||
-                               s->n_seg_pieces > seg_unit_bound(s->n_seg_tiles, s->n_kv_heads)))
+  // places for key pieces: none, or at least one a tile and no more than the plan has room for (head counts that a
+  // caller has put in the place of those of the query can make them more than pv_query_sizes would)
+  if (s->n_seg_pieces != 0 &&
+      (s->n_seg_pieces < s->n_seg_tiles || s->n_seg_pieces > seg_unit_list(s->n_seg_tiles)))
     return PV_ERR_SHAPE;
   plan_layout((int)s->batch, s->total_tokens, s->total_segments, s->n_q_tiles, s->padded_keys,
               s->n_short_rows, s->layout, s->n_seg_tiles, s->n_quads,
@@ -379,7 +381,8 @@ enum { kPhasePrepare = 1, kPhaseAttend = 2 };
 // tiles or fewer (at 32/8 heads 46 tiles of a finished draft are not cut and 23 tiles of its first half are: 64 places).
 static AttnWorkspace prepared_layout(const pv_sizes* s, const PlanHeader& h, int64_t key_capacity, bool own_stride) {
   return attn_workspace_layout(own_stride ? key_capacity : s->total_tokens, key_capacity,
-                               own_stride ? seg_unit_bound(s->n_seg_tiles, s->n_kv_heads) : h.n_seg_units,
+                               own_stride ? std::max<int64_t>(seg_unit_bound(s->n_seg_tiles, s->n_kv_heads), h.n_seg_units)
+                                          : h.n_seg_units,
                                s->n_q_heads, s->n_kv_heads, s->head_dim, s->in_dtype);
 }
 
