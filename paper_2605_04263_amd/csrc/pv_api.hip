@@ -109,7 +109,6 @@ AttnWorkspace attn_workspace_layout(int64_t total_tokens, int64_t padded_keys, i
 struct Totals {
   int64_t tokens = 0, segments = 0, max_len = 0, q_tiles = 0, padded_keys = 0, mask_bytes = 0;
   int64_t short_rows = 0, short_seg_rows = 0, seg_tiles = 0, quads = 0;
-  int64_t seg_longest = 0, seg_sum = 0;         // lengths of the requests with segments, in key tiles: see seg_unit_places
 };
 
 // Rows of request (P, T, S, boundaries) that see at most PV_SHORT_ROW_KEYS keys: the first causal
@@ -156,12 +155,7 @@ static pv_status validate_problem(const pv_problem* p, Totals* t) {
     t->max_len = n > t->max_len ? n : t->max_len;
     t->q_tiles += (n + kTileM - 1) / kTileM;
     t->quads += ((n + kTileM - 1) / kTileM + 3) / 4;
-    if (K > 0) {
-      const int64_t tiles = (n + kTileM - 1) / kTileM - (P + T) / kTileM, length = n / kTileN;
-      t->seg_tiles += tiles;
-      t->seg_sum += tiles * length;
-      t->seg_longest = length > t->seg_longest ? length : t->seg_longest;
-    }
+    if (K > 0) t->seg_tiles += (n + kTileM - 1) / kTileM - (P + T) / kTileM;
     t->padded_keys += align_up(n, kTileN);
     t->mask_bytes += n * n;
   }
@@ -177,6 +171,95 @@ static pv_status validate_heads(int hq, int hkv, int d, int in_dtype) {
   return PV_OK;
 }
 
+// Work of one tile of the segment-only call: key tiles that all its rows see whole, and key tiles listed for it.
+struct SegWork { int open, listed; };
+
+// The tiles that the segment-only call evaluates (segment_tile), for a problem with fewer than kMaxSegUnits of them.
+static int seg_work(const pv_problem* p, SegWork* work) {
+  int n = 0;
+  int64_t seg = 0;
+  for (int b = 0; b < p->batch; ++b) {
+    const int64_t P = p->prompt_len[b], K = p->num_segments[b], S = p->segment_len[b], c = P + p->draft_len[b];
+    const int32_t* bounds = p->boundaries + seg;
+    for (int64_t t0 = S % kTileM == 0 ? c : c / kTileM * kTileM; K > 0 && t0 < c + K * S; t0 += kTileM) {
+      const int64_t last = std::min(t0 + kTileM, c + K * S) - 1, k0 = (std::max(t0, c) - c) / S, k1 = (last - c) / S;
+      int64_t open = P + bounds[k0], low = P + bounds[k1];
+      if (t0 < c) { open = std::min(open, t0 + 1); low = std::max(low, std::min(last, c - 1) + 1); }
+      const int64_t n_a = (low + kTileN - 1) / kTileN, jb0 = std::max(n_a, (c + k0 * S) / kTileN);
+      work[n++] = {(int)(open / kTileN), (int)(n_a + std::max(jb0, last / kTileN + 1) - jb0)};
+    }
+    seg += K;
+  }
+  return n;
+}
+
+// How long the chip takes for `n` items of a kv head (x: key tiles, sorted here), in key tiles of an item that has its
+// compute unit for itself.  More items than the head has units: up to four waves an item are two at a time on a unit,
+// which slow each other down; more waves are a second round, and where the items are pieces that costs its own prologue.
+static double seg_span(float* x, int n, int units, int G, bool cut) {
+  std::sort(x, x + n, [](float a, float b) { return a > b; });
+  if (n <= units) return x[0];
+  if (G <= 4) return G <= 2 ? x[0] : x[0] + 0.6 * x[units];
+  double most = x[0];
+  for (int i = 0; i < n - units && i < units; ++i) most = std::max(most, (double)x[units - 1 - i] + x[units + i]);
+  return cut ? 1.2 * most + 9.0 : most;
+}
+
+// Places for key pieces of the segment-only call, at most kMaxPieces to a tile; 0: its tiles are not cut.  Cut into as
+// many pieces as a head has compute units, or twice as many (all workgroup slots of up to four waves), or not at all,
+// whichever the work of the tiles themselves says is shortest.  Neither can be told from the number of tiles and the
+// requests' lengths: a tile's key list ends with its boundary, half a request's length away from its end on average, a
+// masked key tile takes half as long again, and requests without a segment have no say.  Plan and rows over prepared
+// keys, us, uncut / one a unit / two a unit: 32/8 heads, 13 tiles of up to 84 key tiles 73 / 40 / 42, 22 of 16 26 / 31 /
+// 34, 57 of 107 118 / - / 127; 40/8 heads, 19 of 30 60 / 40 / 49; 64/8 heads, 19 of 48 73 / 80 / 81, 23 of 138 223 /
+// 151 / 123; 8/8 heads, 49 of 70 124 / - / 85; 24/8 heads, 9 of 105 134 / 56 / 48; 28/4 heads, 38 of 32 53 / 61 / 67;
+// 32/8 heads of 64, 53 of 86 92 / - / 71.  Over 1600 random batches (1 to 24 requests, these head counts and others, up
+// to 40 K tokens) the choice is 0.3 % slower than the best of the three on average and more than 3 % slower for 47; by
+// the lengths of the requests it was 2.1 % and 227.  9 K tokens with 4 tiles beside 15 requests of 50 tokens without a
+// segment: 114 by the batch's average length, now 35, as alone.
+// Every piece has a reference of its own, whose weight is exact in bf16; fewer pieces hold fewer such weights.  Error of
+// the rows against fp64, every tile in four pieces / in about two / the whole pass: 3 K tokens at 32/8 heads 2.888e-3 /
+// 2.901e-3 / 2.908e-3, without rotation at 40/8 heads 1.573e-3 / 1.613e-3 / 1.632e-3.
+static int64_t seg_unit_places(const pv_problem* p, int64_t n_seg_tiles, int hq, int hkv, int d) {
+  const int G = hq / hkv, units = 256 / hkv, most = 512 / hkv;
+  if (n_seg_tiles <= 0 || n_seg_tiles >= most) return 0;      // (most <= kMaxSegUnits)
+  SegWork work[kMaxSegUnits];
+  float x[kMaxSegUnits];
+  const int n = seg_work(p, work);
+  const double us = (G <= 2 ? 0.9 : G <= 4 ? 0.7 : 1.0) * (d == 64 ? 0.8 : 1.0);       // a key tile in the open
+  constexpr float kMasked = 1.5f;                                                      // one that is masked
+  int longest = 1;
+  for (int i = 0; i < n; ++i) {
+    x[i] = work[i].open + kMasked * (work[i].listed - work[i].open);
+    longest = std::max(longest, work[i].listed);
+  }
+  const double uncut = us * seg_span(x, n, units, G, false);
+  int64_t best = 0;
+  double best_us = uncut - 2.0;                               // (nearly equal: without the workspace and the merge)
+  for (const int slots : {units, most}) {
+    const int places = (int)std::min<int64_t>(n_seg_tiles * kMaxPieces, slots);
+    if (places < n_seg_tiles) continue;
+    auto pieces = [&](int i, int len) { return std::min((work[i].listed + len - 1) / len, kMaxPieces); };
+    int lo = std::min(kMinPiece, longest), hi = longest;      // the shortest length whose pieces fit, as plan_seg_units
+    while (lo < hi) {
+      const int mid = (lo + hi) / 2;
+      int total = 0;
+      for (int i = 0; i < n; ++i) total += pieces(i, mid);
+      if (total > places) lo = mid + 1; else hi = mid;
+    }
+    int m = 0;
+    for (int i = 0; i < n; ++i)
+      for (int c = 0, k = pieces(i, lo); c < k; ++c) {
+        const int first = c * work[i].listed / k, end = (c + 1) * work[i].listed / k;
+        const int open = std::max(0, std::min(end, work[i].open) - first);
+        x[m++] = open + kMasked * (end - first - open);
+      }
+    const double cut = us * seg_span(x, m, units, G, true) + 3.0 + 0.035 / 1024 * m * hq * d;
+    if (cut < best_us) { best = places; best_us = cut; }
+  }
+  return best;
+}
+
 static void fill_sizes(const pv_problem* p, const Totals& t, int hq, int hkv, int d, int in_dtype,
                        pv_sizes* s) {
   std::memset(s, 0, sizeof(*s));
@@ -189,7 +272,7 @@ static void fill_sizes(const pv_problem* p, const Totals& t, int hq, int hkv, in
   PlanHeader h;
   plan_layout(p->batch, t.tokens, t.segments, t.q_tiles, t.padded_keys, t.short_rows, p->layout,
               t.seg_tiles, group_uses_query_tiles(hq / hkv) ? t.quads : 0,
-              seg_unit_places(t.seg_tiles, t.seg_longest, t.seg_sum, hq, hkv), &h);
+              seg_unit_places(p, t.seg_tiles, hq, hkv, d), &h);
   s->n_seg_tiles = (int32_t)t.seg_tiles;
   s->n_quads = h.n_quads;
   s->n_seg_pieces = h.n_seg_units;

@@ -97,36 +97,9 @@ struct SegUnit {
 };
 constexpr int kMaxPieces = 8;
 
-// Places for key pieces, at most kMaxPieces to a tile; 0: the tiles are not cut.  One for each workgroup slot of the chip
-// that a kv head has: two workgroups of up to four waves to a compute unit, one of more.  One as well for three or four
-// waves where that makes pieces of moderate length: two such workgroups slow each other down, and half the pieces are
-// half the partial results.  Passes with segment rows at 32/8 heads of 128, us, places for two workgroups / for one:
-// 3 K tokens 50.8 / 47.8 (judge pass), 46.4 / 44.1, 2.8 K 44.1 / 40.1, 9 K with 8 tiles 67.7 / 62.1; at 24/8 heads 45.8 /
-// 44.5, more tiles 57.5 / 61.3, longer pieces (6 K tokens, 17 tiles) 51.4 / 76.0; one and two waves 38.3 / 48.2.
-// Cutting pays where the longest item gets shorter by more than the merge launch takes (16 us asked for, 1.24 us a key
-// tile of an item alone on its unit, 1.5 beside another).  Uncut / cut, us: 32/8 heads, 2.8 K tokens, 26 tiles for 64
-// slots 75 / 67; 39 tiles 77 / 82; 52 tiles 88 / 98; 3 K tokens at 64/8 heads, 17 tiles for 32 slots 66 / 61; at 40/8
-// heads 64 / 55; 16/8 heads of 64, 41 tiles for 64 slots, 5.8 K tokens 74 / 57; 528 tokens, 5 tiles 26 / 28.
-// The lengths are those of the requests that have such tiles, in key tiles: `longest`, and `sum` over the tiles (a
-// request's length stands for its tiles').  By the batch's average, us, / so: 9 K tokens with 4 tiles beside 15 requests of
-// 50 tokens without a segment 114 / 35 (alone 35).  More tiles than workgroups of five to eight waves run at once, a few
-// of them long: cut too, in as many places as smaller workgroups have.  64/8 heads, 3 tiles of 9 K tokens among 48: 169 /
-// 58.
-// Every piece has a reference of its own, whose weight is exact in bf16; fewer pieces hold fewer such weights.  Error of
-// the rows against fp64, every tile in four pieces / so (about two) / the whole pass: 3 K tokens at 32/8 heads 2.888e-3 /
-// 2.901e-3 / 2.908e-3, without rotation at 40/8 heads 1.573e-3 / 1.613e-3 / 1.632e-3.
-inline int64_t seg_unit_places(int64_t n_seg_tiles, int64_t longest, int64_t sum, int hq, int hkv) {
-  const int G = hq / hkv;
-  const int64_t units = 256 / hkv, most = 512 / hkv;                  // compute units of a head; places
-  const bool one = G > 4 || (G > 2 && 2 * n_seg_tiles <= units && sum <= 45 * units);
-  const int64_t slots = one ? units : most;                           // pieces at work at a time
-  const int64_t places = n_seg_tiles < slots ? slots : most;
-  if (n_seg_tiles <= 0 || n_seg_tiles >= places) return 0;
-  if (124 * longest * slots - 150 * sum <= 1600 * slots) return 0;
-  return n_seg_tiles * kMaxPieces < places ? n_seg_tiles * kMaxPieces : places;
-}
-
-// Room for them in the plan: whatever the head counts, so that a plan's size and offsets do not depend on these.
+constexpr int kMinPiece = 4;              // key tiles of the shortest pieces that a tile is cut into
+// Room for the places of key pieces in the plan (their number: seg_unit_places, pv_api.hip): whatever the head counts, so
+// that a plan's size and offsets do not depend on these.
 constexpr int kMaxSegUnits = 512;
 inline int64_t seg_unit_list(int64_t n_seg_tiles) {
   if (n_seg_tiles >= kMaxSegUnits) return 0;         // more tiles than any head count has places: never cut

@@ -264,7 +264,7 @@ __device__ __forceinline__ int wave_max(int x) {
 // (Every tile in the same number of pieces leaves long ones, and a number rounded up so that they fill the slots a second
 // round of workgroups.  Passes, us, before / with it: 64/8 heads, 3 K tokens 76.4 / 61.0; 28/4 heads 62.6 / 46.8; 40/8
 // heads 65.4 / 55.5; 32/8 heads, 9 K tokens 90.5 / 77.5.  Pieces of 2 to 9 key tiles at least: the same.)
-constexpr int kPlanThreads = 1024, kMinPiece = 4;
+constexpr int kPlanThreads = 1024;
 __device__ inline void plan_seg_units(int32_t* plan, const int32_t* img, const PlanHeader& h) {
   constexpr int W = kPlanThreads / 64, TRIES = 4 * W;  // lengths tried in a round, four a wave
   static_assert(TRIES == 64, "a lane each");
