@@ -54,6 +54,14 @@ def test_a_long_judged_request_beside_short_ones(short, n, hq, hkv):
         assert s.n_seg_pieces == 0
 
 
+@pytest.mark.parametrize("hq,hkv", HEADS)
+@pytest.mark.parametrize("s", [17, 32])
+def test_keys_behind_the_boundaries_do_not_count(s, hq, hkv):
+    early, late = (wl.Problem([24], [9000], [4], [s], [b]) for b in ([10, 20, 30, 40], [10, 20, 30, 9000]))
+    assert sizes(early, hq, hkv).n_seg_pieces == 0        # two key tiles each
+    assert sizes(late, hq, hkv).n_seg_pieces > 0
+
+
 @pytest.mark.parametrize("change", [1, -1, 512])
 def test_a_number_out_of_range_is_refused(change):
     s = sizes(batch(JUDGED[0]), 32, 8)
