@@ -116,10 +116,11 @@ pv_status pv_query_sizes(const pv_problem* problem, int32_t n_q_heads, int32_t n
  * longest first.
  *   problem         host, validated again here
  *   plan_dev        device, >= sizes->plan_bytes, 16-byte aligned; opaque, position independent
- *                   The head counts of `sizes` reach it through n_quads only: it also serves calls
- *                   whose sizes come from the same problem with other head counts (layers of
- *                   different widths), the segment-only ones always, the others if n_quads is the
- *                   same or 0 in their sizes.
+ *                   The head counts of `sizes` reach it through n_quads and n_seg_pieces only: it
+ *                   also serves calls whose sizes come from the same problem with other head counts
+ *                   (layers of different widths), the segment-only ones always (with another
+ *                   n_seg_pieces they cut every tile alike), the others if n_quads is the same or 0
+ *                   in their sizes.
  *   dense_mask_dev  device or NULL.  If given, also writes the mask entry by entry (uint8 0/1,
  *                   request b at byte offset sum_{b'<b} N_b'^2, row-major [N_b][N_b]); meant
  *                   for tests, sizes->dense_mask_bytes bytes. */
